@@ -102,6 +102,46 @@ nbody_status forward_run(int variant, const Device &dev, const float *x, const f
                          const LfEpi *epi = nullptr, bool *fused = nullptr,
                          const Arena &arena = Arena{});
 
+// Row-group forward kernel (one workgroup per group of rows, every ordered
+// pair, one launch, no partial sums); the rows per group are a multiple of
+// `least`.
+nbody_status forward_rows_run(int least, const char *name, const Device &dev, const float *x,
+                              const float *m, int n, float eps2, float *a, float *p,
+                              hipStream_t stream);
+
+// Sizes at which the one-wave two-row pair-once variants run the row-group
+// kernel instead: the pair-once grid is then one underfilled round of
+// workgroups and a fold of 4-5 us follows it.  Whole calls with the
+// potential, pair-once against row groups: 16.5 / 9.2 us at 4,500 bodies,
+// 20.7 / 13.7 at 6,001, 25.7 / 19.9 at 7,500, 38.4 / 32.5 at 10,000, 46.5 /
+// 44.5 at 12,000, 57.7 / 59.1 at 14,000.  Below 4,500 the default variants
+// are row groups by themselves.
+constexpr int kRowBandBegin = 4500, kRowBandEnd = 12000;
+inline bool row_band(int n) { return n >= kRowBandBegin && n < kRowBandEnd; }
+
+// Rows per group K (a multiple of `least`, at most `most`) for n rows on
+// num_cu CUs: the K with the least estimated time.  A workgroup's four waves
+// take one SIMD each, so a CU holding w workgroups needs time in proportion
+// to w (K + 0.5) per j-tile (half a row's worth for loads and loop), and its
+// start and final sums grow with K (0.3).  Measured at 5,000 bodies: K = 2..8
+// (w = 10, 7, 5, 4, 4, 3, 3) take 11.4, 10.7, 10.3, 10.5, 11.8, 11.1, 12.2 us;
+// the estimate picks 5.
+inline int row_group_rows(int n, int num_cu, int least, int most)
+{
+    int best = least;
+    int64_t cost = INT64_MAX;
+    for (int k = least; k <= most; k += least) {
+        const int64_t groups = ((int64_t)n + k - 1) / k;
+        const int64_t w = (groups + num_cu - 1) / num_cu;
+        const int64_t c = w * (10 * k + 5) + 3 * k;
+        if (c < cost) {
+            cost = c;
+            best = k;
+        }
+    }
+    return best;
+}
+
 // Pair-once forward kernel (forward_sym.hip) with W waves and K rows/lane.
 nbody_status forward_sym_run(int W, int K, int occ, int rounds, const char *name,
                              const Device &dev, const float *x, const float *m, int n, float eps2,

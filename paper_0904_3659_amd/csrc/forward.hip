@@ -328,15 +328,22 @@ __global__ __launch_bounds__(W * 64) void forward_la_kernel(LaArgs P)
 }
 
 // ---------------------------------------------------------------------------
-// Row-per-wave kernel for the smallest n (up to a few thousand bodies),
-// where one call costs launch latency plus its longest chain of dependent
-// steps rather than pairs.  Wave w owns rows [K w, K w + K): their
-// positions are the same for every lane (scalar registers) and lane l sums
-// j = l, l + 64, l + 128, ... for all K rows.  The 64 lane sums of a row
-// are then added by a fixed butterfly (DPP within rows of 16 lanes, then
-// two lane swaps), so every lane ends with the same, bitwise reproducible
-// total.  No LDS tile, no partials, no ticket and no second launch: at
-// n = 1,024 with K = 1 the 1,024 waves give every SIMD of the chip one.
+// Row-group kernel for small and middle n, where the pairs are too few for
+// the pair-once kernel's partial sums and fold to pay.  A workgroup of four
+// waves owns K rows; their positions are the same for every lane, and the
+// lanes of wave w meet the j of the 64-particle tiles w, w + 4, w + 8, ...
+// for all K rows, D tiles loaded ahead.  The lane sums are added by halvings
+// that four sums share (wave_sum4), the four waves' sums in wave order
+// through LDS.  One launch, no partials, bitwise reproducible.
+//
+// Bound by VALU issue: 14 operations per ordered pair, 41 cycles per 64 pairs
+// and SIMD at 16,384 bodies with K = 8 (36 if every pair of operations of two
+// waves issued together), below 5,000 bodies by the launch and the depth of
+// one load, one short loop and the sums.  K trades loads per pair against
+// workgroups to fill the CUs with (row_group_rows).  Per call, one row (two
+// from 3,000 bodies) per wave before: 4.9 -> 4.0 us at 2,000 bodies, 8.1 ->
+// 5.9 at 3,000, 10.1 -> 7.8 at 4,096; against the pair-once kernel and its
+// fold see kRowBandEnd.
 struct RowArgs {
     const float *x;
     const float *m;
@@ -346,57 +353,116 @@ struct RowArgs {
     float *p;
 };
 
-template <int K>
+constexpr int kRowMax = 8;  // rows per group
+
+// One tile of 64 particles (q of this lane) for K rows; MASKED: lanes whose
+// particle is a row itself, or past n, take r = 0.
+template <int K, bool POT, bool MASKED>
+__device__ __forceinline__ void row_tile(const float (&xi)[K], const float (&yi)[K],
+                                         const float (&zi)[K], float4 q, float eps2, int j, int i0,
+                                         int n, float (&acc)[K][4])
+{
+    float dx[K], dy[K], dz[K], r[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        dx[k] = xi[k] - q.x;
+        dy[k] = yi[k] - q.y;
+        dz[k] = zi[k] - q.z;
+        float s = __builtin_fmaf(dx[k], dx[k], eps2);
+        s = __builtin_fmaf(dy[k], dy[k], s);
+        r[k] = __builtin_fmaf(dz[k], dz[k], s);
+    }
+    rsq_group<K>(r);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (MASKED && (j == i0 + k || j >= n)) r[k] = 0.0f;
+        const float mr = q.w * r[k];
+        const float mr3 = mr * (r[k] * r[k]);
+        if (POT) acc[k][3] += mr;
+        acc[k][0] = __builtin_fmaf(mr3, dx[k], acc[k][0]);
+        acc[k][1] = __builtin_fmaf(mr3, dy[k], acc[k][1]);
+        acc[k][2] = __builtin_fmaf(mr3, dz[k], acc[k][2]);
+    }
+}
+
+template <int K, bool POT>
 __global__ __launch_bounds__(256) void forward_row_kernel(RowArgs P)
 {
+    constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
+    __shared__ float red[4][4 * K];
     const int n = P.n;
-    const float eps2 = P.eps2;
     const int lane = threadIdx.x & 63;
-    const int i0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6))) * K;
-    if (i0 >= n) return;  // the whole wave: no barrier follows
-    float xi[K], yi[K], zi[K], ax[K], ay[K], az[K], ap[K];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int i0 = blockIdx.x * K;
+    float eps2 = P.eps2;
+    in_vgpr(eps2);
+    float xi[K], yi[K], zi[K], acc[K][4];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int ik = min(i0 + k, n - 1);  // rows past n are computed, not stored
         xi[k] = P.x[3 * ik];
         yi[k] = P.x[3 * ik + 1];
         zi[k] = P.x[3 * ik + 2];
-        ax[k] = ay[k] = az[k] = ap[k] = 0.f;
+        in_vgpr(xi[k]);
+        in_vgpr(yi[k]);
+        in_vgpr(zi[k]);
+        acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
     }
-#pragma unroll 4
-    for (int j = lane; j < n; j += 64) {
-        const float4 q = make_float4(P.x[3 * j], P.x[3 * j + 1], P.x[3 * j + 2], P.m[j]);
+    // x and m as buffers of their exact sizes: a load past the end gives zero,
+    // so the loads ahead need no clamp
+    const auto bx = make_buffer(P.x, 12u * (unsigned)n), bm = make_buffer(P.m, 4u * (unsigned)n);
+    const auto load = [&](int t) { return load_xm(bx, bm, (unsigned)(t * 64 + lane)); };
+    const int full = n >> 6;  // tiles without particles past n
+    // The tiles that hold a row of the group, and the ragged last one, are met
+    // first, with the pairs to leave out masked; the main loop passes them by
+    // (one masked or unmasked body in the loop alone keeps its sums in place).
+    const int self0 = i0 >> 6, self1 = min(i0 + K - 1, n - 1) >> 6;
+    float4 q[D];
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            pair_term_masked(xi[k], yi[k], zi[k], q, eps2, j == i0 + k, ax[k], ay[k], az[k], ap[k]);
+    for (int d = 0; d < D; ++d) q[d] = load(wv + 4 * d);
+    for (int t = self0; t <= self1; ++t)
+        if ((t & 3) == wv)
+            row_tile<K, POT, true>(xi, yi, zi, load(t), eps2, t * 64 + lane, i0, n, acc);
+    if ((n & 63) != 0 && (full & 3) == wv && full > self1)
+        row_tile<K, POT, true>(xi, yi, zi, load(full), eps2, full * 64 + lane, i0, n, acc);
+    for (int t0 = wv; t0 < full; t0 += 4 * D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int t = t0 + 4 * d;
+            if (t < full && (t < self0 || t > self1))
+                row_tile<K, POT, false>(xi, yi, zi, q[d], eps2, 0, 0, 0, acc);
+            q[d] = load(t + 4 * D);
+        }
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        ax[k] = wave_sum(ax[k]);
-        ay[k] = wave_sum(ay[k]);
-        az[k] = wave_sum(az[k]);
-        ap[k] = wave_sum(ap[k]);
+        const float s = wave_sum4(acc[k]);
+        if ((lane & 15) == 0) red[wv][4 * k + quad_of_row(lane >> 4)] = s;
     }
-    // lane k stores row i0 + k
-    float sx = ax[0], sy = ay[0], sz = az[0], sp = ap[0];
+    __syncthreads();
+    // thread 4 k + c stores component c of row i0 + k (c == 3: the potential)
+    const int k = threadIdx.x >> 2, c = threadIdx.x & 3;
+    if (k >= K || i0 + k >= n) return;
+    float s = red[0][threadIdx.x];
 #pragma unroll
-    for (int k = 1; k < K; ++k)
-        if (lane == k) {
-            sx = ax[k];
-            sy = ay[k];
-            sz = az[k];
-            sp = ap[k];
-        }
-    const int i = i0 + lane;
-    if (lane < K && i < n) {
-        P.a[3 * i + 0] = sx;
-        P.a[3 * i + 1] = sy;
-        P.a[3 * i + 2] = sz;
-        if (P.p) P.p[i] = sp;
-    }
+    for (int w = 1; w < 4; ++w) s += red[w][threadIdx.x];
+    if (c < 3)
+        P.a[3 * (i0 + k) + c] = s;
+    else if (POT)
+        P.p[i0 + k] = s;
 }
 
-using RowFn = void (*)(RowArgs);
+template <int K>
+static void launch_rows(const RowArgs &P, hipStream_t stream)
+{
+    const dim3 grid((unsigned)((P.n + K - 1) / K));
+    if (P.p)
+        hipLaunchKernelGGL((forward_row_kernel<K, true>), grid, dim3(256), 0, stream, P);
+    else
+        hipLaunchKernelGGL((forward_row_kernel<K, false>), grid, dim3(256), 0, stream, P);
+}
+
+using RowFn = void (*)(const RowArgs &, hipStream_t);
 
 using LaFn = void (*)(LaArgs);
 
@@ -414,7 +480,7 @@ struct Variant {
     int la_w;
     bool d64;     // float64 running sums (forward_kernel's D64)
     bool la_one;  // one-launch kernel with a single split: no partials, no ticket
-    RowFn row;    // row-per-wave kernel (K = row_k rows per wave)
+    bool row;     // row-group kernel, groups of a multiple of row_k rows
     int row_k;
 };
 
@@ -430,7 +496,7 @@ struct Variant {
 // The same kernel with one split: the W waves of a row block's workgroup
 // share all of j, and their wave-ordered sum is the result.
 #define FWD_LA1_VARIANT(W) {"fwd_la1_w" #W, 64, 1, 0, nullptr, nullptr, 0, 0, 0, 1, forward_la_kernel<W>, W, false, true}
-#define FWD_ROW_VARIANT(K) {"fwd_row_k" #K, 64, K, 0, nullptr, nullptr, 0, 0, 0, 1, nullptr, 0, false, false, forward_row_kernel<K>, K}
+#define FWD_ROW_VARIANT(K) {"fwd_row_k" #K, 64, K, 0, nullptr, nullptr, 0, 0, 0, 1, nullptr, 0, false, false, true, K}
 
 const Variant kVariants[] = {
     // The paper's three GPU programs as (rows per lane K, j-unroll U):
@@ -537,17 +603,9 @@ int forward_default_variant(int64_t n)
     // one-wave blocks of 128 particles: twice the workgroups of 256-particle
     // blocks, which evens out the one round of workgroups these sizes fill
     // (3-17% faster from 3,000 to 10,000 bodies)
-    // Small n is set by launch latency and the longest dependent chain: one
-    // wave per row (two rows from 3,000 bodies), no LDS, no second launch.
-    // Kernel 3.4 us at 1,024 bodies against 7.1 us for the one-launch split
-    // gather.  Against the pair-once kernel and its fold (forced variants,
-    // same box) the row kernel leads up to 4,000 bodies (plain calls 17.3
-    // against 20.6 us, leap-frog steps 13.9 against 16.4 us), is level with
-    // it for plain calls with the potential at 4,500 and behind from 5,000
-    // (22.5 against 22.0 us); a leap-frog step, whose update the pair-once
-    // fold applies in place and the row kernel needs a launch for, is 6-14%
-    // faster pair-once from 4,500 to 5,000.  Both use one choice, so that a
-    // leap-frog call stays bitwise the composed calls.
+    // Small n: the row-group kernel (an even number of rows per group from
+    // 3,000 bodies), which also serves the two-row one-wave variants below
+    // kRowBandEnd; their names keep the pair-once geometry they have above it.
     if (n >= 4500) return pair_once_small;
     return n >= 3000 ? row_2 : row_1;
 }
@@ -641,7 +699,7 @@ nbody_status forward_variant_occupancy(int variant, int *per_cu)
     hipError_t e;
     if (V.sym_w) return forward_sym_occupancy(V.sym_w, V.sym_k, per_cu);
     if (V.row)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.row, 256, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, forward_row_kernel<kRowMax, true>, 256, 0);
     else if (V.la_w)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.la, V.la_w * 64, 0);
     else
@@ -651,21 +709,29 @@ nbody_status forward_variant_occupancy(int variant, int *per_cu)
     return NBODY_OK;
 }
 
+const RowFn kRowLaunch[kRowMax + 1] = {nullptr, launch_rows<1>, launch_rows<2>, launch_rows<3>,
+                                       launch_rows<4>, launch_rows<5>, launch_rows<6>,
+                                       launch_rows<7>, launch_rows<8>};
+
+nbody_status forward_rows_run(int least, const char *name, const Device &dev, const float *x,
+                              const float *m, int n, float eps2, float *a, float *p,
+                              hipStream_t stream)
+{
+    RowArgs P{x, m, n, eps2, a, p};
+    if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
+    prof_mark(stream, 0);
+    kRowLaunch[row_group_rows(n, dev.num_cu, least, kRowMax)](P, stream);
+    prof_mark(stream, 1);
+    return check_launch(name);
+}
+
 nbody_status forward_run(int variant, const Device &dev, const float *x, const float *m, int n,
                          float eps2, float *a, float *p, hipStream_t stream, const LfEpi *epi,
                          bool *fused, const Arena &arena)
 {
     const Variant &V = kVariants[variant];
     if (fused) *fused = false;
-    if (V.row) {
-        const int64_t waves = ((int64_t)n + V.row_k - 1) / V.row_k;
-        RowArgs P{x, m, n, eps2, a, p};
-        if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
-        prof_mark(stream, 0);
-        hipLaunchKernelGGL(V.row, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, P);
-        prof_mark(stream, 1);
-        return check_launch(V.name);
-    }
+    if (V.row) return forward_rows_run(V.row_k, V.name, dev, x, m, n, eps2, a, p, stream);
     if (V.la_w) {
         const int rb = (n + 63) / 64;
         int splits = 1, chunk = 0;

@@ -57,6 +57,10 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     void *ws = nullptr;
     nbody_status st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
+    if constexpr (W == 1 && K == 2)
+        // the plan and its workspace stay the variant's, whichever kernel runs
+        if (row_band(n))
+            return forward_rows_run(1, name, dev, x, m, n, eps2, a, p, stream);
     float4 *partial = static_cast<float4 *>(ws);
     double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
                                 : nullptr;

@@ -1,5 +1,5 @@
-// Sum over the 64 lanes of a wave in a fixed order, for the row-per-wave
-// kernels of the smallest n.
+// Sum over the 64 lanes of a wave in a fixed order, for the row-group
+// and row-per-wave kernels of small n.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,5 +26,38 @@ __device__ __forceinline__ float wave_sum(float v)
     v += __shfl_xor(v, 32, 64);
     return v;
 }
+
+// The other half of a pair of registers: lanes 32..63 of a and lanes 0..31 of
+// b change places (v_permlane32_swap_b32), then rows 1, 3 of a and rows 0, 2
+// of b (v_permlane16_swap_b32; a row is 16 lanes).
+__device__ __forceinline__ float swap32_add(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a),
+                                                    __builtin_bit_cast(unsigned, b), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+__device__ __forceinline__ float swap16_add(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a),
+                                                    __builtin_bit_cast(unsigned, b), false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// Sums of four values over the 64 lanes, in a fixed order: row g of 16 lanes
+// ends with the total of v[quad_of_row(g)] in every lane.  Four values share
+// the first two halvings, so they take 9 cross-lane steps instead of 24.
+__device__ __forceinline__ float wave_sum4(const float (&v)[4])
+{
+    float s = swap16_add(swap32_add(v[0], v[1]), swap32_add(v[2], v[3]));
+    s = dpp_swap_add<0xB1>(s);
+    s = dpp_swap_add<0x4E>(s);
+    s = dpp_swap_add<0x141>(s);
+    s = dpp_swap_add<0x140>(s);
+    return s;
+}
+
+// Which of the four values row g (lane / 16) of wave_sum4 holds: 0, 2, 1, 3.
+__device__ __forceinline__ int quad_of_row(int g) { return ((g & 1) << 1) | (g >> 1); }
 
 }  // namespace nbody
