@@ -212,62 +212,180 @@ __global__ __launch_bounds__(BLOCK) void backward_kernel(BwdArgs P)
     }
 }
 
-// Row-per-wave adjoint for the smallest n, where launch latency and the
-// longest dependent chain set the time: wave w owns rows [K w, K w + K)
-// (the same for every lane), lane l gathers j = l, l + 64, ... into each
-// row's sums A, B, C, G, and a fixed butterfly adds the 64 lane sums
-// (bitwise reproducible).  One launch, no LDS, no partials.
-template <int K>
+// Row-group adjoint for small and middle n, as the forward's row groups: a
+// workgroup of four waves owns K rows (the same in every lane), wave w meets
+// the 64-particle tiles w, w + 4, ... with both its particles (x, m) and
+// their weights (w, v) loaded ahead, and gathers the row sums A, B, C, G;
+// eight sums per row are added by shared halvings and over the waves in
+// order.  One launch, no partials, bitwise reproducible.  HAS_V false: no
+// potential weights, whose terms are not formed (bitwise the result of zero
+// weights).
+//
+// Bound by VALU issue (30 operations per ordered pair, 27 without potential
+// weights): 92 cycles per 64 pairs and SIMD at 16,384 bodies with K = 4, about
+// 10 of them the loads.  Per call with potential weights, one row per wave
+// before: 7.4 -> 6.2 us at 2,000 bodies, 11.8 -> 8.9 at 2,500, 13.4 -> 9.6 at
+// 3,000.
+constexpr int kBwdRowMax = 4;  // rows per group
+
+// One tile of 64 particles (q, wq of this lane) for K rows, with the opposite
+// difference e = x_j - x_k = -d, so that every term below is a plain product
+// or accumulating FMA (two-operand encodings; a negated operand would need
+// the longer one, which issues slower): with
+//     3 c . e = (3 m_j) (w_k . e) + (-3 m_k) (w_j . e)
+//     u = r^3 (r^2 (3 c . e) + b') = -r^3 (3 r^2 (c . d) - b'),  b' = -b
+// the sums are A, B, G += r v_j + r^3 (w_j . e) and C += u e
+// (u e = r^3 (3 r^2 (c . d) + b) d).  MASKED: lanes whose particle is a row
+// itself, or past n, take r = 0.
+template <int K, bool HAS_V, bool MASKED>
+__device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4 (&wk)[K],
+                                             const float (&m3)[K], const float (&mn)[K], float4 q,
+                                             float4 wq, float eps2, int j, int i0, int n,
+                                             RowAcc (&acc)[K])
+{
+    float ex[K], ey[K], ez[K], rr[K];
+    const float q3 = 3.0f * q.w;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        ex[k] = q.x - xk[k].x;
+        ey[k] = q.y - xk[k].y;
+        ez[k] = q.z - xk[k].z;
+        float s = __builtin_fmaf(ex[k], ex[k], eps2);
+        s = __builtin_fmaf(ey[k], ey[k], s);
+        rr[k] = __builtin_fmaf(ez[k], ez[k], s);
+    }
+    rsq_group<K>(rr);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (MASKED && (j == i0 + k || j >= n)) rr[k] = 0.0f;
+        const float r = rr[k];
+        const float r2 = r * r;
+        const float r3 = r * r2;
+        RowAcc &t = acc[k];
+        t.A = __builtin_fmaf(q.w, r3, t.A);
+        t.Bx = __builtin_fmaf(r3, wq.x, t.Bx);
+        t.By = __builtin_fmaf(r3, wq.y, t.By);
+        t.Bz = __builtin_fmaf(r3, wq.z, t.Bz);
+        float wke = wk[k].x * ex[k];
+        wke = __builtin_fmaf(wk[k].y, ey[k], wke);
+        wke = __builtin_fmaf(wk[k].z, ez[k], wke);
+        float wje = wq.x * ex[k];
+        wje = __builtin_fmaf(wq.y, ey[k], wje);
+        wje = __builtin_fmaf(wq.z, ez[k], wje);
+        const float c3 = __builtin_fmaf(q3, wke, m3[k] * wje);
+        // mn = -m_k, wk.w = -v_k here
+        const float e = HAS_V ? __builtin_fmaf(r2, c3, __builtin_fmaf(mn[k], wq.w, q.w * wk[k].w))
+                              : r2 * c3;
+        const float u = r3 * e;
+        t.Cx = __builtin_fmaf(u, ex[k], t.Cx);
+        t.Cy = __builtin_fmaf(u, ey[k], t.Cy);
+        t.Cz = __builtin_fmaf(u, ez[k], t.Cz);
+        if (HAS_V) t.G = __builtin_fmaf(r, wq.w, t.G);
+        t.G = __builtin_fmaf(r3, wje, t.G);
+    }
+}
+
+template <int K, bool HAS_V>
 __global__ __launch_bounds__(256) void backward_row_kernel(BwdArgs P)
 {
+    constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
+    __shared__ float red[4][8 * K];
     const int n = P.n;
-    const float eps2 = P.eps2;
     const int lane = threadIdx.x & 63;
-    const int i0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6))) * K;
-    if (i0 >= n) return;  // the whole wave: no barrier follows
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int i0 = blockIdx.x * K;
+    float eps2 = P.eps2;
+    in_vgpr(eps2);
+    const auto bx = make_buffer(P.x, 12u * (unsigned)n), bm = make_buffer(P.m, 4u * (unsigned)n);
+    // an absent weight array is an empty buffer: its loads give zero
+    const auto bw = make_buffer(P.ga, P.ga ? 12u * (unsigned)n : 0u);
+    const auto bv = make_buffer(P.gp, P.gp ? 4u * (unsigned)n : 0u);
+    const auto weights = [&](unsigned j) {
+        float4 v = buffer_xm(bw, bv, j);
+        if (!HAS_V) v.w = 0.f;
+        return v;
+    };
     float4 xk[K], wk[K];
+    float m3[K], mn[K];  // -3 m_k, -m_k
     RowAcc acc[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int ic = min(i0 + k, n - 1);  // rows past n are computed, not stored
-        xk[k] = load_xm(P, ic);
-        wk[k] = load_wv(P, ic);
+        const unsigned ic = (unsigned)min(i0 + k, n - 1);  // rows past n are computed, not stored
+        xk[k] = buffer_xm(bx, bm, ic);
+        wk[k] = weights(ic);
+        wk[k].w = -wk[k].w;
+        mn[k] = -xk[k].w;
+        m3[k] = 3.0f * mn[k];
         zero(acc[k]);
     }
-#pragma unroll 2
-    for (int j = lane; j < n; j += 64) {
-        const float4 q = load_xm(P, j);
-        const float4 wq = load_wv(P, j);
+    const int full = n >> 6;  // tiles without particles past n
+    const int self0 = i0 >> 6, self1 = min(i0 + K - 1, n - 1) >> 6;
+    float4 q[D], wq[D];
+    const auto load = [&](int t, float4 &a, float4 &b) {
+        const unsigned j = (unsigned)(t * 64 + lane);
+        a = buffer_xm(bx, bm, j);
+        b = weights(j);
+    };
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            adj_term(xk[k].x, xk[k].y, xk[k].z, xk[k].w, wk[k].x, wk[k].y, wk[k].z, wk[k].w, q,
-                     wq, eps2, j == i0 + k, acc[k]);
+    for (int d = 0; d < D; ++d) load(wv + 4 * d, q[d], wq[d]);
+    const auto masked = [&](int t) {
+        float4 a, b;
+        load(t, a, b);
+        adj_row_tile<K, HAS_V, true>(xk, wk, m3, mn, a, b, eps2, t * 64 + lane, i0, n, acc);
+    };
+    // the tiles with pairs to leave out first, as in the forward kernel
+    for (int t = self0; t <= self1; ++t)
+        if ((t & 3) == wv) masked(t);
+    if ((n & 63) != 0 && (full & 3) == wv && full > self1) masked(full);
+    for (int t0 = wv; t0 < full; t0 += 4 * D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int t = t0 + 4 * d;
+            if (t < full && (t < self0 || t > self1))
+                adj_row_tile<K, HAS_V, false>(xk, wk, m3, mn, q[d], wq[d], eps2, 0, 0, 0, acc);
+            load(t + 4 * D, q[d], wq[d]);
+        }
     }
-    float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        RowAcc c = acc[k];
-        c.A = wave_sum(c.A);
-        c.Bx = wave_sum(c.Bx);
-        c.By = wave_sum(c.By);
-        c.Bz = wave_sum(c.Bz);
-        c.Cx = wave_sum(c.Cx);
-        c.Cy = wave_sum(c.Cy);
-        c.Cz = wave_sum(c.Cz);
-        c.G = wave_sum(c.G);
-        // dL/dx_k = w_k A - m_k B - C
-        const float4 g = make_float4(wk[k].x * c.A - xk[k].w * c.Bx - c.Cx,
-                                     wk[k].y * c.A - xk[k].w * c.By - c.Cy,
-                                     wk[k].z * c.A - xk[k].w * c.Bz - c.Cz, c.G);
-        if (lane == k) out = g;  // lane k stores row i0 + k
+        const float u[4] = {acc[k].A, acc[k].Bx, acc[k].By, acc[k].Bz};
+        const float v[4] = {acc[k].G, acc[k].Cx, acc[k].Cy, acc[k].Cz};
+        const float su = wave_sum4(u), sv = wave_sum4(v);
+        if ((lane & 15) == 0) {
+            red[wv][8 * k + quad_of_row(lane >> 4)] = su;
+            red[wv][8 * k + 4 + quad_of_row(lane >> 4)] = sv;
+        }
     }
-    const int i = i0 + lane;
-    if (lane < K && i < n) {
-        P.gx[3 * i + 0] = out.x;
-        P.gx[3 * i + 1] = out.y;
-        P.gx[3 * i + 2] = out.z;
-        if (P.gm) P.gm[i] = out.w;
+    __syncthreads();
+    // thread 4 k + c stores component c of row i0 + k (c == 3: dL/dm)
+    const int k = threadIdx.x >> 2, c = threadIdx.x & 3;
+    const int i = i0 + k;
+    if (k >= K || i >= n) return;
+    const auto total = [&](int e) {
+        float s = red[0][8 * k + e];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) s += red[w][8 * k + e];
+        return s;
+    };
+    if (c == 3) {
+        if (P.gm) P.gm[i] = total(4);
+        return;
     }
+    // dL/dx_k = w_k A - m_k B - C
+    const float w = P.ga ? P.ga[3 * (size_t)i + c] : 0.f;
+    P.gx[3 * (size_t)i + c] = w * total(0) - P.m[i] * total(1 + c) - total(5 + c);
+}
+
+using RowFn = void (*)(const BwdArgs &, hipStream_t);
+
+template <int K>
+static void launch_bwd_rows(const BwdArgs &P, hipStream_t stream)
+{
+    const dim3 grid((unsigned)((P.n + K - 1) / K));
+    if (P.gp)
+        hipLaunchKernelGGL((backward_row_kernel<K, true>), grid, dim3(256), 0, stream, P);
+    else
+        hipLaunchKernelGGL((backward_row_kernel<K, false>), grid, dim3(256), 0, stream, P);
 }
 
 __global__ __launch_bounds__(256) void backward_reduce_kernel(const float4 *__restrict__ partial,
@@ -678,6 +796,29 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
         if (kk[k] < n) A.partial[(size_t)c * n + kk[k]] = acc[k];
 }
 
+// Sizes at which the two-wave step-split pair-once variants run the row-group
+// kernel instead (as kRowBandEnd of the forward).  Whole calls with / without
+// potential weights, pair-once against row groups: 21.1 / 20.4 and 14.6 / 13.2
+// us at 4,096 bodies, 24.1 / 23.3 and 20.5 / 18.8 at 5,000, 29.9 / 28.8 and
+// 27.3 / 24.9 at 6,001, 31.8 / 30.3 and 33.0 / 30.4 at 6,500.
+constexpr int kBwdRowBandBegin = 4000, kBwdRowBandEnd = 6200;
+bool bwd_row_band(int n) { return n >= kBwdRowBandBegin && n < kBwdRowBandEnd; }
+
+const RowFn kRowLaunch[kBwdRowMax + 1] = {nullptr, launch_bwd_rows<1>, launch_bwd_rows<2>,
+                                          launch_bwd_rows<3>, launch_bwd_rows<4>};
+
+nbody_status backward_rows_run(int least, const char *name, const Device &dev, const float *x,
+                               const float *m, int n, float eps2, const float *ga, const float *gp,
+                               float *gx, float *gm, hipStream_t stream)
+{
+    BwdArgs P{x, m, ga, gp, n, eps2, 0, nullptr, gx, gm};
+    if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
+    prof_mark(stream, 0);
+    kRowLaunch[row_group_rows(n, dev.num_cu, least, kBwdRowMax, 10)](P, stream);
+    prof_mark(stream, 1);
+    return check_launch(name);
+}
+
 // OCC divides the chunk count and ROUNDS multiplies it (as in the
 // pair-once forward kernel); S splits each tile's steps between the waves.
 template <int W, int K, int OCC, int ROUNDS = 1, int S = 1>
@@ -701,6 +842,10 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     void *ws = nullptr;
     nbody_status st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
+    if constexpr (S == 2 && K == 2)
+        // the plan and its workspace stay the variant's, whichever kernel runs
+        if (bwd_row_band(n))
+            return backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm, stream);
     float4 *partial = static_cast<float4 *>(ws);
     double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
                                 : nullptr;
@@ -752,7 +897,7 @@ struct Variant {
     SymRunFn sym;
     SymKernelFn sym_kernel;
     int sym_w, sym_k, sym_occ, sym_rounds;
-    KernelFn row;  // row-per-wave kernel (K = row_k rows per wave)
+    bool row;      // row-group kernel, groups of a multiple of row_k rows
     int row_k;
     int sym_split;  // pair-once: waves sharing a block's rows (0 or 1: none)
 };
@@ -777,10 +922,10 @@ int sym_block(const Variant &V)
 // R rounds of workgroups.
 #define BWD_SYM_S_VARIANT(W, K, R) \
     {"bwd_sym_s" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, 1, R, W>, \
-     backward_sym_kernel<W, K, true, W>, W, K, 1, R, nullptr, 0, W}
+     backward_sym_kernel<W, K, true, W>, W, K, 1, R, false, 0, W}
 
 #define BWD_ROW_VARIANT(K) \
-    {"bwd_row_k" #K, 64, K, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 1, backward_row_kernel<K>, K}
+    {"bwd_row_k" #K, 64, K, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 1, true, K}
 
 const Variant kVariants[] = {
     BWD_VARIANT(256, 2, 4),
@@ -830,8 +975,8 @@ static int variant_index(const char *name)
     return 0;
 }
 
-// Measured on MI355X: the pair-once adjoint wins from about 4,000 particles
-// on, one wave per row below; its workspace is bounded as the forward's (ring
+// Measured on MI355X: the pair-once adjoint wins from about 6,200 particles
+// on, row groups below; its workspace is bounded as the forward's (ring
 // groups), and above 2^24 particles the gather kernel takes over.  The same
 // choice serves calls with and without potential weights.
 int backward_default_variant(int64_t n)
@@ -867,9 +1012,8 @@ int backward_default_variant(int64_t n)
     if (n >= 24000 && n < 30000) return pair_once_r16;
     if (n >= 12000) return pair_once_r8;
     if (n >= 4000) return pair_once_split;
-    // one wave per row below 4,000 bodies (two rows from 3,500): 4.7 against
-    // 16.1 us per call at 1,024 (split gather and its reduction), 13.3-14.4
-    // against 21.5-22.0 at 1,500 (pair-once and its fold)
+    // row groups below 4,000 bodies (an even number of rows from 3,500), which
+    // also serve the step-split variant below kBwdRowBandEnd
     return n >= 3500 ? row_2 : row_1;
 }
 
@@ -912,7 +1056,7 @@ int64_t backward_plan_bytes(int variant, int64_t n, int num_cu, int per_cu)
 int64_t backward_variant_max_n(int variant)
 {
     if (variant < 0 || variant >= kNumVariants) return -1;
-    // the row-per-wave kernels are built for launch-latency-bound sizes
+    // the row-group kernels are built for small sizes
     return kVariants[variant].row ? (1 << 16) : NBODY_MAX_N;
 }
 
@@ -921,7 +1065,7 @@ nbody_status backward_variant_occupancy(int variant, int *per_cu)
     const Variant &V = kVariants[variant];
     const hipError_t e =
         V.sym   ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.sym_kernel, V.sym_w * 64, 0)
-        : V.row ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.row, 256, 0)
+        : V.row ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, backward_row_kernel<kBwdRowMax, true>, 256, 0)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.partial, V.block, 0);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (*per_cu < 1) *per_cu = 1;
@@ -935,15 +1079,8 @@ nbody_status backward_run(int variant, const Device &dev, const float *x, const 
     const Variant &V = kVariants[variant];
     if (fused) *fused = false;
     if (V.sym) return V.sym(V.name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi, fused, arena);
-    if (V.row) {
-        const int64_t waves = ((int64_t)n + V.row_k - 1) / V.row_k;
-        BwdArgs P{x, m, ga, gp, n, eps2, 0, nullptr, gx, gm};
-        if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
-        prof_mark(stream, 0);
-        hipLaunchKernelGGL(V.row, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, P);
-        prof_mark(stream, 1);
-        return check_launch(V.name);
-    }
+    if (V.row)
+        return backward_rows_run(V.row_k, V.name, dev, x, m, n, eps2, ga, gp, gx, gm, stream);
     const int iblk = V.block * V.k;
     const int iblocks = (n + iblk - 1) / iblk;
     int splits = 1, chunk = 0;

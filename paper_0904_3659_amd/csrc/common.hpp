@@ -122,18 +122,19 @@ inline bool row_band(int n) { return n >= kRowBandBegin && n < kRowBandEnd; }
 // Rows per group K (a multiple of `least`, at most `most`) for n rows on
 // num_cu CUs: the K with the least estimated time.  A workgroup's four waves
 // take one SIMD each, so a CU holding w workgroups needs time in proportion
-// to w (K + 0.5) per j-tile (half a row's worth for loads and loop), and its
-// start and final sums grow with K (0.3).  Measured at 5,000 bodies: K = 2..8
+// to w (K + load10 / 10) per j-tile (half a row's worth for loads and loop in
+// the forward, one row's in the adjoint), and its start and final sums grow
+// with K (0.3).  Measured at 5,000 bodies: K = 2..8
 // (w = 10, 7, 5, 4, 4, 3, 3) take 11.4, 10.7, 10.3, 10.5, 11.8, 11.1, 12.2 us;
 // the estimate picks 5.
-inline int row_group_rows(int n, int num_cu, int least, int most)
+inline int row_group_rows(int n, int num_cu, int least, int most, int load10)
 {
     int best = least;
-    int64_t cost = INT64_MAX;
+    unsigned cost = ~0u;  // w k < 2^28 / 256 + k: no overflow
     for (int k = least; k <= most; k += least) {
-        const int64_t groups = ((int64_t)n + k - 1) / k;
-        const int64_t w = (groups + num_cu - 1) / num_cu;
-        const int64_t c = w * (10 * k + 5) + 3 * k;
+        const unsigned groups = ((unsigned)n + k - 1) / k;
+        const unsigned w = (groups + num_cu - 1) / num_cu;
+        const unsigned c = w * (10 * k + load10) + 3 * k;
         if (c < cost) {
             cost = c;
             best = k;

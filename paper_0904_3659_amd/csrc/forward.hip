@@ -411,7 +411,7 @@ __global__ __launch_bounds__(256) void forward_row_kernel(RowArgs P)
     // x and m as buffers of their exact sizes: a load past the end gives zero,
     // so the loads ahead need no clamp
     const auto bx = make_buffer(P.x, 12u * (unsigned)n), bm = make_buffer(P.m, 4u * (unsigned)n);
-    const auto load = [&](int t) { return load_xm(bx, bm, (unsigned)(t * 64 + lane)); };
+    const auto load = [&](int t) { return buffer_xm(bx, bm, (unsigned)(t * 64 + lane)); };
     const int full = n >> 6;  // tiles without particles past n
     // The tiles that hold a row of the group, and the ragged last one, are met
     // first, with the pairs to leave out masked; the main loop passes them by
@@ -689,7 +689,7 @@ int64_t forward_plan_bytes(int variant, int64_t n, int num_cu, int per_cu)
 int64_t forward_variant_max_n(int variant)
 {
     if (variant < 0 || variant >= kNumVariants) return -1;
-    // the one-launch kernels are built for launch-latency-bound sizes
+    // the one-launch kernels are built for small sizes
     return (kVariants[variant].la_w || kVariants[variant].row) ? (1 << 16) : NBODY_MAX_N;
 }
 
@@ -720,7 +720,7 @@ nbody_status forward_rows_run(int least, const char *name, const Device &dev, co
     RowArgs P{x, m, n, eps2, a, p};
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     prof_mark(stream, 0);
-    kRowLaunch[row_group_rows(n, dev.num_cu, least, kRowMax)](P, stream);
+    kRowLaunch[row_group_rows(n, dev.num_cu, least, kRowMax, 5)](P, stream);
     prof_mark(stream, 1);
     return check_launch(name);
 }

@@ -56,8 +56,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const float *p, un
 }
 
 // (x_j, y_j, z_j, m_j), or zeros where j is past the end of the buffers.
-__device__ __forceinline__ float4 load_xm(__amdgpu_buffer_rsrc_t bx, __amdgpu_buffer_rsrc_t bm,
-                                          unsigned j)
+__device__ __forceinline__ float4 buffer_xm(__amdgpu_buffer_rsrc_t bx, __amdgpu_buffer_rsrc_t bm,
+                                            unsigned j)
 {
     const auto v = __builtin_amdgcn_raw_buffer_load_b96(bx, (int)(12u * j), 0, 0);
     const auto w = __builtin_amdgcn_raw_buffer_load_b32(bm, (int)(4u * j), 0, 0);

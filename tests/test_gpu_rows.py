@@ -38,3 +38,28 @@ def test_forward(nb, n, eps2):
     rows = np.unique(np.concatenate([np.arange(min(n, 700)), np.arange(max(0, n - 300), n)]))
     ar, pr = R.forces_rows(x, m, eps2, rows)
     assert_parity(host(a1[:n])[rows], host(p1[:n])[rows], ar, pr, label=f"rows n={n} eps2={eps2}")
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 129, 255, 1021, 1601, 2501, 3001, 3501, 3999, 4000, 4501, 5003,
+                               6199, 6200])
+@pytest.mark.parametrize("with_v", [False, True])
+def test_adjoint(nb, n, with_v):
+    dev = need_gpu()
+    x = inputs.plummer_positions(n, (72, n))
+    m = inputs.lognormal_masses(n, (72, n, 1))
+    w, v = inputs.normal((n, 3), (72, n, 2)), inputs.normal((n,), (72, n, 3))
+    xd, md, wd = to_dev(x, dev), to_dev(m, dev), to_dev(w, dev)
+    vd = to_dev(v, dev) if with_v else None
+    gx = torch.full((n + 9, 3), 7.0, device=dev)
+    gm = torch.full((n + 9,), 7.0, device=dev)
+    nb.forces_backward(xd, md, 1e-4, wd, vd, out=(gx[:n], gm[:n]))
+    assert bool((gx[n:] == 7.0).all()) and bool((gm[n:] == 7.0).all())
+    gx2, _ = nb.forces_backward(xd, md, 1e-4, wd, vd, need_grad_m=False)
+    assert torch.equal(gx[:n], gx2)
+    rx, rm = R.forces_vjp(x, m, 1e-4, w, v if with_v else None)
+    if n == 1:
+        assert not gx[:n].any() and not gm[:n].any()
+        return
+    # normwise, the adjoint's tolerance of the other GPU tests
+    assert np.linalg.norm(host(gx[:n]) - rx, axis=1).max() <= 1e-4 * np.linalg.norm(rx, axis=1).max()
+    assert np.abs(host(gm[:n]) - rm).max() <= 1e-4 * np.abs(rm).max()
