@@ -28,7 +28,7 @@
  *   stream's workspace, counters and the batched plan exist; a first call
  *   allocates and a first batched call synchronises, which capture forbids).
  *   The graph keeps the workspace addresses of that stream (partial sums,
- *   the leap-frog adjoint's 16 n-byte buffer, counters): while it may
+ *   the leap-frog calls' second buffers, counters): while it may
  *   replay, make no call on that stream that needs a larger one of them, do
  *   not call nbody_release_workspace(), run no variant timer
  *   (nbody_autotune, nbody_autotune_batched) on that stream, and keep the
@@ -265,8 +265,10 @@ nbody_status nbody_kick_drift(float *x, float *v, const float *a, int64_t n, flo
  * repeated steps times (the same float32 FMAs in the same order).  A
  * step's end kick, the next step's start kick and its drift run in the
  * final reduction kernel of the pair-once force variants (two launches per
- * step), otherwise in one element-wise launch after the force.  Library
- * memory: that of nbody_forces.
+ * step), in the force kernel itself where that is the row-group kernel (one
+ * launch per step), otherwise in one element-wise launch after the force.
+ * Library memory: that of nbody_forces plus, where the row-group kernel
+ * runs, 12 n bytes per (device, stream) for a second position array.
  * Errors: n < 0 or > NBODY_MAX_N, steps < 0 or > NBODY_MAX_STEPS, eps2 as
  * for nbody_forces, dt not finite, NULL x, v, a or m with n > 0 and
  * steps > 0, any two of x, v, a, m, x_hist overlapping -> INVALID_ARGUMENT.
@@ -299,8 +301,9 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
  *     lv += dt lx;  lx += c VJP(pos[t-1])[lv];  lm += c VJP_m(pos[t-1])[lv]
  * bitwise as that sequence of nbody_axpy and nbody_forces_backward calls.
  * The updates run in the final reduction kernel of the pair-once adjoint
- * variants (the next step's lv += dt lx with them).  Library memory: that
- * of nbody_forces_backward plus 16 n bytes per (device, stream).
+ * variants and in the row-group adjoint kernel itself (the next step's
+ * lv += dt lx with them).  Library memory: that of nbody_forces_backward
+ * plus 16 n bytes per (device, stream), 28 n with the row-group kernel.
  * Errors: unknown flag bits, n, steps, eps2 or dt as for nbody_leapfrog,
  * NULL pos, m, lx, lv or lm with n > 0 and steps > 0, any two arrays
  * overlapping -> INVALID_ARGUMENT.

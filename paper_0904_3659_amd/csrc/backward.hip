@@ -35,6 +35,7 @@ struct BwdArgs {
     float4 *partial;  // [splits][n] (dL/dx, dL/dm) per split when PARTIAL
     float *gx;
     float *gm;
+    LfEpi e;  // row groups: the leap-frog update instead of the stores
 };
 
 struct RowAcc {
@@ -285,7 +286,7 @@ __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4
     }
 }
 
-template <int K, bool HAS_V>
+template <int K, bool HAS_V, bool EPI = false>
 __global__ __launch_bounds__(256) void backward_row_kernel(BwdArgs P)
 {
     constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
@@ -368,12 +369,19 @@ __global__ __launch_bounds__(256) void backward_row_kernel(BwdArgs P)
         return s;
     };
     if (c == 3) {
-        if (P.gm) P.gm[i] = total(4);
+        if (EPI)
+            P.e.lm[i] = __builtin_fmaf(P.e.c, total(4), P.e.lm[i]);
+        else if (P.gm)
+            P.gm[i] = total(4);
         return;
     }
     // dL/dx_k = w_k A - m_k B - C
     const float w = P.ga ? P.ga[3 * (size_t)i + c] : 0.f;
-    P.gx[3 * (size_t)i + c] = w * total(0) - P.m[i] * total(1 + c) - total(5 + c);
+    const float g = w * total(0) - P.m[i] * total(1 + c) - total(5 + c);
+    if (EPI)
+        lf_coord(P.e, 3 * (size_t)i + c, g);
+    else
+        P.gx[3 * (size_t)i + c] = g;
 }
 
 using RowFn = void (*)(const BwdArgs &, hipStream_t);
@@ -382,7 +390,9 @@ template <int K>
 static void launch_bwd_rows(const BwdArgs &P, hipStream_t stream)
 {
     const dim3 grid((unsigned)((P.n + K - 1) / K));
-    if (P.gp)
+    if (P.e.mode != kLfNone)
+        hipLaunchKernelGGL((backward_row_kernel<K, false, true>), grid, dim3(256), 0, stream, P);
+    else if (P.gp)
         hipLaunchKernelGGL((backward_row_kernel<K, true>), grid, dim3(256), 0, stream, P);
     else
         hipLaunchKernelGGL((backward_row_kernel<K, false>), grid, dim3(256), 0, stream, P);
@@ -809,9 +819,16 @@ const RowFn kRowLaunch[kBwdRowMax + 1] = {nullptr, launch_bwd_rows<1>, launch_bw
 
 nbody_status backward_rows_run(int least, const char *name, const Device &dev, const float *x,
                                const float *m, int n, float eps2, const float *ga, const float *gp,
-                               float *gx, float *gm, hipStream_t stream)
+                               float *gx, float *gm, hipStream_t stream, const LfEpi *epi,
+                               bool *fused)
 {
-    BwdArgs P{x, m, ga, gp, n, eps2, 0, nullptr, gx, gm};
+    BwdArgs P{x, m, ga, gp, n, eps2, 0, nullptr, gx, gm, LfEpi{}};
+    // an update that changes lv, the weights the other groups still read,
+    // needs a second buffer for it
+    if (epi && !gp && epi->mode == kLfAdjoint && (!epi->chain || epi->lvo)) {
+        P.e = *epi;
+        if (fused) *fused = true;
+    }
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     prof_mark(stream, 0);
     kRowLaunch[row_group_rows(n, dev.num_cu, least, kBwdRowMax, 10)](P, stream);
@@ -845,7 +862,7 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     if constexpr (S == 2 && K == 2)
         // the plan and its workspace stay the variant's, whichever kernel runs
         if (bwd_row_band(n))
-            return backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm, stream);
+            return backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi, fused);
     float4 *partial = static_cast<float4 *>(ws);
     double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
                                 : nullptr;
@@ -1017,6 +1034,12 @@ int backward_default_variant(int64_t n)
     return n >= 3500 ? row_2 : row_1;
 }
 
+bool backward_takes_rows(int variant, int n)
+{
+    const Variant &V = kVariants[variant];
+    return V.row || (V.sym_split == 2 && V.sym_k == 2 && bwd_row_band(n));
+}
+
 // Geometry of the row gather: j-splits and j per split.
 static void bwd_gather_geometry(const Variant &V, int n, int num_cu, int *splits_out,
                                 int *chunk_out)
@@ -1080,13 +1103,14 @@ nbody_status backward_run(int variant, const Device &dev, const float *x, const 
     if (fused) *fused = false;
     if (V.sym) return V.sym(V.name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi, fused, arena);
     if (V.row)
-        return backward_rows_run(V.row_k, V.name, dev, x, m, n, eps2, ga, gp, gx, gm, stream);
+        return backward_rows_run(V.row_k, V.name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi,
+                                 fused);
     const int iblk = V.block * V.k;
     const int iblocks = (n + iblk - 1) / iblk;
     int splits = 1, chunk = 0;
     bwd_gather_geometry(V, n, dev.num_cu, &splits, &chunk);
 
-    BwdArgs P{x, m, ga, gp, n, eps2, chunk, nullptr, gx, gm};
+    BwdArgs P{x, m, ga, gp, n, eps2, chunk, nullptr, gx, gm, LfEpi{}};
     if (splits == 1) {
         if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
         prof_mark(stream, 0);

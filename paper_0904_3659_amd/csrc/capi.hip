@@ -156,6 +156,27 @@ nbody_status workspace_aux(const Device &dev, hipStream_t stream, size_t bytes, 
     return grow_buffer(dev, stream, 1, bytes, ptr);
 }
 
+void *workspace_aux_try(const Device &dev, hipStream_t stream, size_t bytes)
+{
+    {
+        std::lock_guard<std::mutex> lock(g_ws_mu);
+        auto it = g_ws.find({dev.id, stream, 1});
+        if (it != g_ws.end() && it->second.bytes >= bytes) return it->second.ptr;
+    }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void *ptr = nullptr;
+    if (workspace_aux(dev, stream, bytes, &ptr) != NBODY_OK) {
+        (void)hipGetLastError();
+        clear_error();
+        return nullptr;
+    }
+    return ptr;
+}
+
 size_t workspace_size(const Device &dev, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lock(g_ws_mu);
@@ -636,7 +657,7 @@ nbody_status nbody_axpy(float *y, const float *xv, int64_t len, float alpha, voi
     Device dev;
     nbody_status st = current_device(&dev);
     if (st != NBODY_OK) return st;
-    return axpy_run(y, xv, len, alpha, (hipStream_t)stream);
+    return axpy_run(y, y, xv, len, alpha, (hipStream_t)stream);
 }
 
 nbody_status nbody_kick_drift(float *x, float *v, const float *a, int64_t n, float kick, float dt,
@@ -685,6 +706,15 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
     const hipStream_t s = (hipStream_t)stream;
     const int variant = select_variant(NBODY_KIND_FORWARD, n);
     const float kick = -0.5f * dt;  // half kick with the physical acceleration -a
+    // The row-group kernels update v and x after their sums while other
+    // workgroups still read x: the positions then alternate between x and a
+    // second buffer, starting where the last drift ends in x.
+    // Without that buffer the update runs in a launch of its own.
+    float *cur = x, *other = nullptr;
+    if (steps > 1 && forward_takes_rows(variant, (int)n))
+        other = static_cast<float *>(workspace_aux_try(dev, s, v3));
+    const bool rows = other != nullptr;
+    if (rows && ((steps - 1) & 1)) std::swap(cur, other);
     // start kick and drift of the first step
     LfEpi e;
     e.mode = kLfKick;
@@ -695,6 +725,7 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
     e.dt = dt;
     e.v = v;
     e.x = x;
+    e.xo = cur;
     e.xh = x_hist;
     st = lf_epilogue_run(a, nullptr, n, e, s);
     for (int64_t t = 0; t < steps && st == NBODY_OK; ++t) {
@@ -703,12 +734,15 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
         const bool last = t == steps - 1;
         e.kicks = last ? 1 : 2;
         e.drift = last ? 0 : 1;
+        e.x = cur;
+        e.xo = rows ? other : nullptr;
         e.xh = (!last && x_hist) ? x_hist + 3 * (size_t)n * (size_t)(t + 1) : nullptr;
         bool fused = false;
         prof_mark(s, -1);
-        st = forward_run(variant, dev, x, m, (int)n, eps2, a, nullptr, s, &e, &fused);
+        st = forward_run(variant, dev, cur, m, (int)n, eps2, a, nullptr, s, &e, &fused);
         if (st == NBODY_OK && !fused) st = lf_epilogue_run(a, nullptr, n, e, s);
         if (st == NBODY_OK) prof_mark(s, 2);
+        if (rows && !last) std::swap(cur, other);
     }
     return st;
 }
@@ -745,42 +779,56 @@ nbody_status nbody_leapfrog_adjoint(const float *pos, const float *m, int64_t n,
     const hipStream_t s = (hipStream_t)stream;
     const int variant = select_variant(NBODY_KIND_BACKWARD, n);
     // VJP results of variants that cannot take the update in their final
-    // reduction
-    void *aux = nullptr;
-    st = workspace_aux(dev, s, 16 * (size_t)n, &aux);
-    if (st != NBODY_OK) return st;
+    // reduction; for the row-group kernels, whose other workgroups still read
+    // the weights lv when a row's update is due, a second lv to alternate with
+    // (without it the update runs in a launch of its own)
+    void *aux = backward_takes_rows(variant, (int)n) ? workspace_aux_try(dev, s, 28 * (size_t)n)
+                                                     : nullptr;
+    const bool rows = aux != nullptr;
+    if (!rows) {
+        st = workspace_aux(dev, s, 16 * (size_t)n, &aux);
+        if (st != NBODY_OK) return st;
+    }
     float *gx = static_cast<float *>(aux);
     float *gm = gx + 3 * (size_t)n;
+    float *cur = lv, *other = rows ? gm + n : nullptr;
     LfEpi e;
     e.mode = kLfAdjoint;
     e.dt = dt;
     e.lx = lx;
     e.lm = lm;
-    e.lv = lv;
     // lx, lm += c VJP(positions)[lv]; then lv += dt lx if `chain`
     auto vjp = [&](const float *xp, float c, bool chain) {
         e.c = c;
         e.chain = chain ? 1 : 0;
+        e.lv = cur;
+        e.lvo = rows ? other : nullptr;
         bool fused = false;
         prof_mark(s, -1);
-        nbody_status r = backward_run(variant, dev, xp, m, (int)n, eps2, lv, nullptr, gx, gm, s,
+        nbody_status r = backward_run(variant, dev, xp, m, (int)n, eps2, cur, nullptr, gx, gm, s,
                                       &e, &fused);
         if (r == NBODY_OK && !fused) r = lf_epilogue_run(gx, gm, n, e, s);
         if (r == NBODY_OK) prof_mark(s, 2);
+        if (rows && chain) std::swap(cur, other);
         return r;
     };
     const float half = 0.5f * dt;
     const size_t stride = 3 * (size_t)n;
-    if (flags & NBODY_LEAPFROG_FINAL)
+    if (flags & NBODY_LEAPFROG_FINAL) {
         st = vjp(pos + stride * (size_t)steps, -half, true);  // end kick of the last step
-    else
-        st = axpy_run(lv, lx, 3 * n, dt, s);  // drift of the segment's last step
+    } else {
+        // drift of the segment's last step, into the buffer from which the
+        // remaining steps - 1 alternations end in lv
+        if (rows && ((steps - 1) & 1)) std::swap(cur, other);
+        st = axpy_run(cur, lv, lx, 3 * n, dt, s);
+    }
     for (int64_t t = steps; t >= 1 && st == NBODY_OK; --t) {
         // positions before step t of the segment: its start kick, plus the
         // end kick of the step before at the same positions (none at step 0)
         const bool first = (flags & NBODY_LEAPFROG_INITIAL) && t == 1;
         st = vjp(pos + stride * (size_t)(t - 1), first ? -half : -dt, t > 1);
     }
+    if (st == NBODY_OK && cur != lv) st = copy_run(lv, cur, 3 * n, s);
     return st;
 }
 

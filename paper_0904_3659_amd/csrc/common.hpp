@@ -38,6 +38,9 @@ nbody_status workspace(const Device &dev, hipStream_t stream, size_t bytes, void
 // keep data across calls that use workspace() (the leap-frog adjoint's
 // unfused VJP results).
 nbody_status workspace_aux(const Device &dev, hipStream_t stream, size_t bytes, void **ptr);
+// That buffer where the caller can do without: NULL if it would have to be
+// allocated while the stream is being captured, or cannot be.
+void *workspace_aux_try(const Device &dev, hipStream_t stream, size_t bytes);
 
 // Per-(device, stream) array of at least `count` int counters that are zero
 // between calls (kernels that use them leave them at zero); zero-filled
@@ -107,7 +110,11 @@ nbody_status forward_run(int variant, const Device &dev, const float *x, const f
 // `least`.
 nbody_status forward_rows_run(int least, const char *name, const Device &dev, const float *x,
                               const float *m, int n, float eps2, float *a, float *p,
-                              hipStream_t stream);
+                              hipStream_t stream, const LfEpi *epi, bool *fused);
+// Whether a variant runs the row-group kernel at n (whose leap-frog update
+// needs the second buffers of LfEpi).
+bool forward_takes_rows(int variant, int n);
+bool backward_takes_rows(int variant, int n);
 
 // Sizes at which the one-wave two-row pair-once variants run the row-group
 // kernel instead: the pair-once grid is then one underfilled round of
@@ -187,7 +194,10 @@ nbody_status batched_run(int variant, const Device &dev, const int64_t *offsets,
                          float *a, float *p, hipStream_t stream);
 
 // ---- elementwise
-nbody_status axpy_run(float *y, const float *xv, int64_t len, float alpha, hipStream_t stream);
+// out = y + alpha xv; out may be y.
+nbody_status axpy_run(float *out, const float *y, const float *xv, int64_t len, float alpha,
+                      hipStream_t stream);
+nbody_status copy_run(float *out, const float *in, int64_t len, hipStream_t stream);
 nbody_status kick_drift_run(float *x, float *v, const float *a, int64_t len, float kick, float dt,
                             hipStream_t stream);
 // The update `e` for n rows whose result is in r3[n][3] (and r1[n], may be

@@ -6,14 +6,22 @@
 namespace nbody {
 namespace {
 
-// y[t] += alpha * xv[t]; grid-stride over 64-bit lengths.
-__global__ __launch_bounds__(256) void axpy_kernel(float *__restrict__ y,
+// out[t] = y[t] + alpha * xv[t] (out may be y); grid-stride over 64-bit
+// lengths.
+__global__ __launch_bounds__(256) void axpy_kernel(float *out, const float *y,
                                                    const float *__restrict__ xv, int64_t len,
                                                    float alpha)
 {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < len; t += stride)
-        y[t] = __builtin_fmaf(alpha, xv[t], y[t]);
+        out[t] = __builtin_fmaf(alpha, xv[t], y[t]);
+}
+
+__global__ __launch_bounds__(256) void copy_kernel(float *__restrict__ out,
+                                                   const float *__restrict__ in, int64_t len)
+{
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < len; t += stride) out[t] = in[t];
 }
 
 // Kick then drift of one leap-frog step, Eqs. (1)-(2): v += kick * a, then
@@ -90,13 +98,23 @@ nbody_status fill_zero_int(int *p, size_t len, hipStream_t stream)
     return check_launch("zero_int");
 }
 
-nbody_status axpy_run(float *y, const float *xv, int64_t len, float alpha, hipStream_t stream)
+nbody_status axpy_run(float *out, const float *y, const float *xv, int64_t len, float alpha,
+                      hipStream_t stream)
 {
     int64_t blocks = (len + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
-    hipLaunchKernelGGL(axpy_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y, xv, len, alpha);
+    hipLaunchKernelGGL(axpy_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, out, y, xv, len,
+                       alpha);
     return check_launch("axpy");
+}
+
+nbody_status copy_run(float *out, const float *in, int64_t len, hipStream_t stream)
+{
+    int64_t blocks = (len + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, out, in, len);
+    return check_launch("copy");
 }
 
 nbody_status kick_drift_run(float *x, float *v, const float *a, int64_t len, float kick, float dt,

@@ -351,6 +351,7 @@ struct RowArgs {
     float eps2;
     float *a;
     float *p;
+    LfEpi e;  // EPI: the leap-frog update after the store of a
 };
 
 constexpr int kRowMax = 8;  // rows per group
@@ -385,7 +386,7 @@ __device__ __forceinline__ void row_tile(const float (&xi)[K], const float (&yi)
     }
 }
 
-template <int K, bool POT>
+template <int K, bool POT, bool EPI = false>
 __global__ __launch_bounds__(256) void forward_row_kernel(RowArgs P)
 {
     constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
@@ -446,17 +447,21 @@ __global__ __launch_bounds__(256) void forward_row_kernel(RowArgs P)
     float s = red[0][threadIdx.x];
 #pragma unroll
     for (int w = 1; w < 4; ++w) s += red[w][threadIdx.x];
-    if (c < 3)
-        P.a[3 * (i0 + k) + c] = s;
-    else if (POT)
+    if (c < 3) {
+        P.a[3 * (size_t)(i0 + k) + c] = s;
+        if (EPI) lf_coord(P.e, 3 * (size_t)(i0 + k) + c, s);
+    } else if (POT) {
         P.p[i0 + k] = s;
+    }
 }
 
 template <int K>
 static void launch_rows(const RowArgs &P, hipStream_t stream)
 {
     const dim3 grid((unsigned)((P.n + K - 1) / K));
-    if (P.p)
+    if (P.e.mode != kLfNone)
+        hipLaunchKernelGGL((forward_row_kernel<K, false, true>), grid, dim3(256), 0, stream, P);
+    else if (P.p)
         hipLaunchKernelGGL((forward_row_kernel<K, true>), grid, dim3(256), 0, stream, P);
     else
         hipLaunchKernelGGL((forward_row_kernel<K, false>), grid, dim3(256), 0, stream, P);
@@ -713,11 +718,23 @@ const RowFn kRowLaunch[kRowMax + 1] = {nullptr, launch_rows<1>, launch_rows<2>, 
                                        launch_rows<4>, launch_rows<5>, launch_rows<6>,
                                        launch_rows<7>, launch_rows<8>};
 
+bool forward_takes_rows(int variant, int n)
+{
+    const Variant &V = kVariants[variant];
+    return V.row || (V.sym_w == 1 && V.sym_k == 2 && row_band(n));
+}
+
 nbody_status forward_rows_run(int least, const char *name, const Device &dev, const float *x,
                               const float *m, int n, float eps2, float *a, float *p,
-                              hipStream_t stream)
+                              hipStream_t stream, const LfEpi *epi, bool *fused)
 {
-    RowArgs P{x, m, n, eps2, a, p};
+    RowArgs P{x, m, n, eps2, a, p, LfEpi{}};
+    // an update that drifts x needs a second position buffer: the other
+    // groups still read x
+    if (epi && !p && epi->mode == kLfKick && (!epi->drift || epi->xo)) {
+        P.e = *epi;
+        if (fused) *fused = true;
+    }
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     prof_mark(stream, 0);
     kRowLaunch[row_group_rows(n, dev.num_cu, least, kRowMax, 5)](P, stream);
@@ -731,7 +748,8 @@ nbody_status forward_run(int variant, const Device &dev, const float *x, const f
 {
     const Variant &V = kVariants[variant];
     if (fused) *fused = false;
-    if (V.row) return forward_rows_run(V.row_k, V.name, dev, x, m, n, eps2, a, p, stream);
+    if (V.row)
+        return forward_rows_run(V.row_k, V.name, dev, x, m, n, eps2, a, p, stream, epi, fused);
     if (V.la_w) {
         const int rb = (n + 63) / 64;
         int splits = 1, chunk = 0;

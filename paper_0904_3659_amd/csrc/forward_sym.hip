@@ -60,7 +60,7 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     if constexpr (W == 1 && K == 2)
         // the plan and its workspace stay the variant's, whichever kernel runs
         if (row_band(n))
-            return forward_rows_run(1, name, dev, x, m, n, eps2, a, p, stream);
+            return forward_rows_run(1, name, dev, x, m, n, eps2, a, p, stream, epi, fused);
     float4 *partial = static_cast<float4 *>(ws);
     double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
                                 : nullptr;

@@ -63,3 +63,77 @@ def test_adjoint(nb, n, with_v):
     # normwise, the adjoint's tolerance of the other GPU tests
     assert np.linalg.norm(host(gx[:n]) - rx, axis=1).max() <= 1e-4 * np.linalg.norm(rx, axis=1).max()
     assert np.abs(host(gm[:n]) - rm).max() <= 1e-4 * np.abs(rm).max()
+
+
+@pytest.mark.parametrize("n", [1, 130, 2501, 5003, 11999])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4])
+def test_leapfrog_is_the_composed_calls(nb, n, steps):
+    # one launch per step, the positions alternating between the caller's
+    # array and a second buffer: bitwise the separate calls, ending in x
+    dev = need_gpu()
+    x = to_dev(inputs.plummer_positions(n, (73, n)), dev)
+    v = to_dev(inputs.plummer_velocities(host(x).astype(np.float32), (73, n, 1)), dev)
+    m = to_dev(inputs.lognormal_masses(n, (73, n, 2)), dev)
+    dt, eps2 = 1e-2, 1e-3
+    a, _ = nb.forces(x, m, eps2)
+    x1, v1, a1 = x.clone(), v.clone(), a.clone()
+    hist = torch.empty((steps, n, 3), device=dev)
+    nb.leapfrog_(x1, v1, a1, m, eps2, dt, steps, x_hist=hist)
+    for t in range(steps):
+        nb.kick_drift_(x, v, a, -0.5 * dt, dt)
+        assert torch.equal(hist[t], x), t
+        a, _ = nb.forces(x, m, eps2, potential=False)
+        nb.axpy_(v, a, -0.5 * dt)
+    assert torch.equal(x1, x) and torch.equal(v1, v) and torch.equal(a1, a)
+
+
+@pytest.mark.parametrize("n", [1, 130, 2501, 4500, 6199])
+@pytest.mark.parametrize("steps", [1, 2, 3])
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+def test_leapfrog_adjoint_is_the_composed_calls(nb, n, steps, flags):
+    dev = need_gpu()
+    pos = to_dev(np.stack([inputs.plummer_positions(n, (74, n, t)) for t in range(steps + 1)]), dev)
+    m = to_dev(inputs.lognormal_masses(n, (74, n, 9)), dev)
+    lx, lv = (to_dev(inputs.normal((n, 3), (74, n, 10 + k)), dev) for k in (0, 1))
+    lm = to_dev(inputs.normal((n,), (74, n, 12)), dev)
+    dt, eps2 = 1e-2, 1e-3
+    lx1, lv1, lm1 = lx.clone(), lv.clone(), lm.clone()
+    nb.leapfrog_adjoint_(pos, m, eps2, dt, lx1, lv1, lm1, flags=flags)
+
+    def kick(t, c):
+        gx, gm = nb.forces_backward(pos[t], m, eps2, lv)
+        nb.axpy_(lx, gx, c)
+        nb.axpy_(lm, gm, c)
+
+    if flags & nb.LEAPFROG_FINAL:
+        kick(steps, -0.5 * dt)
+    for t in range(steps, 0, -1):
+        nb.axpy_(lv, lx, dt)
+        kick(t - 1, -0.5 * dt if flags & nb.LEAPFROG_INITIAL and t == 1 else -dt)
+    assert torch.equal(lx1, lx) and torch.equal(lv1, lv) and torch.equal(lm1, lm)
+
+
+def test_leapfrog_captured_on_a_fresh_stream(nb):
+    # no eager call on the stream, so no second position buffer there: the
+    # updates run in launches of their own, with the same bits
+    dev = need_gpu()
+    n, steps = 1500, 3
+    x = to_dev(inputs.plummer_positions(n, (75, 0)), dev)
+    v = to_dev(inputs.normal((n, 3), (75, 1)), dev)
+    m = to_dev(inputs.equal_masses(n), dev)
+    a, _ = nb.forces(x, m, 1e-3)
+    want = [t.clone() for t in (x, v, a)]
+    nb.leapfrog_(*want, m, 1e-3, 1e-2, steps)
+    got = [t.clone() for t in (x, v, a)]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        nb.leapfrog_(*got, m, 1e-3, 1e-2, steps)
+    for _ in range(3):
+        for t, src in zip(got, (x, v, a)):
+            t.copy_(src)
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(t, w) for t, w in zip(got, want))
+        nb.forces(x, m, 1e-3)
+        torch.cuda.synchronize()
