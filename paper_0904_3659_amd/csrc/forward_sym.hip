@@ -21,8 +21,8 @@ struct SymArgs {
 template <int W, int K, bool POT>
 __global__ __launch_bounds__(W * 64) void forward_sym_kernel(SymArgs A)
 {
-    __shared__ float4 tile[kTileLds];
-    __shared__ float4 jacc[W][kSlotLds];
+    __shared__ float4 tile[kSymBuffers<W> * kTileLds];
+    __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
     const int I = blockIdx.x / A.C;
     const int c = blockIdx.x - I * A.C;
     pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,

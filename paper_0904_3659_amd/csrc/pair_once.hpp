@@ -262,48 +262,12 @@ __device__ __forceinline__ float4 load_particle(const float *__restrict__ x,
                    : make_float4(kPadCol, kPadCol, kPadCol, 0.0f);
 }
 
-// One pair met once: i-side added to (tx, ty, tz, tp); j-side added to
-// (gx, gy, gz, gp), or stored there when FIRST (the first row of a step).
-template <bool FIRST>
-__device__ __forceinline__ void pair_once_term(float xi, float yi, float zi, float mi, float4 q,
-                                               float eps2, float &tx, float &ty, float &tz,
-                                               float &tp, float &gx, float &gy, float &gz,
-                                               float &gp)
-{
-    const float dx = xi - q.x;
-    const float dy = yi - q.y;
-    const float dz = zi - q.z;
-    float s2 = __builtin_fmaf(dx, dx, eps2);
-    s2 = __builtin_fmaf(dy, dy, s2);
-    s2 = __builtin_fmaf(dz, dz, s2);
-    const float r = __builtin_amdgcn_rsqf(s2);
-    const float r3 = r * (r * r);
-    // i-side: + m_j r^3 d, + m_j r
-    const float f = q.w * r3;
-    tp = __builtin_fmaf(q.w, r, tp);
-    tx = __builtin_fmaf(f, dx, tx);
-    ty = __builtin_fmaf(f, dy, ty);
-    tz = __builtin_fmaf(f, dz, tz);
-    // j-side: - m_i r^3 d, + m_i r
-    const float g = mi * r3;
-    if (FIRST) {
-        gx = -g * dx;
-        gy = -g * dy;
-        gz = -g * dz;
-        gp = mi * r;
-    } else {
-        gx = __builtin_fmaf(-g, dx, gx);
-        gy = __builtin_fmaf(-g, dy, gy);
-        gz = __builtin_fmaf(-g, dz, gz);
-        gp = __builtin_fmaf(mi, r, gp);
-    }
-}
-
-// One pair of a ring tile: i-side added to (tx, ty, tz, tp), j-side added
-// to the slot value g (the chain of a step's K rows starts from the slot,
-// so no separate add folds it in).  POT false: the caller stores no
-// potential, and its two terms (2 of the pair's 19 instructions) are not
-// formed.
+// One pair met once: i-side added to (tx, ty, tz, tp), j-side added to the
+// slot value g (the chain of a step's K rows starts from the slot, so no
+// separate add folds it in).  The slots hold +m_i r^3 d, the opposite of the
+// j-side's force, which their readers negate: a negated factor here would
+// take the long encoding.  POT false: the caller stores no potential, and its
+// two terms (2 of the pair's 19 instructions) are not formed.
 template <bool POT = true>
 __device__ __forceinline__ void pair_once_fold(float xi, float yi, float zi, float mi, float4 q,
                                                float eps2, float &tx, float &ty, float &tz,
@@ -323,47 +287,53 @@ __device__ __forceinline__ void pair_once_fold(float xi, float yi, float zi, flo
     ty = __builtin_fmaf(f, dy, ty);
     tz = __builtin_fmaf(f, dz, tz);
     const float h = mi * r3;
-    g.x = __builtin_fmaf(-h, dx, g.x);
-    g.y = __builtin_fmaf(-h, dy, g.y);
-    g.z = __builtin_fmaf(-h, dz, g.z);
+    g.x = __builtin_fmaf(h, dx, g.x);
+    g.y = __builtin_fmaf(h, dy, g.y);
+    g.z = __builtin_fmaf(h, dz, g.z);
     if (POT) g.w = __builtin_fmaf(mi, r, g.w);
 }
 
-// pair_once_fold for the K rows of a lane, the rows' reciprocal square roots
+// pair_once_fold for the first R rows of a lane, the rows' reciprocal square roots
 // taken as one group (rsq_group); the same operations in the same order.
 // Whole calls, against K separate pair_once_fold: 215.5 -> 208.7 ms at 2^20
 // bodies, 919 -> 907 us at 65,536, 69.1 -> 68.2 us at 16,384 without the
 // potential.
-template <int K, bool POT = true>
+template <int K, int R = K, bool POT = true, int B = 0>
 __device__ __forceinline__ void pair_once_rows(const float (&xi)[K], const float (&yi)[K],
                                                const float (&zi)[K], const float (&mi)[K], float4 q,
                                                float eps2, float (&tx)[K], float (&ty)[K],
                                                float (&tz)[K], float (&tp)[K], float4 &g)
 {
-    float dx[K], dy[K], dz[K], r[K];
+    constexpr int G = R < 4 ? R : 4;  // rows of this group (the first R rows in groups of four)
+    float dx[G], dy[G], dz[G], r[G];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        dx[k] = xi[k] - q.x;
-        dy[k] = yi[k] - q.y;
-        dz[k] = zi[k] - q.z;
+    for (int k = 0; k < G; ++k) {
+        dx[k] = xi[B + k] - q.x;
+        dy[k] = yi[B + k] - q.y;
+        dz[k] = zi[B + k] - q.z;
         float s2 = __builtin_fmaf(dx[k], dx[k], eps2);
         s2 = __builtin_fmaf(dy[k], dy[k], s2);
         r[k] = __builtin_fmaf(dz[k], dz[k], s2);
     }
-    rsq_group<K>(r);
+    rsq_group<G>(r);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; k < G; ++k) {
         const float r3 = r[k] * (r[k] * r[k]);
         const float f = q.w * r3;
-        if (POT) tp[k] = __builtin_fmaf(q.w, r[k], tp[k]);
-        tx[k] = __builtin_fmaf(f, dx[k], tx[k]);
-        ty[k] = __builtin_fmaf(f, dy[k], ty[k]);
-        tz[k] = __builtin_fmaf(f, dz[k], tz[k]);
-        const float h = -mi[k] * r3;
+        if (POT) tp[B + k] = __builtin_fmaf(q.w, r[k], tp[B + k]);
+        tx[B + k] = __builtin_fmaf(f, dx[k], tx[B + k]);
+        ty[B + k] = __builtin_fmaf(f, dy[k], ty[B + k]);
+        tz[B + k] = __builtin_fmaf(f, dz[k], tz[B + k]);
+        const float h = mi[B + k] * r3;
         g.x = __builtin_fmaf(h, dx[k], g.x);
         g.y = __builtin_fmaf(h, dy[k], g.y);
         g.z = __builtin_fmaf(h, dz[k], g.z);
-        if (POT) g.w = __builtin_fmaf(mi[k], r[k], g.w);
+        if (POT) g.w = __builtin_fmaf(mi[B + k], r[k], g.w);
+    }
+    if constexpr (R > 4) {
+        // the groups one after the other: their temporaries share registers
+        __builtin_amdgcn_sched_barrier(0);
+        pair_once_rows<K, R - 4, POT, B + 4>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
     }
 }
 
@@ -384,7 +354,8 @@ __device__ __forceinline__ void ring_tile_steps(const float (&xi)[K], const floa
     const float4 *tq = tile + lane;
     float4 *sl = slot + lane;
     float4 q = tq[0];
-#pragma unroll 8
+    constexpr int kUnroll = K > 8 ? 2 : K > 4 ? 4 : 8;  // about 600 to 1,200 operations per trip
+#pragma unroll kUnroll
     for (int s = 0; s < 64; ++s) {
         // Compiler-only barrier: this step's slot read stays after the
         // previous step's slot write (another lane wrote the slot read here).
@@ -398,7 +369,7 @@ __device__ __forceinline__ void ring_tile_steps(const float (&xi)[K], const floa
                     pair_once_fold<POT>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k],
                                         tp[k], g);
         } else {
-            pair_once_rows<K, POT>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
+            pair_once_rows<K, K, POT>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
         }
         sl[s] = g;
         q = qn;
@@ -419,13 +390,12 @@ __device__ __forceinline__ void diag_step(const float (&xi)[K], const float (&yi
                                           float (&tp)[K])
 {
     if constexpr (R > 0) {
+        static_assert(R <= 4, "one group of rows");
         // keep this step's slot read after the previous step's slot write
         __asm__ volatile("" ::: "memory");
         const float4 q = tq[s];
         float4 g = sl[s];
-#pragma unroll
-        for (int k = 0; k < R; ++k)
-            pair_once_fold<POT>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k], tp[k], g);
+        pair_once_rows<K, R, POT>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
         sl[s] = g;
     }
 }
@@ -487,62 +457,53 @@ __device__ __forceinline__ void diag_tile_dispatch(int kt, const float (&xi)[K],
         diag_tile_dispatch<K, KT + 1, POT>(kt, xi, yi, zi, mi, tile, slot, lane, eps2, tx, ty, tz, tp);
 }
 
-// The 64 steps of one tile for one wave.  Lane l meets tile particle
-// (l + s) mod 64 at step s.  Ring tiles (DIAG false): every row tile meets
-// the tile pair-once.  Diagonal tile t (DIAG true): row tile a = a0 + k
-// meets it pair-once if a < t, as masked ordered pairs if a == t, not at all
-// if a > t.  j-side sums go to this wave's LDS slots (read-modify-write).
-template <int K, bool DIAG>
-__device__ __forceinline__ void tile_steps(const float (&xi)[K], const float (&yi)[K],
-                                           const float (&zi)[K], const float (&mi)[K],
-                                           const int (&ii)[K], const float4 *tile, float4 *slot,
-                                           int lane, int a0, int t, int jbase, float eps2,
-                                           float (&tx)[K], float (&ty)[K], float (&tz)[K],
-                                           float (&tp)[K])
+// The 64 steps of diagonal tile t for one wave of a wider block.  Lane l meets
+// tile particle (l + s) mod 64 at step s: row tile a = a0 + k meets it
+// pair-once if a < t, as masked ordered pairs if a == t, not at all if a > t.
+// j-side sums go to this wave's LDS slots (read-modify-write).
+template <int K>
+__device__ __forceinline__ void diag_tile_steps(const float (&xi)[K], const float (&yi)[K],
+                                                const float (&zi)[K], const float (&mi)[K],
+                                                const int (&ii)[K], const float4 *tile,
+                                                float4 *slot, int lane, int a0, int t, int jbase,
+                                                float eps2, float (&tx)[K], float (&ty)[K],
+                                                float (&tz)[K], float (&tp)[K])
 {
-    const bool any_once = !DIAG || a0 < t;
+    const bool any_once = a0 < t;
     float4 q = tile[lane];
     for (int s = 0; s < 64; ++s) {
         const int jj = (lane + s) & 63;
         // Compiler-only barrier: this step's slot read stays after the
         // previous step's slot write (another lane may have written it).
         __asm__ volatile("" ::: "memory");
-        float4 ja = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (any_once) ja = slot[jj];
+        float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (any_once) g = slot[jj];
         const float4 qn = tile[(jj + 1) & 63];  // next step's particle (read-only tile)
-        float gx = 0.f, gy = 0.f, gz = 0.f, gp = 0.f;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (!DIAG) {
-                if (k == 0)
-                    pair_once_term<true>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k],
-                                         tp[k], gx, gy, gz, gp);
-                else
-                    pair_once_term<false>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k],
-                                          tp[k], gx, gy, gz, gp);
-            } else if (a0 + k < t) {
-                pair_once_term<false>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k],
-                                      tp[k], gx, gy, gz, gp);
-            } else if (a0 + k == t) {
+            if (a0 + k < t)
+                pair_once_fold<true>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k],
+                                     tp[k], g);
+            else if (a0 + k == t)
                 pair_term_masked(xi[k], yi[k], zi[k], q, eps2, jbase + jj == ii[k], tx[k], ty[k],
                                  tz[k], tp[k]);
-            }
         }
-        if (any_once) {
-            ja.x += gx;
-            ja.y += gy;
-            ja.z += gz;
-            ja.w += gp;
-            slot[jj] = ja;
-        }
+        if (any_once) slot[jj] = g;
         q = qn;
     }
 }
 
+// LDS buffers of a pair-once workgroup: blocks of several waves keep two tiles
+// and two sets of slots, so that one barrier per tile suffices; a one-wave
+// block needs no barrier, and its single set leaves room for more workgroups.
+template <int W>
+constexpr int kSymBuffers = W > 1 ? 2 : 1;
+
 // One workgroup of W*64 lanes evaluates chunk c of block I.  x, m and
-// partial are the system's own arrays (offsets already applied).  tile and
-// jacc are the workgroup's LDS buffers.  Starts with a workgroup barrier, so
-// the LDS buffers may be reused by consecutive calls.
+// partial are the system's own arrays (offsets already applied).  tile
+// (kSymBuffers<W> tiles) and jacc (kSymBuffers<W> sets of W slot arrays) are
+// the workgroup's LDS buffers.  Starts with a workgroup barrier, so the LDS
+// buffers may be reused by consecutive calls.
 //
 // Diagonal tiles are pair-once too (for W <= 8; larger blocks meet them as
 // masked ordered pairs): the rows of lane-slot k of wave wv form
@@ -559,6 +520,12 @@ __device__ __forceinline__ void tile_steps(const float (&xi)[K], const float (&y
 // of small systems, where a last block is often part padding (5% of the
 // row-group work on the 4,096-system ensemble); single systems keep the
 // lighter loop.
+//
+// Blocks of several waves pass one barrier per tile: while a wave takes the
+// steps of tile b, the next tile is staged in the other buffer; after the
+// barrier every wave clears its slots of the other set (whose sums were read
+// before the barrier) and all threads share the sum of the W slot sets, one
+// component each.
 template <int W, int K, bool SKIP_PAD = false, bool POT = true>
 __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                                                 const float *__restrict__ m, int n, float eps2,
@@ -568,6 +535,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
 {
     constexpr int PB = W * 64 * K;   // particles per block
     constexpr int TPB = PB / 64;     // 64-particle tiles per block
+    constexpr int NB = kSymBuffers<W>;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wv = tid >> 6;
@@ -615,29 +583,55 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     // keep the masked ordered self tile: there the diagonal is rare, and
     // the larger code changed the schedule of their ring loop (6-8% slower
     // at 2^20 bodies).
-    constexpr bool kSelfDiag = (W == 1);
+    constexpr bool kSelfDiag = (W == 1 && K <= 4);
     int u = u0, delta = 0, jbase = 0;
     for (; u < u1; ++u)
         if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
     float4 next = make_float4(0.f, 0.f, 0.f, 0.f);
     if (kPrefetch && u < u1 && tid < 64) next = load_particle(x, m, jbase + tid, n);
+    in_vgpr(eps2);
+    // The rows have arrived here, so that no wait for them in the tile loop
+    // also waits for the prefetch.
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        __asm__ volatile("" : "+v"(xi[k]), "+v"(yi[k]), "+v"(zi[k]), "+v"(mi[k]));
 
-    while (u < u1) {
-        // previous tile and its j-slot sums are done (and the LDS buffers
-        // free on entry: callers may loop over blocks)
-        __syncthreads();
+    const auto stage = [&](int b) {
         if (tid < 64) {
             const float4 v = kPrefetch ? next : load_particle(x, m, jbase + tid, n);
-            tile[tid] = v;
-            tile[tid + 64] = v;
+            tile[b * kTileLds + tid] = v;
+            tile[b * kTileLds + tid + 64] = v;
         }
-        jacc[wv][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-        jacc[wv][lane + 64] = make_float4(0.f, 0.f, 0.f, 0.f);
-        __syncthreads();
-        const int cur_u = u, cur_delta = delta, cur_base = jbase;
+    };
+    const auto clear_slots = [&](int b) {
+        jacc[b * W + wv][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        jacc[b * W + wv][lane + 64] = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    // the tile after the current one, and its load
+    const auto advance = [&]() {
         for (++u; u < u1; ++u)
             if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
         if (kPrefetch && u < u1 && tid < 64) next = load_particle(x, m, jbase + tid, n);
+    };
+
+    int b = 0;
+    if (NB == 2 && u < u1) {
+        __syncthreads();  // the LDS buffers are free
+        stage(0);
+        clear_slots(0);
+        __syncthreads();
+    }
+    while (u < u1) {
+        if (NB == 1) {
+            // the previous tile and its slot sums are done (the LDS buffers
+            // free on entry: callers may loop over blocks)
+            __syncthreads();
+            stage(0);
+            clear_slots(0);
+            __syncthreads();
+        }
+        const int cur_u = u, cur_delta = delta, cur_base = jbase;
+        advance();
 
         float tx[K], ty[K], tz[K], tp[K];
 #pragma unroll
@@ -645,24 +639,27 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
 
         const int t = cur_u;                         // diagonal tile index when cur_delta == 0
         const bool diag = (cur_delta == 0);
-        float4 *slot = &jacc[wv][0];
+        const float4 *cur_tile = tile + b * kTileLds;
+        float4 *slot = &jacc[b * W + wv][0];
         if (!diag) {
             if (!SKIP_PAD || kv == K)
-                ring_tile_steps<K, false, POT>(xi, yi, zi, mi, tile, slot, lane, eps2, tx, ty, tz, tp);
+                ring_tile_steps<K, false, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz,
+                                               tp);
             else if (kv > 0)
-                ring_tile_steps<K, true, POT>(xi, yi, zi, mi, tile, slot, lane, eps2, tx, ty, tz, tp,
-                                         kv);
+                ring_tile_steps<K, true, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz,
+                                              tp, kv);
         } else if constexpr (kSelfDiag) {
             // one wave: its row group k is the block's tile k, so diagonal
             // tile t meets row groups k < t pair-once and row group t itself
-            diag_tile_dispatch<K, 0, POT>(t, xi, yi, zi, mi, tile, slot, lane, eps2, tx, ty, tz, tp);
+            diag_tile_dispatch<K, 0, POT>(t, xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz,
+                                          tp);
         } else if (kOnceDiag) {
-            tile_steps<K, true>(xi, yi, zi, mi, ii, tile, slot, lane, wv * K, t, cur_base, eps2, tx,
-                                ty, tz, tp);
+            diag_tile_steps<K>(xi, yi, zi, mi, ii, cur_tile, slot, lane, wv * K, t, cur_base, eps2, tx,
+                               ty, tz, tp);
         } else {
             // ordered pairs, i-side only, j == i removed by index
             for (int s = 0; s < 64; ++s) {
-                const float4 q = tile[s];
+                const float4 q = cur_tile[s];
                 const int j = cur_base + s;
 #pragma unroll
                 for (int k = 0; k < K; ++k)
@@ -678,30 +675,32 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
             az[k] += tz[k];
             ap[k] += tp[k];
         }
+        if (NB == 2 && u < u1) stage(b ^ 1);
         __syncthreads();  // every wave's j-side slots are complete
+        if (NB == 2 && u < u1) clear_slots(b ^ 1);
+        // every wave left particle e's sums in its slot e (components xyz with
+        // the opposite sign); they are added in wave order
         if (!diag) {
-            if (tid < 64) {
-                // particle tid: every wave folded its slot tid + 64 into slot
-                // tid (ring_tile_steps); add the waves' slots in wave order
-                float4 sum = jacc[0][tid];
+            float4 *out = partial + (size_t)(C + cur_delta - dj) * n + cur_base;
+            if constexpr (W == 1) {
+                const float4 sum = jacc[0][tid];
+                if (cur_base + tid < n) out[tid] = make_float4(-sum.x, -sum.y, -sum.z, sum.w);
+            } else {
+                for (int f = tid; f < 256; f += W * 64) {
+                    float sum = reinterpret_cast<const float *>(jacc[b * W])[f];
 #pragma unroll
-                for (int w2 = 1; w2 < W; ++w2) {
-                    const float4 v = jacc[w2][tid];
-                    sum.x += v.x;
-                    sum.y += v.y;
-                    sum.z += v.z;
-                    sum.w += v.w;
+                    for (int w2 = 1; w2 < W; ++w2)
+                        sum += reinterpret_cast<const float *>(jacc[b * W + w2])[f];
+                    if (cur_base + (f >> 2) < n)
+                        reinterpret_cast<float *>(out)[f] = (f & 3) == 3 ? sum : -sum;
                 }
-                const int j = cur_base + tid;
-                if (j < n) partial[(size_t)(C + cur_delta - dj) * n + j] = sum;
             }
         } else if (kOnceDiag && wv == t / K) {
-            // this wave holds diagonal tile t's rows (lane-slot t % K); the
-            // diagonal steps leave their sums in slots 0..63
-            float4 sum = jacc[0][lane];
+            // this wave holds diagonal tile t's rows (lane-slot t % K)
+            float4 sum = jacc[b * W][lane];
 #pragma unroll
             for (int w2 = 1; w2 < W; ++w2) {
-                const float4 v = jacc[w2][lane];
+                const float4 v = jacc[b * W + w2][lane];
                 sum.x += v.x;
                 sum.y += v.y;
                 sum.z += v.z;
@@ -711,12 +710,13 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 if (k == kt) {
-                    ax[k] += sum.x;
-                    ay[k] += sum.y;
-                    az[k] += sum.z;
+                    ax[k] -= sum.x;
+                    ay[k] -= sum.y;
+                    az[k] -= sum.z;
                     ap[k] += sum.w;
                 }
         }
+        if (NB == 2) b ^= 1;
     }
 
 #pragma unroll
