@@ -16,6 +16,7 @@ struct SymArgs {
     int C;            // chunks per block
     int d_lo, d_hi;   // ring deltas of this launch's group
     float4 *partial;  // [C + G][n]
+    ChunkCut cut;
 };
 
 template <int W, int K, bool POT>
@@ -23,9 +24,9 @@ __global__ __launch_bounds__(W * 64) void forward_sym_kernel(SymArgs A)
 {
     __shared__ float4 tile[kSymBuffers<W> * kTileLds];
     __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
-    const int I = blockIdx.x / A.C;
-    const int c = blockIdx.x - I * A.C;
-    pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
+    const int c = blockIdx.x / A.M;  // chunk-major (ChunkCut)
+    const int I = blockIdx.x - c * A.M;
+    pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.cut, A.d_lo, A.d_hi,
                                       A.partial, tile, jacc);
 }
 
@@ -67,8 +68,10 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
     for (int g = 0; g < pl.groups; ++g) {
-        SymArgs A{x, m, n, eps2, pl.M, pl.C, 0, 0, partial};
+        SymArgs A{x, m, n, eps2, pl.M, pl.C, 0, 0, partial, ChunkCut{}};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
+        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * dev.num_cu,
+                          group_tiles(0, pl.M, A.d_lo, A.d_hi, PB / 64));
         prof_mark(stream, 0);
         if (p)
             hipLaunchKernelGGL((forward_sym_kernel<W, K, true>), dim3(pl.M * pl.C), dim3(W * 64), 0,
