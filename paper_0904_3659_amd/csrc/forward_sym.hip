@@ -36,11 +36,14 @@ __global__ __launch_bounds__(W * 64) void forward_sym_kernel(SymArgs A)
 // many rounds of shorter workgroups (down to one tile each), which the
 // hardware dispatcher hands out as slots free up, evening out the tail of
 // a grid whose workgroups hold only a few tiles.
-template <int W, int K, int OCC, int ROUNDS = 1>
+// The kernel may hold a block of W waves x K rows as KW waves x KK rows (the
+// same P = 64 W K particles and the same plan).
+template <int W, int K, int OCC, int ROUNDS = 1, int KW = W, int KK = K>
 nbody_status run_sym(const char *name, const Device &dev, const float *x, const float *m, int n,
                      float eps2, float *a, float *p, hipStream_t stream, const LfEpi *epi,
                      bool *fused, const Arena &arena)
 {
+    static_assert(KW * KK == W * K, "the same block");
     constexpr int PB = W * 64 * K;
     int per_cu = 0;
     // sized by the kernel that forms the potential, also when p is not
@@ -70,14 +73,14 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     for (int g = 0; g < pl.groups; ++g) {
         SymArgs A{x, m, n, eps2, pl.M, pl.C, 0, 0, partial, ChunkCut{}};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
-        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * dev.num_cu,
+        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * W / KW * dev.num_cu,
                           group_tiles(0, pl.M, A.d_lo, A.d_hi, PB / 64));
         prof_mark(stream, 0);
         if (p)
-            hipLaunchKernelGGL((forward_sym_kernel<W, K, true>), dim3(pl.M * pl.C), dim3(W * 64), 0,
-                               stream, A);
+            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, true>), dim3(pl.M * pl.C), dim3(KW * 64),
+                               0, stream, A);
         else
-            hipLaunchKernelGGL((forward_sym_kernel<W, K, false>), dim3(pl.M * pl.C), dim3(W * 64),
+            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, false>), dim3(pl.M * pl.C), dim3(KW * 64),
                                0, stream, A);
         prof_mark(stream, 1);
         st = check_launch(name);
@@ -133,8 +136,14 @@ nbody_status forward_sym_run(int W, int K, int occ, int rounds, const char *name
     if (rounds == 8) {
         if (W == 1 && K == 4 && occ == 1) return run_sym<1, 4, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         if (W == 1 && K == 2 && occ == 1) return run_sym<1, 2, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
+        // Eight rows per lane halve the LDS reads and writes per pair against
+        // four (the two take turns in groups of four, so three waves per SIMD
+        // still fit).  Sustained calls: 8 x 4 as 4 x 8 220.1 -> 212.5 ms at 2^20
+        // bodies; 4 x 4 as 2 x 8 874 -> 860 us at 65,536, 1975 -> 1947 at
+        // 100,000, but 358 -> 363 at 40,000, where the workgroups are too few.
+        if (W == 4 && K == 4 && occ == 1 && n >= 50000) return run_sym<4, 4, 1, 8, 2, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         if (W == 4 && K == 4 && occ == 1) return run_sym<4, 4, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
-        if (W == 8 && K == 4 && occ == 1) return run_sym<8, 4, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
+        if (W == 8 && K == 4 && occ == 1) return run_sym<8, 4, 1, 8, 4, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         return fail(NBODY_ERROR_INTERNAL, "no pair-once forward kernel for W=%d K=%d occ=%d rounds=%d", W, K, occ, rounds);
     }
     if (W == 8 && K == 4 && occ == 1) return run_sym<8, 4, 1>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
