@@ -441,90 +441,79 @@ struct SymBwdArgs {
     int C;
     int d_lo, d_hi;   // ring deltas of this launch's group
     float4 *partial;  // [C + G][n]: (dL/dx, dL/dm)
+    ChunkCut cut;
 };
 
-// One unordered pair: adds F and the k mass term to tk; returns the j-side
-// contributions (-F, j mass term) through jx..jm.
-__device__ __forceinline__ void adj_pair_once(const float4 &xk, const float4 &wk, const float4 &q,
-                                              const float4 &wq, float eps2, float4 &tk, float &jx,
-                                              float &jy, float &jz, float &jm)
-{
-    const float dx = xk.x - q.x;
-    const float dy = xk.y - q.y;
-    const float dz = xk.z - q.z;
-    float s = __builtin_fmaf(dx, dx, eps2);
-    s = __builtin_fmaf(dy, dy, s);
-    s = __builtin_fmaf(dz, dz, s);
-    const float r = __builtin_amdgcn_rsqf(s);
-    const float r2 = r * r;
-    const float r3 = r * r2;
-    float wkd = wk.x * dx;
-    wkd = __builtin_fmaf(wk.y, dy, wkd);
-    wkd = __builtin_fmaf(wk.z, dz, wkd);
-    float wjd = wq.x * dx;
-    wjd = __builtin_fmaf(wq.y, dy, wjd);
-    wjd = __builtin_fmaf(wq.z, dz, wjd);
-    const float cd = __builtin_fmaf(q.w, wkd, -xk.w * wjd);
-    const float b = __builtin_fmaf(xk.w, wq.w, q.w * wk.w);
-    // F = r^3 (c - t d) with t = 3 r^2 (c . d) + b
-    const float t = __builtin_fmaf(3.0f * r2, cd, b);
-    const float cx = __builtin_fmaf(q.w, wk.x, -xk.w * wq.x);
-    const float cy = __builtin_fmaf(q.w, wk.y, -xk.w * wq.y);
-    const float cz = __builtin_fmaf(q.w, wk.z, -xk.w * wq.z);
-    const float Fx = r3 * __builtin_fmaf(-t, dx, cx);
-    const float Fy = r3 * __builtin_fmaf(-t, dy, cy);
-    const float Fz = r3 * __builtin_fmaf(-t, dz, cz);
-    tk.x += Fx;
-    tk.y += Fy;
-    tk.z += Fz;
-    tk.w = __builtin_fmaf(r, wq.w, tk.w);
-    tk.w = __builtin_fmaf(-r3, wjd, tk.w);
-    jx = -Fx;
-    jy = -Fy;
-    jz = -Fz;
-    jm = __builtin_fmaf(r3, wkd, r * wk.w);
-}
+// A lane's row constants in the form the pair terms read (all terms are then
+// plain products and accumulating FMAs; a negated operand would take the long
+// encoding).
+struct AdjRow {
+    float x, y, z, m;      // position, mass
+    float mn, m3;          // -m, 3 m
+    float wx, wy, wz, v;   // weights
+    float vn;              // -v
+};
 
-// adj_pair_once for ring tiles, with the j-side added straight into the
-// slot value ja: F = r^3 u with u = c - t d enters both sides as one FMA per
-// component (r^3 u to tk, -r^3 u to ja), and the j mass term likewise.
-template <bool HAS_V = true>
-__device__ __forceinline__ void adj_pair_fold(const float4 &xk, const float4 &wk, const float4 &q,
-                                              const float4 &wq, float eps2, float4 &tk, float4 &ja)
+// The first R rows (from row B on, in groups of four) of a lane against the
+// tile particle (q, wq), each pair met once, the rows' reciprocal square roots
+// as one group.  With e = x_j - x_k = -d:
+//     F = r^3 (c - t d) = r^3 (c + t e),  t = r^2 (3 m_k (w_j . e) - 3 m_j (w_k . e)) + b
+// enters tk as +F and the slot ja as +F too, which the slots' readers negate,
+// as the j mass term r v_k + r^3 (w_k . d) = r v_k - r^3 (w_k . e): the slot
+// takes its opposite, r^3 (w_k . e) - r v_k.
+template <int K, bool HAS_V, int R = K, int B = 0>
+__device__ __forceinline__ void adj_pair_rows(const AdjRow (&row)[K], const float4 &q,
+                                              const float4 &wq, float q3n, float eps2,
+                                              float4 (&tk)[K], float4 &ja)
 {
-    const float dx = xk.x - q.x;
-    const float dy = xk.y - q.y;
-    const float dz = xk.z - q.z;
-    float s = __builtin_fmaf(dx, dx, eps2);
-    s = __builtin_fmaf(dy, dy, s);
-    s = __builtin_fmaf(dz, dz, s);
-    const float r = __builtin_amdgcn_rsqf(s);
-    const float r2 = r * r;
-    const float r3 = r * r2;
-    float wkd = wk.x * dx;
-    wkd = __builtin_fmaf(wk.y, dy, wkd);
-    wkd = __builtin_fmaf(wk.z, dz, wkd);
-    float wjd = wq.x * dx;
-    wjd = __builtin_fmaf(wq.y, dy, wjd);
-    wjd = __builtin_fmaf(wq.z, dz, wjd);
-    const float cd = __builtin_fmaf(q.w, wkd, -xk.w * wjd);
-    // without potential weights (v = 0) b vanishes and t = 3 r^2 (c . d)
-    // exactly as the fused form with a zero addend
-    const float t = HAS_V ? __builtin_fmaf(3.0f * r2, cd, __builtin_fmaf(xk.w, wq.w, q.w * wk.w))
-                          : (3.0f * r2) * cd;
-    const float ux = __builtin_fmaf(-t, dx, __builtin_fmaf(q.w, wk.x, -xk.w * wq.x));
-    const float uy = __builtin_fmaf(-t, dy, __builtin_fmaf(q.w, wk.y, -xk.w * wq.y));
-    const float uz = __builtin_fmaf(-t, dz, __builtin_fmaf(q.w, wk.z, -xk.w * wq.z));
-    tk.x = __builtin_fmaf(r3, ux, tk.x);
-    tk.y = __builtin_fmaf(r3, uy, tk.y);
-    tk.z = __builtin_fmaf(r3, uz, tk.z);
-    if (HAS_V) tk.w = __builtin_fmaf(r, wq.w, tk.w);
-    tk.w = __builtin_fmaf(-r3, wjd, tk.w);
-    ja.x = __builtin_fmaf(-r3, ux, ja.x);
-    ja.y = __builtin_fmaf(-r3, uy, ja.y);
-    ja.z = __builtin_fmaf(-r3, uz, ja.z);
-    ja.w = __builtin_fmaf(r3, wkd, ja.w);
-    if (HAS_V) ja.w = __builtin_fmaf(r, wk.w, ja.w);
+    constexpr int G = R < 4 ? R : 4;
+    float ex[G], ey[G], ez[G], rr[G];
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        ex[k] = q.x - row[B + k].x;
+        ey[k] = q.y - row[B + k].y;
+        ez[k] = q.z - row[B + k].z;
+        float s = __builtin_fmaf(ex[k], ex[k], eps2);
+        s = __builtin_fmaf(ey[k], ey[k], s);
+        rr[k] = __builtin_fmaf(ez[k], ez[k], s);
+    }
+    rsq_group<G>(rr);
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        const AdjRow &w = row[B + k];
+        float4 &t4 = tk[B + k];
+        const float r = rr[k];
+        const float r2 = r * r;
+        const float r3 = r * r2;
+        float wke = w.wx * ex[k];
+        wke = __builtin_fmaf(w.wy, ey[k], wke);
+        wke = __builtin_fmaf(w.wz, ez[k], wke);
+        float wje = wq.x * ex[k];
+        wje = __builtin_fmaf(wq.y, ey[k], wje);
+        wje = __builtin_fmaf(wq.z, ez[k], wje);
+        const float c3 = __builtin_fmaf(q3n, wke, w.m3 * wje);
+        // without potential weights (v = 0) b vanishes and t = r^2 c3 exactly
+        // as the fused form with a zero addend
+        const float t = HAS_V ? __builtin_fmaf(r2, c3, __builtin_fmaf(w.m, wq.w, q.w * w.v))
+                              : r2 * c3;
+        const float ux = __builtin_fmaf(t, ex[k], __builtin_fmaf(q.w, w.wx, w.mn * wq.x));
+        const float uy = __builtin_fmaf(t, ey[k], __builtin_fmaf(q.w, w.wy, w.mn * wq.y));
+        const float uz = __builtin_fmaf(t, ez[k], __builtin_fmaf(q.w, w.wz, w.mn * wq.z));
+        t4.x = __builtin_fmaf(r3, ux, t4.x);
+        t4.y = __builtin_fmaf(r3, uy, t4.y);
+        t4.z = __builtin_fmaf(r3, uz, t4.z);
+        if (HAS_V) t4.w = __builtin_fmaf(r, wq.w, t4.w);
+        t4.w = __builtin_fmaf(r3, wje, t4.w);
+        ja.x = __builtin_fmaf(r3, ux, ja.x);
+        ja.y = __builtin_fmaf(r3, uy, ja.y);
+        ja.z = __builtin_fmaf(r3, uz, ja.z);
+        ja.w = __builtin_fmaf(r3, wke, ja.w);
+        if (HAS_V) ja.w = __builtin_fmaf(r, w.vn, ja.w);
+    }
+    if constexpr (R > 4) {
+        __builtin_amdgcn_sched_barrier(0);
+        adj_pair_rows<K, HAS_V, R - 4, B + 4>(row, q, wq, q3n, eps2, tk, ja);
+    }
 }
 
 // The k-side alone, with the pair removed when `skip` holds (diagonal tiles).
@@ -571,18 +560,16 @@ __device__ __forceinline__ void load_xw(const SymBwdArgs &A, int j, float4 &xm, 
     }
 }
 
-// Steps s0 .. s0 + NS - 1 of one tile for one wave (lane l meets tile
-// particle (l + s) mod 64 at step s).  Ring tiles: every row tile pair-once.
-// Diagonal tile t: row tile a = a0 + k pair-once if a < t, masked ordered
-// pairs if a == t, nothing if a > t (met on diagonal tile a).
-template <int K, bool DIAG, int NS = 64>
-__device__ __forceinline__ void adj_tile_steps(const float4 (&xk)[K], const float4 (&wk)[K],
-                                               const int (&kk)[K], const float4 *tile_xm,
-                                               const float4 *tile_wv, float4 *slot, int lane,
-                                               int a0, int t, int jbase, int s0, float eps2,
-                                               float4 (&tk)[K])
+// Steps s0 .. s0 + NS - 1 of diagonal tile t for one wave (lane l meets tile
+// particle (l + s) mod 64 at step s): row tile a = a0 + k pair-once if a < t,
+// masked ordered pairs if a == t, nothing if a > t (met on diagonal tile a).
+template <int K, int NS = 64>
+__device__ __forceinline__ void adj_diag_steps(const AdjRow (&row)[K], const int (&kk)[K],
+                                               const float4 *tile_xm, const float4 *tile_wv,
+                                               float4 *slot, int lane, int a0, int t, int jbase,
+                                               int s0, float eps2, float4 (&tk)[K])
 {
-    const bool any_once = !DIAG || a0 < t;
+    const bool any_once = a0 < t;
     float4 q = tile_xm[(lane + s0) & 63];
     float4 wq = tile_wv[(lane + s0) & 63];
     for (int s = s0; s < s0 + NS; ++s) {
@@ -593,17 +580,18 @@ __device__ __forceinline__ void adj_tile_steps(const float4 (&xk)[K], const floa
         if (any_once) ja = slot[jj];
         const float4 qn = tile_xm[(jj + 1) & 63];
         const float4 wqn = tile_wv[(jj + 1) & 63];
+        const float q3n = -3.0f * q.w;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (!DIAG || a0 + k < t) {
-                float jx, jy, jz, jm;
-                adj_pair_once(xk[k], wk[k], q, wq, eps2, tk[k], jx, jy, jz, jm);
-                ja.x += jx;
-                ja.y += jy;
-                ja.z += jz;
-                ja.w += jm;
+            if (a0 + k < t) {
+                const AdjRow one[1] = {row[k]};
+                float4 tk1[1] = {tk[k]};
+                adj_pair_rows<1, true>(one, q, wq, q3n, eps2, tk1, ja);
+                tk[k] = tk1[0];
             } else if (a0 + k == t) {
-                adj_row_term(xk[k], wk[k], q, wq, eps2, jbase + jj == kk[k], tk[k]);
+                const AdjRow &w = row[k];
+                adj_row_term(make_float4(w.x, w.y, w.z, w.m), make_float4(w.wx, w.wy, w.wz, w.v), q,
+                             wq, eps2, jbase + jj == kk[k], tk[k]);
             }
         }
         if (any_once) slot[jj] = ja;
@@ -621,10 +609,9 @@ __device__ __forceinline__ void adj_tile_steps(const float4 (&xk)[K], const floa
 // s0 .. s0 + NS - 1 (all 64 unless a tile's steps are split between waves;
 // s0 + NS <= 64 keeps every entry and slot below 128).
 template <int K, bool HAS_V = true, int NS = 64>
-__device__ __forceinline__ void adj_ring_steps(const float4 (&xk)[K], const float4 (&wk)[K],
-                                               const float4 *tile_xm, const float4 *tile_wv,
-                                               float4 *slot, int lane, int s0, float eps2,
-                                               float4 (&tk)[K])
+__device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const float4 *tile_xm,
+                                               const float4 *tile_wv, float4 *slot, int lane,
+                                               int s0, float eps2, float4 (&tk)[K])
 {
     const float4 *txm = tile_xm + lane + s0;
     const float4 *twv = tile_wv + lane + s0;
@@ -638,8 +625,7 @@ __device__ __forceinline__ void adj_ring_steps(const float4 (&xk)[K], const floa
         float4 ja = sl[s];
         const float4 qn = txm[s + 1];
         const float4 wqn = twv[s + 1];
-#pragma unroll
-        for (int k = 0; k < K; ++k) adj_pair_fold<HAS_V>(xk[k], wk[k], q, wq, eps2, tk[k], ja);
+        adj_pair_rows<K, HAS_V>(row, q, wq, -3.0f * q.w, eps2, tk, ja);
         sl[s] = ja;
         q = qn;
         wq = wqn;
@@ -656,6 +642,7 @@ __device__ __forceinline__ void adj_ring_steps(const float4 (&xk)[K], const floa
 // share the block's K * 64 rows and each takes 64 / W of every tile's steps
 // (workgroups W times shorter for the same block size, so the grid's drain
 // is shorter); their row sums are added in wave order at the end.
+// Buffers, barriers and slot sums as in pair_once_block.
 template <int W, int K, bool HAS_V, int S = 1>
 __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
 {
@@ -663,33 +650,34 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
     constexpr int PB = (S > 1 ? 64 : W * 64) * K;
     constexpr int TPB = PB / 64;
     constexpr int NS = 64 / S;
-    __shared__ float4 tile_xm[128];
-    __shared__ float4 tile_wv[128];
-    __shared__ float4 jacc[W][128];
+    constexpr int NB = kSymBuffers<W>;
+    __shared__ float4 tile_xm[NB * kTileLds];
+    __shared__ float4 tile_wv[NB * kTileLds];
+    __shared__ float4 jacc[NB * W][kSlotLds];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wv = tid >> 6;
     const int n = A.n;
     const int M = A.M, C = A.C;
-    const int I = blockIdx.x / C;
-    const int c = blockIdx.x - I * C;
-    const float eps2 = A.eps2;
+    const int c = blockIdx.x / M;  // chunk-major (ChunkCut)
+    const int I = blockIdx.x - c * M;
+    float eps2 = A.eps2;
+    in_vgpr(eps2);
     const int wrow = S > 1 ? 0 : wv;      // this wave's row group
     const int s0 = S > 1 ? wv * NS : 0;   // and first step of each tile
 
-    float4 xk[K], wk[K], acc[K];
+    AdjRow row[K];
+    float4 acc[K];
     int kk[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = I * PB + wrow * 64 * K + k * 64 + lane;
         kk[k] = i;
-        if (i < n) {
-            load_xw(A, i, xk[k], wk[k]);
-        } else {
-            xk[k] = make_float4(kBwdPadRow, kBwdPadRow, kBwdPadRow, 0.f);
-            wk[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        float4 xm = make_float4(kBwdPadRow, kBwdPadRow, kBwdPadRow, 0.f);
+        float4 wv4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i < n) load_xw(A, i, xm, wv4);
+        row[k] = AdjRow{xm.x, xm.y, xm.z, xm.w, -xm.w, 3.0f * xm.w, wv4.x, wv4.y, wv4.z, wv4.w, -wv4.w};
         acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 
@@ -699,25 +687,45 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
     const int d_lo = A.d_lo;
     const int dj = group_first_delta(d_lo);
     const int U = group_tiles(I, M, d_lo, A.d_hi, TPB);
-    const int u0 = (int)((long long)U * c / C);
-    const int u1 = (int)((long long)U * (c + 1) / C);
+    const int u0 = chunk_begin(A.cut, U, C, c);
+    const int u1 = chunk_begin(A.cut, U, C, c + 1);
     int u = u0, delta = 0, jbase = 0;
     for (; u < u1; ++u)
         if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
     float4 nxm = make_float4(0.f, 0.f, 0.f, 0.f), nwv = nxm;
     if (u < u1 && tid < 64) load_xw(A, jbase + tid, nxm, nwv);
+    // the rows have arrived here, so that no wait for them in the tile loop
+    // also waits for the prefetch
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        __asm__ volatile("" : "+v"(row[k].x), "+v"(row[k].y), "+v"(row[k].z), "+v"(row[k].m),
+                         "+v"(row[k].wx), "+v"(row[k].wy), "+v"(row[k].wz), "+v"(row[k].v));
 
-    while (u < u1) {
-        __syncthreads();  // the previous tile and its slot sums are done
+    const auto stage = [&](int b) {
         if (tid < 64) {
-            tile_xm[tid] = nxm;
-            tile_wv[tid] = nwv;
-            tile_xm[tid + 64] = nxm;
-            tile_wv[tid + 64] = nwv;
+            tile_xm[b * kTileLds + tid] = nxm;
+            tile_wv[b * kTileLds + tid] = nwv;
+            tile_xm[b * kTileLds + tid + 64] = nxm;
+            tile_wv[b * kTileLds + tid + 64] = nwv;
         }
-        jacc[wv][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-        jacc[wv][lane + 64] = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    const auto clear_slots = [&](int b) {
+        jacc[b * W + wv][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        jacc[b * W + wv][lane + 64] = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    int b = 0;
+    if (NB == 2 && u < u1) {
+        stage(0);
+        clear_slots(0);
         __syncthreads();
+    }
+    while (u < u1) {
+        if (NB == 1) {
+            __syncthreads();  // the previous tile and its slot sums are done
+            stage(0);
+            clear_slots(0);
+            __syncthreads();
+        }
         const int cur_u = u, cur_delta = delta, cur_base = jbase;
         for (++u; u < u1; ++u)
             if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
@@ -726,13 +734,14 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
         float4 tk[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) tk[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 *slot = &jacc[wv][0];
+        float4 *slot = &jacc[b * W + wv][0];
+        const float4 *txm = tile_xm + b * kTileLds, *twv = tile_wv + b * kTileLds;
         const bool diag = (cur_delta == 0);
         if (!diag)
-            adj_ring_steps<K, HAS_V, NS>(xk, wk, tile_xm, tile_wv, slot, lane, s0, eps2, tk);
+            adj_ring_steps<K, HAS_V, NS>(row, txm, twv, slot, lane, s0, eps2, tk);
         else
-            adj_tile_steps<K, true, NS>(xk, wk, kk, tile_xm, tile_wv, slot, lane, wrow * K,
-                                        cur_u, cur_base, s0, eps2, tk);
+            adj_diag_steps<K, NS>(row, kk, txm, twv, slot, lane, wrow * K, cur_u, cur_base, s0, eps2,
+                                  tk);
         __asm__ volatile("" ::: "memory");
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -741,29 +750,33 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
             acc[k].z += tk[k].z;
             acc[k].w += tk[k].w;
         }
+        if (NB == 2 && u < u1) stage(b ^ 1);
         __syncthreads();  // every wave's j-side slots are complete
+        if (NB == 2 && u < u1) clear_slots(b ^ 1);
+        // every wave left the opposite of particle e's sums in its slot e;
+        // they are added in wave order
         if (!diag) {
-            if (tid < 64) {
-                float4 sum = jacc[0][tid];
+            float4 *out = A.partial + (size_t)(C + cur_delta - dj) * n + cur_base;
+            if constexpr (W == 1) {
+                const float4 sum = jacc[0][tid];
+                if (cur_base + tid < n) out[tid] = make_float4(-sum.x, -sum.y, -sum.z, -sum.w);
+            } else {
+                for (int f = tid; f < 256; f += W * 64) {
+                    float sum = reinterpret_cast<const float *>(jacc[b * W])[f];
 #pragma unroll
-                for (int w2 = 1; w2 < W; ++w2) {
-                    const float4 v = jacc[w2][tid];
-                    sum.x += v.x;
-                    sum.y += v.y;
-                    sum.z += v.z;
-                    sum.w += v.w;
+                    for (int w2 = 1; w2 < W; ++w2)
+                        sum += reinterpret_cast<const float *>(jacc[b * W + w2])[f];
+                    if (cur_base + (f >> 2) < n) reinterpret_cast<float *>(out)[f] = -sum;
                 }
-                const int j = cur_base + tid;
-                if (j < n) A.partial[(size_t)(C + cur_delta - dj) * n + j] = sum;
             }
         } else if (wv == (S > 1 ? 0 : cur_u / K)) {
             // this wave holds diagonal tile cur_u's rows (lane-slot cur_u % K;
             // with a step split every wave does, and wave 0 adds); the
             // diagonal steps use slots 0..63 only
-            float4 sum = jacc[0][lane];
+            float4 sum = jacc[b * W][lane];
 #pragma unroll
             for (int w2 = 1; w2 < W; ++w2) {
-                const float4 v = jacc[w2][lane];
+                const float4 v = jacc[b * W + w2][lane];
                 sum.x += v.x;
                 sum.y += v.y;
                 sum.z += v.z;
@@ -773,12 +786,13 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 if (k == kt) {
-                    acc[k].x += sum.x;
-                    acc[k].y += sum.y;
-                    acc[k].z += sum.z;
-                    acc[k].w += sum.w;
+                    acc[k].x -= sum.x;
+                    acc[k].y -= sum.y;
+                    acc[k].z -= sum.z;
+                    acc[k].w -= sum.w;
                 }
         }
+        if (NB == 2) b ^= 1;
     }
     if (S > 1) {
         // the waves' row sums, added in wave order by wave 0 (through the
@@ -869,8 +883,10 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
     for (int g = 0; g < pl.groups; ++g) {
-        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, pl.C, 0, 0, partial};
+        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, pl.C, 0, 0, partial, ChunkCut{}};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
+        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * dev.num_cu,
+                          group_tiles(0, pl.M, A.d_lo, A.d_hi, PB / 64));
         prof_mark(stream, 0);
         if (gp)
             hipLaunchKernelGGL((backward_sym_kernel<W, K, true, S>), dim3(pl.M * pl.C),
