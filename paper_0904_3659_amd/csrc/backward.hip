@@ -852,12 +852,15 @@ nbody_status backward_rows_run(int least, const char *name, const Device &dev, c
 
 // OCC divides the chunk count and ROUNDS multiplies it (as in the
 // pair-once forward kernel); S splits each tile's steps between the waves.
-template <int W, int K, int OCC, int ROUNDS = 1, int S = 1>
+// The kernel may hold a block of W waves x K rows as KW waves x KK rows (the
+// same particles and plan).
+template <int W, int K, int OCC, int ROUNDS = 1, int S = 1, int KW = W, int KK = K>
 nbody_status run_backward_sym(const char *name, const Device &dev, const float *x, const float *m,
                               int n, float eps2, const float *ga, const float *gp, float *gx,
                               float *gm, hipStream_t stream, const LfEpi *epi, bool *fused,
                               const Arena &arena)
 {
+    static_assert(KW * KK == W * K && (S == 1 || KW == W), "the same block");
     constexpr int PB = (S > 1 ? 64 : W * 64) * K;
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -885,15 +888,15 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     for (int g = 0; g < pl.groups; ++g) {
         SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, pl.C, 0, 0, partial, ChunkCut{}};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
-        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * dev.num_cu,
+        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * W / KW * dev.num_cu,
                           group_tiles(0, pl.M, A.d_lo, A.d_hi, PB / 64));
         prof_mark(stream, 0);
         if (gp)
-            hipLaunchKernelGGL((backward_sym_kernel<W, K, true, S>), dim3(pl.M * pl.C),
-                               dim3(W * 64), 0, stream, A);
+            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, true, S>), dim3(pl.M * pl.C),
+                               dim3(KW * 64), 0, stream, A);
         else
-            hipLaunchKernelGGL((backward_sym_kernel<W, K, false, S>), dim3(pl.M * pl.C),
-                               dim3(W * 64), 0, stream, A);
+            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, false, S>), dim3(pl.M * pl.C),
+                               dim3(KW * 64), 0, stream, A);
         prof_mark(stream, 1);
         st = check_launch(name);
         if (st != NBODY_OK) return st;
@@ -951,6 +954,15 @@ int sym_block(const Variant &V)
     {"bwd_sym_w" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, 1, R>, \
      backward_sym_kernel<W, K, true>, W, K, 1, R}
 
+// The same with each block held by half the waves, twice the rows per lane:
+// half the LDS traffic per pair.  GPU time per call with / without potential
+// weights, 4 x 2 as 2 x 4: 671 / 612 -> 656 / 596 us at 40,000 bodies, 1016 /
+// 932 -> 982 / 898 at 50,021; 8 x 2 as 4 x 4: 27.9 / 25.7 -> 26.4 / 24.0 ms at
+// 2^18.
+#define BWD_SYM_R_HALF_VARIANT(W, K, R) \
+    {"bwd_sym_w" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, \
+     run_backward_sym<W, K, 1, R, 1, W / 2, 2 * K>, backward_sym_kernel<W, K, true>, W, K, 1, R}
+
 // Pair-once blocks of K * 64 rows whose W waves split each tile's steps, in
 // R rounds of workgroups.
 #define BWD_SYM_S_VARIANT(W, K, R) \
@@ -982,8 +994,8 @@ const Variant kVariants[] = {
     BWD_SYM_R_VARIANT(1, 2, 8),
     BWD_SYM_R_VARIANT(2, 2, 8),
     BWD_SYM_R_VARIANT(2, 1, 8),
-    BWD_SYM_R_VARIANT(8, 2, 8),
-    BWD_SYM_R_VARIANT(4, 2, 8),
+    BWD_SYM_R_HALF_VARIANT(8, 2, 8),
+    BWD_SYM_R_HALF_VARIANT(4, 2, 8),
     BWD_ROW_VARIANT(1),
     BWD_ROW_VARIANT(2),
     BWD_SYM_S_VARIANT(2, 2, 8),
