@@ -441,7 +441,6 @@ struct SymBwdArgs {
     int C;
     int d_lo, d_hi;   // ring deltas of this launch's group
     float4 *partial;  // [C + G][n]: (dL/dx, dL/dm)
-    ChunkCut cut;
 };
 
 // A lane's row constants in the form the pair terms read (all terms are then
@@ -660,7 +659,7 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
     const int wv = tid >> 6;
     const int n = A.n;
     const int M = A.M, C = A.C;
-    const int c = blockIdx.x / M;  // chunk-major (ChunkCut)
+    const int c = blockIdx.x / M;  // chunk-major (chunk_begin)
     const int I = blockIdx.x - c * M;
     float eps2 = A.eps2;
     in_vgpr(eps2);
@@ -687,8 +686,8 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
     const int d_lo = A.d_lo;
     const int dj = group_first_delta(d_lo);
     const int U = group_tiles(I, M, d_lo, A.d_hi, TPB);
-    const int u0 = chunk_begin(A.cut, U, C, c);
-    const int u1 = chunk_begin(A.cut, U, C, c + 1);
+    const int u0 = chunk_begin(U, C, c);
+    const int u1 = chunk_begin(U, C, c + 1);
     int u = u0, delta = 0, jbase = 0;
     for (; u < u1; ++u)
         if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
@@ -886,10 +885,8 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
     for (int g = 0; g < pl.groups; ++g) {
-        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, pl.C, 0, 0, partial, ChunkCut{}};
+        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, pl.C, 0, 0, partial};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
-        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * W / KW * dev.num_cu,
-                          group_tiles(0, pl.M, A.d_lo, A.d_hi, PB / 64));
         prof_mark(stream, 0);
         if (gp)
             hipLaunchKernelGGL((backward_sym_kernel<KW, KK, true, S>), dim3(pl.M * pl.C),

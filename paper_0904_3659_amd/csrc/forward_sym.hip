@@ -16,7 +16,6 @@ struct SymArgs {
     int C;            // chunks per block
     int d_lo, d_hi;   // ring deltas of this launch's group
     float4 *partial;  // [C + G][n]
-    ChunkCut cut;
 };
 
 template <int W, int K, bool POT>
@@ -24,9 +23,9 @@ __global__ __launch_bounds__(W * 64) void forward_sym_kernel(SymArgs A)
 {
     __shared__ float4 tile[kSymBuffers<W> * kTileLds];
     __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
-    const int c = blockIdx.x / A.M;  // chunk-major (ChunkCut)
+    const int c = blockIdx.x / A.M;  // chunk-major (chunk_begin)
     const int I = blockIdx.x - c * A.M;
-    pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.cut, A.d_lo, A.d_hi,
+    pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
                                       A.partial, tile, jacc);
 }
 
@@ -71,10 +70,8 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
     for (int g = 0; g < pl.groups; ++g) {
-        SymArgs A{x, m, n, eps2, pl.M, pl.C, 0, 0, partial, ChunkCut{}};
+        SymArgs A{x, m, n, eps2, pl.M, pl.C, 0, 0, partial};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
-        A.cut = chunk_cut(pl.C, pl.M, (int64_t)per_cu * W / KW * dev.num_cu,
-                          group_tiles(0, pl.M, A.d_lo, A.d_hi, PB / 64));
         prof_mark(stream, 0);
         if (p)
             hipLaunchKernelGGL((forward_sym_kernel<KW, KK, true>), dim3(pl.M * pl.C), dim3(KW * 64),

@@ -19,7 +19,7 @@
 //       H_I = (M-1)/2, plus delta = M/2 when M is even and I < M/2,
 //   so every unordered pair of distinct blocks is met exactly once.  The
 //   block's tile sequence (diagonal tiles, then ring tiles delta-major) is
-//   cut into the C chunks in falling shares (ChunkCut).
+//   cut into the C chunks (chunk_begin).
 //
 // j-tiles of 64 particles are staged in LDS twice over (entries e and
 // e + 64 hold particle e).  On a ring tile, lane l at step s (0..63) meets
@@ -54,8 +54,6 @@
 
 #include "common.hpp"
 
-#include <algorithm>
-#include <cmath>
 #include <cstdlib>
 
 namespace nbody {
@@ -212,39 +210,22 @@ inline void sym_group(const SymPlan &pl, int g, int *d_lo, int *d_hi)
     *d_hi = hi < pl.M / 2 + 1 ? hi : pl.M / 2 + 1;
 }
 
-// How a block's U tiles are cut into its C chunks: every chunk has one tile
-// and the other U - C are dealt in falling geometric shares, the first chunk
-// the largest.  The grid runs chunk-major (all blocks' first chunks, then all
-// second ones, ...), so a launch ends on its smallest workgroups instead of on
-// equal ones: with C equal chunks of 1/8 of a slot's share, the last of eight
+// First tile of chunk c of the C chunks a block's U tiles are cut into (c == C:
+// U).  Every chunk has one tile; the other U - C are dealt in equal shares to
+// the first half of the chunks and in shares falling linearly to nothing over
+// the second half.  The grid runs chunk-major (all blocks' first chunks, then
+// all second ones, ...), so a launch ends on its smallest workgroups instead
+// of on equal ones, and no workgroup's running sums span more than 4/3 of the
+// mean chunk.  With C equal chunks of 1/8 of a slot's share, the last of eight
 // rounds left CUs idle for 5-12% of the launch (65,536 and 2^18 bodies, 92 and
-// 87% CU-busy).  The last share is about 1/64 of what one workgroup slot
-// works in all (or one tile).  log2q = 0 with C <= 1.
-struct ChunkCut {
-    float log2q = 0.f;  // each share is q times the one before
-    float scale = 0.f;  // 1 / (1 - q^C)
-};
-
-// `resident` workgroups are resident at once, M blocks of at most U tiles.
-inline ChunkCut chunk_cut(int C, int M, int64_t resident, int U)
-{
-    ChunkCut cut;
-    if (C <= 1) return cut;
-    const double per_block = (double)resident / M;  // slots that share a block's tiles
-    const double least = std::max(0.5 / U, 1.0 / (64.0 * std::max(per_block, 1.0)));
-    cut.log2q = (float)(std::log2(least) / C);
-    cut.scale = (float)(1.0 / (1.0 - std::exp2((double)cut.log2q * C)));
-    return cut;
-}
-
-// First tile of chunk c (c == C: U).
-__device__ __forceinline__ int chunk_begin(const ChunkCut &cut, int U, int C, int c)
+// 87% CU-busy).
+__device__ __forceinline__ int chunk_begin(int U, int C, int c)
 {
     if (U <= C) return (int)((long long)U * c / C);
-    if (c == 0) return 0;
     if (c == C) return U;
-    const float share = (1.0f - __builtin_amdgcn_exp2f(cut.log2q * (float)c)) * cut.scale;
-    return c + min(U - C, (int)((float)(U - C) * share));
+    const float x = (float)c / (float)C;
+    const float t = fmaxf(x - 0.5f, 0.0f);
+    return c + (int)((float)(U - C) * (4.0f / 3.0f) * (x - t * t));
 }
 
 // Library workspace allowed for one pair-once evaluation of n particles
@@ -566,8 +547,8 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 template <int W, int K, bool SKIP_PAD = false, bool POT = true>
 __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                                                 const float *__restrict__ m, int n, float eps2,
-                                                int M, int I, int c, int C, const ChunkCut &cut,
-                                                int d_lo, int d_hi, float4 *partial, float4 *tile,
+                                                int M, int I, int c, int C, int d_lo, int d_hi,
+                                                float4 *partial, float4 *tile,
                                                 float4 (*jacc)[kSlotLds])
 {
     constexpr int PB = W * 64 * K;   // particles per block
@@ -604,8 +585,8 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     // tiles that hold only padding are skipped (uniform).
     const int U = group_tiles(I, M, d_lo, d_hi, TPB);
     const int dj = group_first_delta(d_lo);
-    const int u0 = chunk_begin(cut, U, C, c);
-    const int u1 = chunk_begin(cut, U, C, c + 1);
+    const int u0 = chunk_begin(U, C, c);
+    const int u1 = chunk_begin(U, C, c + 1);
     // Small workgroups prefetch the next tile into registers while the
     // current one is consumed; 16-wave blocks (one per CU, 128 VGPRs) have
     // no registers to spare and rely on the other waves to hide the load.
