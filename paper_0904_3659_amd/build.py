@@ -1,4 +1,5 @@
-"""Build libnbody.so (HIP, gfx950) in-tree with hipcc.
+"""Build libnbody.so (HIP, gfx950) in-tree with hipcc, and the native front of
+the Python binding (_binding.so, host code against torch's headers) with g++.
 
 Run as ``python -m paper_0904_3659_amd.build``; ``__graft_entry__.build()``
 calls :func:`build`.
@@ -14,6 +15,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIBRARY = os.path.join(HERE, "libnbody.so")
+BINDING = os.path.join(HERE, "_binding.so")
 ARCH = "gfx950"
 
 HIPFLAGS = [
@@ -36,7 +38,28 @@ def build(verbose: bool = False, extra: list[str] | None = None) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIBRARY)
+    build_binding(verbose)
     return LIBRARY
+
+
+def build_binding(verbose: bool = False) -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = BINDING + ".tmp"
+    includes = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{i}" for i in includes), os.path.join(CSRC, "binding.cpp"),
+           f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, BINDING)
+    return BINDING
 
 
 if __name__ == "__main__":

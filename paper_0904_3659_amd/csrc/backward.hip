@@ -20,6 +20,7 @@
 #include "wave_sum.hpp"
 
 #include <cstring>
+#include <type_traits>
 
 namespace nbody {
 namespace {
@@ -35,7 +36,11 @@ struct BwdArgs {
     float4 *partial;  // [splits][n] (dL/dx, dL/dm) per split when PARTIAL
     float *gx;
     float *gm;
-    LfEpi e;  // row groups: the leap-frog update instead of the stores
+};
+
+// Row groups with the leap-frog update instead of the stores.
+struct BwdEpiArgs : BwdArgs {
+    LfEpi e;
 };
 
 struct RowAcc {
@@ -287,7 +292,8 @@ __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4
 }
 
 template <int K, bool HAS_V, bool EPI = false>
-__global__ __launch_bounds__(256) void backward_row_kernel(BwdArgs P)
+__global__ __launch_bounds__(256) void backward_row_kernel(
+    typename std::conditional<EPI, BwdEpiArgs, BwdArgs>::type P)
 {
     constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
     __shared__ float red[4][8 * K];
@@ -369,7 +375,7 @@ __global__ __launch_bounds__(256) void backward_row_kernel(BwdArgs P)
         return s;
     };
     if (c == 3) {
-        if (EPI)
+        if constexpr (EPI)
             P.e.lm[i] = __builtin_fmaf(P.e.c, total(4), P.e.lm[i]);
         else if (P.gm)
             P.gm[i] = total(4);
@@ -378,20 +384,21 @@ __global__ __launch_bounds__(256) void backward_row_kernel(BwdArgs P)
     // dL/dx_k = w_k A - m_k B - C
     const float w = P.ga ? P.ga[3 * (size_t)i + c] : 0.f;
     const float g = w * total(0) - P.m[i] * total(1 + c) - total(5 + c);
-    if (EPI)
+    if constexpr (EPI)
         lf_coord(P.e, 3 * (size_t)i + c, g);
     else
         P.gx[3 * (size_t)i + c] = g;
 }
 
-using RowFn = void (*)(const BwdArgs &, hipStream_t);
+using RowFn = void (*)(const BwdArgs &, const LfEpi *, hipStream_t);
 
 template <int K>
-static void launch_bwd_rows(const BwdArgs &P, hipStream_t stream)
+static void launch_bwd_rows(const BwdArgs &P, const LfEpi *epi, hipStream_t stream)
 {
     const dim3 grid((unsigned)((P.n + K - 1) / K));
-    if (P.e.mode != kLfNone)
-        hipLaunchKernelGGL((backward_row_kernel<K, false, true>), grid, dim3(256), 0, stream, P);
+    if (epi)
+        hipLaunchKernelGGL((backward_row_kernel<K, false, true>), grid, dim3(256), 0, stream,
+                           (BwdEpiArgs{P, *epi}));
     else if (P.gp)
         hipLaunchKernelGGL((backward_row_kernel<K, true>), grid, dim3(256), 0, stream, P);
     else
@@ -835,16 +842,14 @@ nbody_status backward_rows_run(int least, const char *name, const Device &dev, c
                                float *gx, float *gm, hipStream_t stream, const LfEpi *epi,
                                bool *fused)
 {
-    BwdArgs P{x, m, ga, gp, n, eps2, 0, nullptr, gx, gm, LfEpi{}};
+    const BwdArgs P{x, m, ga, gp, n, eps2, 0, nullptr, gx, gm};
     // an update that changes lv, the weights the other groups still read,
     // needs a second buffer for it
-    if (epi && !gp && epi->mode == kLfAdjoint && (!epi->chain || epi->lvo)) {
-        P.e = *epi;
-        if (fused) *fused = true;
-    }
+    if (epi && (gp || epi->mode != kLfAdjoint || (epi->chain && !epi->lvo))) epi = nullptr;
+    if (epi && fused) *fused = true;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     prof_mark(stream, 0);
-    kRowLaunch[row_group_rows(n, dev.num_cu, least, kBwdRowMax, 10)](P, stream);
+    kRowLaunch[row_group_rows(n, dev.num_cu, least, kBwdRowMax, 10)](P, epi, stream);
     prof_mark(stream, 1);
     return check_launch(name);
 }
@@ -1135,7 +1140,7 @@ nbody_status backward_run(int variant, const Device &dev, const float *x, const 
     int splits = 1, chunk = 0;
     bwd_gather_geometry(V, n, dev.num_cu, &splits, &chunk);
 
-    BwdArgs P{x, m, ga, gp, n, eps2, chunk, nullptr, gx, gm, LfEpi{}};
+    BwdArgs P{x, m, ga, gp, n, eps2, chunk, nullptr, gx, gm};
     if (splits == 1) {
         if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
         prof_mark(stream, 0);

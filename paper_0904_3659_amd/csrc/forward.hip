@@ -351,7 +351,12 @@ struct RowArgs {
     float eps2;
     float *a;
     float *p;
-    LfEpi e;  // EPI: the leap-frog update after the store of a
+};
+
+// With the leap-frog update after the store of a (a struct of its own: the
+// launch copies its arguments, and a plain call should not copy these).
+struct RowEpiArgs : RowArgs {
+    LfEpi e;
 };
 
 constexpr int kRowMax = 8;  // rows per group
@@ -387,7 +392,8 @@ __device__ __forceinline__ void row_tile(const float (&xi)[K], const float (&yi)
 }
 
 template <int K, bool POT, bool EPI = false>
-__global__ __launch_bounds__(256) void forward_row_kernel(RowArgs P)
+__global__ __launch_bounds__(256) void forward_row_kernel(
+    typename std::conditional<EPI, RowEpiArgs, RowArgs>::type P)
 {
     constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
     __shared__ float red[4][4 * K];
@@ -449,25 +455,26 @@ __global__ __launch_bounds__(256) void forward_row_kernel(RowArgs P)
     for (int w = 1; w < 4; ++w) s += red[w][threadIdx.x];
     if (c < 3) {
         P.a[3 * (size_t)(i0 + k) + c] = s;
-        if (EPI) lf_coord(P.e, 3 * (size_t)(i0 + k) + c, s);
+        if constexpr (EPI) lf_coord(P.e, 3 * (size_t)(i0 + k) + c, s);
     } else if (POT) {
         P.p[i0 + k] = s;
     }
 }
 
 template <int K>
-static void launch_rows(const RowArgs &P, hipStream_t stream)
+static void launch_rows(const RowArgs &P, const LfEpi *epi, hipStream_t stream)
 {
     const dim3 grid((unsigned)((P.n + K - 1) / K));
-    if (P.e.mode != kLfNone)
-        hipLaunchKernelGGL((forward_row_kernel<K, false, true>), grid, dim3(256), 0, stream, P);
+    if (epi)
+        hipLaunchKernelGGL((forward_row_kernel<K, false, true>), grid, dim3(256), 0, stream,
+                           (RowEpiArgs{P, *epi}));
     else if (P.p)
         hipLaunchKernelGGL((forward_row_kernel<K, true>), grid, dim3(256), 0, stream, P);
     else
         hipLaunchKernelGGL((forward_row_kernel<K, false>), grid, dim3(256), 0, stream, P);
 }
 
-using RowFn = void (*)(const RowArgs &, hipStream_t);
+using RowFn = void (*)(const RowArgs &, const LfEpi *, hipStream_t);
 
 using LaFn = void (*)(LaArgs);
 
@@ -728,16 +735,14 @@ nbody_status forward_rows_run(int least, const char *name, const Device &dev, co
                               const float *m, int n, float eps2, float *a, float *p,
                               hipStream_t stream, const LfEpi *epi, bool *fused)
 {
-    RowArgs P{x, m, n, eps2, a, p, LfEpi{}};
+    const RowArgs P{x, m, n, eps2, a, p};
     // an update that drifts x needs a second position buffer: the other
     // groups still read x
-    if (epi && !p && epi->mode == kLfKick && (!epi->drift || epi->xo)) {
-        P.e = *epi;
-        if (fused) *fused = true;
-    }
+    if (epi && (p || epi->mode != kLfKick || (epi->drift && !epi->xo))) epi = nullptr;
+    if (epi && fused) *fused = true;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     prof_mark(stream, 0);
-    kRowLaunch[row_group_rows(n, dev.num_cu, least, kRowMax, 5)](P, stream);
+    kRowLaunch[row_group_rows(n, dev.num_cu, least, kRowMax, 5)](P, epi, stream);
     prof_mark(stream, 1);
     return check_launch(name);
 }

@@ -5,7 +5,10 @@ current HIP device, right shape), their device pointers and torch's current
 stream are handed to the C ABI (include/nbody.h), and a failing status is
 raised as :class:`NBodyError`.  Every arithmetic step runs in the HIP
 kernels of the library; there is no CPU fallback, and a missing library
-raises at first use.
+raises at first use.  The common case of :func:`forces` and
+:func:`forces_backward` takes the native front (``_binding.so``,
+csrc/binding.cpp), which does the same checks; every other case, and every
+error, is handled here.
 """
 
 from __future__ import annotations
@@ -42,6 +45,8 @@ class NBodyError(RuntimeError):
 
 
 _LIB = None
+# the native front and its calls, set when the library is loaded
+_native = _fast_forces = _fast_backward = None
 _vp, _i64, _f32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_float
 
 
@@ -95,7 +100,22 @@ def lib() -> ctypes.CDLL:
         if L.nbody_abi_version() != ABI_VERSION:
             raise NBodyError(5, f"ABI version {L.nbody_abi_version()} != {ABI_VERSION}")
         _LIB = L
+        _bind_native(L)
     return _LIB
+
+
+def _bind_native(L) -> None:
+    """Hand the library's addresses to the native front.  With several devices
+    a call may have to make its tensors' device current, which is left to the
+    Python path."""
+    global _native, _fast_forces, _fast_backward
+    _native = _fast_forces = _fast_backward = None
+    if _RAW_STREAM is None or torch.cuda.device_count() != 1 or not os.path.exists(_build.BINDING):
+        return
+    from . import _binding
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    _binding.bind(address(L.nbody_forces_ex), address(L.nbody_forces_backward), _RAW_STREAM)
+    _native, _fast_forces, _fast_backward = _binding, _binding.forces, _binding.backward
 
 
 def _check(status: int) -> None:
@@ -180,6 +200,12 @@ def forces(x: torch.Tensor, m: torch.Tensor, eps2: float, *, out=None, potential
     potential is not stored and ``p`` is returned as None.  ``f64_sum`` keeps
     each row's running sum (over j-tiles and j-splits) in float64.
     """
+    if _fast_forces is not None:
+        r = _fast_forces(x, m, eps2, out, potential, F64_SUM if f64_sum else 0)
+        if type(r) is tuple:
+            return r
+        if r is not None:
+            _check(r)
     sh = x.shape
     n = sh[0] if len(sh) == 2 else -1
     _want(x, "x", (n, 3))
@@ -216,7 +242,7 @@ class BoundForces:
         call()            # a, p = forces of the current x, m
     """
 
-    __slots__ = ("_fn", "_args", "_dev", "_keep")
+    __slots__ = ("_fn", "_args", "_dev", "_keep", "_native")
 
     def __init__(self, x: torch.Tensor, m: torch.Tensor, eps2: float, a: torch.Tensor,
                  p: torch.Tensor | None = None):
@@ -232,8 +258,16 @@ class BoundForces:
         self._args = (_ptr(x), _ptr(m), n, _eps2(eps2), _ptr(a), _ptr(p))
         self._dev = dev
         self._keep = (x, m, a, p)
+        self._native = None
+        if _native is not None and dev.index is not None:
+            self._native = _native.prepare(*self._args[:5], self._args[5] or 0, dev.index)
 
     def __call__(self) -> None:
+        if self._native is not None:
+            status = _native.call(self._native)
+            if status:
+                _check(status)
+            return
         dev = self._dev
         with _on(dev):
             status = self._fn(*self._args, _stream(dev))
@@ -263,6 +297,12 @@ def forces_noalloc(x: torch.Tensor, m: torch.Tensor, eps2: float, a: torch.Tenso
 
 def forces_backward(x, m, eps2, grad_a=None, grad_p=None, *, need_grad_m: bool = True, out=None):
     """Vector-Jacobian product of :func:`forces`: (dL/dx [n,3], dL/dm [n] or None)."""
+    if _fast_backward is not None:
+        r = _fast_backward(x, m, eps2, grad_a, grad_p, need_grad_m, out)
+        if type(r) is tuple:
+            return r
+        if r is not None:
+            _check(r)
     sh = x.shape
     n = sh[0] if len(sh) == 2 else -1
     _want(x, "x", (n, 3))
