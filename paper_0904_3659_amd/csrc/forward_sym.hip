@@ -18,15 +18,40 @@ struct SymArgs {
     float4 *partial;  // [C + G][n]
 };
 
+// Waves per workgroup: those of a block, or those that split a one-wave
+// block's tiles.
+template <int W>
+constexpr int kSymSplit = W == 1 ? kTileSplit : 1;
+template <int W>
+constexpr int kSymThreads = 64 * W * kSymSplit<W>;
+
 template <int W, int K, bool POT>
-__global__ __launch_bounds__(W * 64) void forward_sym_kernel(SymArgs A)
+__global__ __launch_bounds__(kSymThreads<W>) void forward_sym_kernel(SymArgs A)
 {
-    __shared__ float4 tile[kSymBuffers<W> * kTileLds];
-    __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
     const int c = blockIdx.x / A.M;  // chunk-major (chunk_begin)
     const int I = blockIdx.x - c * A.M;
-    pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
-                                      A.partial, tile, jacc);
+    if constexpr (W == 1) {
+        __shared__ float4 lds[kTileSplit * kWaveLds];
+        pair_once_block<1, K, false, POT, kTileSplit>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo,
+                                                      A.d_hi, A.partial, lds, nullptr);
+    } else {
+        __shared__ float4 tile[kSymBuffers<W> * kTileLds];
+        __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
+        pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
+                                          A.partial, tile, jacc);
+    }
+}
+
+// Workgroups of W waves per CU (counting each wave of a tile split as one).
+template <int W, int K>
+nbody_status sym_occupancy(int *per_cu)
+{
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        per_cu, forward_sym_kernel<W, K, true>, kSymThreads<W>, 0);
+    if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
+    if (*per_cu < 1) *per_cu = 1;
+    *per_cu *= kSymSplit<W>;
+    return NBODY_OK;
 }
 
 // OCC divides the chunk count: 1 fills every resident workgroup slot once;
@@ -47,10 +72,8 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     int per_cu = 0;
     // sized by the kernel that forms the potential, also when p is not
     // stored: the same plan keeps a bitwise the same either way
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, forward_sym_kernel<W, K, true>, W * 64, 0);
-    if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-    if (per_cu < 1) per_cu = 1;
+    nbody_status st = sym_occupancy<W, K>(&per_cu);
+    if (st != NBODY_OK) return st;
     SymPlan pl;
     if (!sym_plan(n, PB, (int64_t)per_cu * dev.num_cu * ROUNDS, OCC,
                   arena.budget(sym_workspace_budget(n)), &pl))
@@ -58,7 +81,7 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
                     "n = %d needs more than the %zu-byte workspace limit of %s", n,
                     arena.budget(sym_workspace_budget(n)), name);
     void *ws = nullptr;
-    nbody_status st = arena.get(dev, stream, pl.bytes(), &ws);
+    st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
     if constexpr (W == 1 && K == 2)
         // the plan and its workspace stay the variant's, whichever kernel runs
@@ -69,42 +92,34 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
                                 : nullptr;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
+    // a tile split needs a partial per workgroup, fewer than the plan allows
+    const int C = (pl.C + kSymSplit<KW> - 1) / kSymSplit<KW>;
     for (int g = 0; g < pl.groups; ++g) {
-        SymArgs A{x, m, n, eps2, pl.M, pl.C, 0, 0, partial};
+        SymArgs A{x, m, n, eps2, pl.M, C, 0, 0, partial};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (p)
-            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, true>), dim3(pl.M * pl.C), dim3(KW * 64),
-                               0, stream, A);
+            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, true>), dim3(pl.M * C),
+                               dim3(kSymThreads<KW>), 0, stream, A);
         else
-            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, false>), dim3(pl.M * pl.C), dim3(KW * 64),
-                               0, stream, A);
+            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, false>), dim3(pl.M * C),
+                               dim3(kSymThreads<KW>), 0, stream, A);
         prof_mark(stream, 1);
         st = check_launch(name);
         if (st != NBODY_OK) return st;
         const int first = g == 0, last = g == pl.groups - 1;
         if (last && lf)
             hipLaunchKernelGGL((slot_fold_kernel<PB, true>), dim3((n + 63) / 64), dim3(256), 0,
-                               stream, partial, n, pl.M, pl.C, A.d_lo, A.d_hi, first, last, acc, a,
+                               stream, partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, a,
                                p, *epi);
         else
             hipLaunchKernelGGL((slot_fold_kernel<PB>), dim3((n + 63) / 64), dim3(256), 0, stream,
-                               partial, n, pl.M, pl.C, A.d_lo, A.d_hi, first, last, acc, a, p,
+                               partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, a, p,
                                LfEpi{});
         st = check_launch("slot_fold");
         if (st != NBODY_OK) return st;
     }
     if (lf && fused) *fused = true;
-    return NBODY_OK;
-}
-
-template <int W, int K>
-nbody_status sym_occupancy(int *per_cu)
-{
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        per_cu, forward_sym_kernel<W, K, true>, W * 64, 0);
-    if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-    if (*per_cu < 1) *per_cu = 1;
     return NBODY_OK;
 }
 

@@ -511,6 +511,15 @@ __device__ __forceinline__ void diag_tile_steps(const float (&xi)[K], const floa
     }
 }
 
+// LDS entries of one wave of a tile-split workgroup: the tile and the slots,
+// and at the end K <= 4 rows of row sums.
+constexpr int kWaveLds = kTileLds + kSlotLds;
+// Waves that share a one-wave block's chunk.  The chunk partials of one-wave
+// blocks were two thirds of what the fold reads: 1 tile, 1 partial.  With four
+// waves to a partial the fold takes 4.9 us instead of 9.1 at 16,384 bodies, 9
+// instead of 21 at 30,000.
+constexpr int kTileSplit = 4;
+
 // LDS buffers of a pair-once workgroup: blocks of several waves keep two tiles
 // and two sets of slots, so that one barrier per tile suffices; a one-wave
 // block needs no barrier, and its single set leaves room for more workgroups.
@@ -544,7 +553,13 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 // barrier every wave clears its slots of the other set (whose sums were read
 // before the barrier) and all threads share the sum of the W slot sets, one
 // component each.
-template <int W, int K, bool SKIP_PAD = false, bool POT = true>
+//
+// T > 1 (one-wave blocks): T waves of a workgroup hold the same rows and take
+// one of T consecutive sub-chunks of chunk c each, with an LDS region of
+// kWaveLds entries per wave (its tile, then its slots) from `tile` on; their
+// row sums are added in wave order at the end, so that a chunk writes (and the
+// fold reads) one partial for T waves' tiles.
+template <int W, int K, bool SKIP_PAD = false, bool POT = true, int T = 1>
 __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                                                 const float *__restrict__ m, int n, float eps2,
                                                 int M, int I, int c, int C, int d_lo, int d_hi,
@@ -554,9 +569,24 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     constexpr int PB = W * 64 * K;   // particles per block
     constexpr int TPB = PB / 64;     // 64-particle tiles per block
     constexpr int NB = kSymBuffers<W>;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    static_assert(T == 1 || (W == 1 && K * 64 <= kWaveLds), "a tile split is of one-wave blocks");
+    const int lane = threadIdx.x & 63;
+    const int tw = T > 1 ? (int)(threadIdx.x >> 6) : 0;  // which of T sub-chunks
+    const int tid = T > 1 ? lane : (int)threadIdx.x;     // thread of the block's W waves
     const int wv = tid >> 6;
+    float4 *const lds = tile;
+    if (T > 1) {
+        tile = lds + tw * kWaveLds;
+        jacc = reinterpret_cast<float4(*)[kSlotLds]>(tile + kTileLds);
+    }
+    // One wave's LDS accesses complete in issue order: between its lanes a
+    // compiler barrier is enough.
+    const auto block_sync = [&]() {
+        if (W == 1)
+            __asm__ volatile("" ::: "memory");
+        else
+            __syncthreads();
+    };
 
     // ---- own rows
     float xi[K], yi[K], zi[K], mi[K];
@@ -585,8 +615,8 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     // tiles that hold only padding are skipped (uniform).
     const int U = group_tiles(I, M, d_lo, d_hi, TPB);
     const int dj = group_first_delta(d_lo);
-    const int u0 = chunk_begin(U, C, c);
-    const int u1 = chunk_begin(U, C, c + 1);
+    const int u0 = chunk_begin(U, C * T, c * T + tw);
+    const int u1 = chunk_begin(U, C * T, c * T + tw + 1);
     // Small workgroups prefetch the next tile into registers while the
     // current one is consumed; 16-wave blocks (one per CU, 128 VGPRs) have
     // no registers to spare and rely on the other waves to hide the load.
@@ -643,10 +673,10 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
         if (NB == 1) {
             // the previous tile and its slot sums are done (the LDS buffers
             // free on entry: callers may loop over blocks)
-            __syncthreads();
+            block_sync();
             stage(0);
             clear_slots(0);
-            __syncthreads();
+            block_sync();
         }
         const int cur_u = u, cur_delta = delta, cur_base = jbase;
         advance();
@@ -694,7 +724,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
             ap[k] += tp[k];
         }
         if (NB == 2 && u < u1) stage(b ^ 1);
-        __syncthreads();  // every wave's j-side slots are complete
+        block_sync();  // every wave's j-side slots are complete
         if (NB == 2 && u < u1) clear_slots(b ^ 1);
         // every wave left particle e's sums in its slot e (components xyz with
         // the opposite sign); they are added in wave order
@@ -737,9 +767,26 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
         if (NB == 2) b ^= 1;
     }
 
+    if constexpr (T == 1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (ii[k] < n) partial[(size_t)c * n + ii[k]] = make_float4(ax[k], ay[k], az[k], ap[k]);
+        for (int k = 0; k < K; ++k)
+            if (ii[k] < n) partial[(size_t)c * n + ii[k]] = make_float4(ax[k], ay[k], az[k], ap[k]);
+    } else {
+        // the T waves' row sums through their own LDS regions, one component
+        // of every 64 T / 4 rows per thread
+        __asm__ volatile("" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < K; ++k) tile[k * 64 + lane] = make_float4(ax[k], ay[k], az[k], ap[k]);
+        __syncthreads();
+        float *out = reinterpret_cast<float *>(partial + (size_t)c * n + I * PB);
+        const float *all = reinterpret_cast<const float *>(lds);
+        for (int f = threadIdx.x; f < K * 256; f += T * 64) {
+            float sum = all[f];
+#pragma unroll
+            for (int w = 1; w < T; ++w) sum += all[w * kWaveLds * 4 + f];
+            if (I * PB + (f >> 2) < n) out[f] = sum;
+        }
+    }
 }
 
 }  // namespace nbody
