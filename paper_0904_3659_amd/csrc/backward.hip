@@ -648,22 +648,40 @@ __device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const flo
 // share the block's K * 64 rows and each takes 64 / W of every tile's steps
 // (workgroups W times shorter for the same block size, so the grid's drain
 // is shorter); their row sums are added in wave order at the end.
-// Buffers, barriers and slot sums as in pair_once_block.
+// Buffers, barriers, slot sums and the tile split of one-wave blocks (T waves)
+// as in pair_once_block.
+template <int W>
+constexpr int kAdjSplit = W == 1 ? kTileSplit : 1;
+template <int W>
+constexpr int kAdjThreads = 64 * W * kAdjSplit<W>;
+
 template <int W, int K, bool HAS_V, int S = 1>
-__global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
+__global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs A)
 {
     static_assert(S == 1 || (S == W && K <= 2), "a step split spans all waves, two rows at most");
     constexpr int PB = (S > 1 ? 64 : W * 64) * K;
     constexpr int TPB = PB / 64;
     constexpr int NS = 64 / S;
     constexpr int NB = kSymBuffers<W>;
-    __shared__ float4 tile_xm[NB * kTileLds];
-    __shared__ float4 tile_wv[NB * kTileLds];
-    __shared__ float4 jacc[NB * W][kSlotLds];
+    constexpr int T = kAdjSplit<W>;
+    static_assert(K * 64 <= kTileLds + kTileLds + kSlotLds, "row sums fit a wave's region");
+    // per set of W waves: the tile twice over, its weights, the W slot arrays
+    constexpr int kLds = NB * (2 * kTileLds + W * kSlotLds);
+    __shared__ float4 lds[T * kLds];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    const int lane = threadIdx.x & 63;
+    const int tw = T > 1 ? (int)(threadIdx.x >> 6) : 0;  // which of T sub-chunks
+    const int tid = T > 1 ? lane : (int)threadIdx.x;     // thread of the block's W waves
     const int wv = tid >> 6;
+    float4 *const tile_xm = lds + tw * kLds;
+    float4 *const tile_wv = tile_xm + NB * kTileLds;
+    float4(*const jacc)[kSlotLds] = reinterpret_cast<float4(*)[kSlotLds]>(tile_wv + NB * kTileLds);
+    const auto block_sync = [&]() {
+        if (W == 1)
+            __asm__ volatile("" ::: "memory");
+        else
+            __syncthreads();
+    };
     const int n = A.n;
     const int M = A.M, C = A.C;
     const int c = blockIdx.x / M;  // chunk-major (chunk_begin)
@@ -693,8 +711,8 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
     const int d_lo = A.d_lo;
     const int dj = group_first_delta(d_lo);
     const int U = group_tiles(I, M, d_lo, A.d_hi, TPB);
-    const int u0 = chunk_begin(U, C, c);
-    const int u1 = chunk_begin(U, C, c + 1);
+    const int u0 = chunk_begin(U, C * T, c * T + tw);
+    const int u1 = chunk_begin(U, C * T, c * T + tw + 1);
     int u = u0, delta = 0, jbase = 0;
     for (; u < u1; ++u)
         if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
@@ -727,10 +745,10 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
     }
     while (u < u1) {
         if (NB == 1) {
-            __syncthreads();  // the previous tile and its slot sums are done
+            block_sync();  // the previous tile and its slot sums are done
             stage(0);
             clear_slots(0);
-            __syncthreads();
+            block_sync();
         }
         const int cur_u = u, cur_delta = delta, cur_base = jbase;
         for (++u; u < u1; ++u)
@@ -757,7 +775,7 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
             acc[k].w += tk[k].w;
         }
         if (NB == 2 && u < u1) stage(b ^ 1);
-        __syncthreads();  // every wave's j-side slots are complete
+        block_sync();  // every wave's j-side slots are complete
         if (NB == 2 && u < u1) clear_slots(b ^ 1);
         // every wave left the opposite of particle e's sums in its slot e;
         // they are added in wave order
@@ -821,9 +839,37 @@ __global__ __launch_bounds__(W * 64) void backward_sym_kernel(SymBwdArgs A)
                 acc[k].w += v.w;
             }
     }
+    if constexpr (T == 1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (kk[k] < n) A.partial[(size_t)c * n + kk[k]] = acc[k];
+        for (int k = 0; k < K; ++k)
+            if (kk[k] < n) A.partial[(size_t)c * n + kk[k]] = acc[k];
+    } else {
+        // the T waves' row sums through their own LDS regions
+        __asm__ volatile("" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < K; ++k) tile_xm[k * 64 + lane] = acc[k];
+        __syncthreads();
+        float *out = reinterpret_cast<float *>(A.partial + (size_t)c * n + I * PB);
+        const float *all = reinterpret_cast<const float *>(lds);
+        for (int f = threadIdx.x; f < K * 256; f += T * 64) {
+            float sum = all[f];
+#pragma unroll
+            for (int w = 1; w < T; ++w) sum += all[w * kLds * 4 + f];
+            if (I * PB + (f >> 2) < n) out[f] = sum;
+        }
+    }
+}
+
+// Workgroups of W waves per CU (counting each wave of a tile split as one).
+template <int W, int K, int S>
+nbody_status adj_occupancy(int *per_cu)
+{
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        per_cu, backward_sym_kernel<W, K, true, S>, kAdjThreads<W>, 0);
+    if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
+    if (*per_cu < 1) *per_cu = 1;
+    *per_cu *= kAdjSplit<W>;
+    return NBODY_OK;
 }
 
 // Sizes at which the two-wave step-split pair-once variants run the row-group
@@ -867,10 +913,8 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     static_assert(KW * KK == W * K && (S == 1 || KW == W), "the same block");
     constexpr int PB = (S > 1 ? 64 : W * 64) * K;
     int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, backward_sym_kernel<W, K, true, S>, W * 64, 0);
-    if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-    if (per_cu < 1) per_cu = 1;
+    nbody_status st = adj_occupancy<W, K, S>(&per_cu);
+    if (st != NBODY_OK) return st;
     SymPlan pl;
     if (!sym_plan(n, PB, (int64_t)per_cu * dev.num_cu * ROUNDS, OCC,
                   arena.budget(sym_workspace_budget(n)), &pl))
@@ -878,7 +922,7 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
                     "n = %d needs more than the %zu-byte workspace limit of %s", n,
                     arena.budget(sym_workspace_budget(n)), name);
     void *ws = nullptr;
-    nbody_status st = arena.get(dev, stream, pl.bytes(), &ws);
+    st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
     if constexpr (S == 2 && K == 2)
         // the plan and its workspace stay the variant's, whichever kernel runs
@@ -889,27 +933,29 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
                                 : nullptr;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
+    // a tile split needs a partial per workgroup, fewer than the plan allows
+    const int C = (pl.C + kAdjSplit<KW> - 1) / kAdjSplit<KW>;
     for (int g = 0; g < pl.groups; ++g) {
-        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, pl.C, 0, 0, partial};
+        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, C, 0, 0, partial};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (gp)
-            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, true, S>), dim3(pl.M * pl.C),
-                               dim3(KW * 64), 0, stream, A);
+            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, true, S>), dim3(pl.M * C),
+                               dim3(kAdjThreads<KW>), 0, stream, A);
         else
-            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, false, S>), dim3(pl.M * pl.C),
-                               dim3(KW * 64), 0, stream, A);
+            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, false, S>), dim3(pl.M * C),
+                               dim3(kAdjThreads<KW>), 0, stream, A);
         prof_mark(stream, 1);
         st = check_launch(name);
         if (st != NBODY_OK) return st;
         const int first = g == 0, last = g == pl.groups - 1;
         if (last && lf)
             hipLaunchKernelGGL((slot_fold_kernel<PB, true>), dim3((n + 63) / 64), dim3(256), 0,
-                               stream, partial, n, pl.M, pl.C, A.d_lo, A.d_hi, first, last, acc, gx,
+                               stream, partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, gx,
                                gm, *epi);
         else
             hipLaunchKernelGGL((slot_fold_kernel<PB>), dim3((n + 63) / 64), dim3(256), 0, stream,
-                               partial, n, pl.M, pl.C, A.d_lo, A.d_hi, first, last, acc, gx, gm,
+                               partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, gx, gm,
                                LfEpi{});
         st = check_launch("slot_fold");
         if (st != NBODY_OK) return st;
@@ -924,8 +970,6 @@ using SymRunFn = nbody_status (*)(const char *, const Device &, const float *, c
                                   int, float, const float *, const float *, float *, float *,
                                   hipStream_t, const LfEpi *, bool *, const Arena &);
 
-using SymKernelFn = void (*)(SymBwdArgs);
-
 // A gather variant (rows own all j) or, with sym set, a pair-once variant
 // with W waves, K rows per lane and chunk divisor O.
 struct Variant {
@@ -933,7 +977,7 @@ struct Variant {
     int block, k, unroll;
     KernelFn direct, partial;
     SymRunFn sym;
-    SymKernelFn sym_kernel;
+    nbody_status (*sym_occupancy)(int *);
     int sym_w, sym_k, sym_occ, sym_rounds;
     bool row;      // row-group kernel, groups of a multiple of row_k rows
     int row_k;
@@ -950,11 +994,11 @@ int sym_block(const Variant &V)
     {"bwd_b" #B "_k" #K "_u" #U, B, K, U, backward_kernel<B, K, U, false>, backward_kernel<B, K, U, true>, nullptr, nullptr, 0, 0, 0, 1}
 #define BWD_SYM_VARIANT(W, K, O) \
     {"bwd_sym_w" #W "_k" #K "_o" #O, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, O>, \
-     backward_sym_kernel<W, K, true>, W, K, O, 1}
+     adj_occupancy<W, K, 1>, W, K, O, 1}
 // Pair-once blocks in R rounds of workgroups (R times the chunks).
 #define BWD_SYM_R_VARIANT(W, K, R) \
     {"bwd_sym_w" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, 1, R>, \
-     backward_sym_kernel<W, K, true>, W, K, 1, R}
+     adj_occupancy<W, K, 1>, W, K, 1, R}
 
 // The same with each block held by half the waves, twice the rows per lane:
 // half the LDS traffic per pair.  GPU time per call with / without potential
@@ -963,13 +1007,13 @@ int sym_block(const Variant &V)
 // 2^18.
 #define BWD_SYM_R_HALF_VARIANT(W, K, R) \
     {"bwd_sym_w" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, \
-     run_backward_sym<W, K, 1, R, 1, W / 2, 2 * K>, backward_sym_kernel<W, K, true>, W, K, 1, R}
+     run_backward_sym<W, K, 1, R, 1, W / 2, 2 * K>, adj_occupancy<W, K, 1>, W, K, 1, R}
 
 // Pair-once blocks of K * 64 rows whose W waves split each tile's steps, in
 // R rounds of workgroups.
 #define BWD_SYM_S_VARIANT(W, K, R) \
     {"bwd_sym_s" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, 1, R, W>, \
-     backward_sym_kernel<W, K, true, W>, W, K, 1, R, false, 0, W}
+     adj_occupancy<W, K, W>, W, K, 1, R, false, 0, W}
 
 #define BWD_ROW_VARIANT(K) \
     {"bwd_row_k" #K, 64, K, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 1, true, K}
@@ -1116,9 +1160,9 @@ int64_t backward_variant_max_n(int variant)
 nbody_status backward_variant_occupancy(int variant, int *per_cu)
 {
     const Variant &V = kVariants[variant];
+    if (V.sym) return V.sym_occupancy(per_cu);
     const hipError_t e =
-        V.sym   ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.sym_kernel, V.sym_w * 64, 0)
-        : V.row ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, backward_row_kernel<kBwdRowMax, true>, 256, 0)
+        V.row ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, backward_row_kernel<kBwdRowMax, true>, 256, 0)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, V.partial, V.block, 0);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (*per_cu < 1) *per_cu = 1;
