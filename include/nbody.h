@@ -94,15 +94,15 @@ const char *nbody_last_error(void);
  * Arithmetic: float32 with fused multiply-add, hardware reciprocal square
  * root, and partial sums folded per j-tile (two-level accumulation).
  * The result is bitwise reproducible for a fixed n, variant and device.
- * Kernels: for 12,000 <= n <= 2^24 the default variant evaluates each
+ * Kernels: for 10,500 <= n <= 2^24 the default variant evaluates each
  * unordered pair once and gives the term to both particles (the softened
  * force is antisymmetric in the pair), in blocks of P = 2048 particles from
- * 2^20 up, 1024 from 40,000, 256 from 18,000 and 128 below.  Each block meets
+ * 2^20 up, 1024 from 50,000 and 256 below.  Each block meets
  * the blocks after it on a ring; the ring offsets run in groups, one launch
  * per group, each followed by a launch that adds the group's partial sums
  * to a float64 running sum per particle, so the library workspace stays at
  * most 1 GiB up to n = 2^22 (256 n bytes above; 0.97 GiB at n = 2^20).
- * Outside that range the default evaluates every ordered pair: below 12,000
+ * Outside that range the default evaluates every ordered pair: below 10,500
  * in one launch of row groups (a workgroup of four waves owns 1 to 8 rows,
  * its lanes splitting j, their sums added in a fixed order in registers and
  * LDS; no partial sums.  From 4,500 bodies that is the small-n form of the
@@ -189,15 +189,14 @@ nbody_status nbody_forces_ex(const float *x, const float *m, int64_t n, float ep
  * error rules as nbody_forces; NULL grad_x with n > 0 -> INVALID_ARGUMENT.
  * Kernels: for 6,200 <= n <= 2^24 the default variant evaluates each
  * unordered pair once (the x-gradient term is antisymmetric in the pair),
- * for blocks of P = 1024 particles from 2^18, 512 from 40,000 and 128
- * below (up to 11,999 two waves share a block's rows and split
- * each tile's steps), with the ring groups and bounded workspace of the
+ * for blocks of P = 1024 particles from 2^18, 512 from 40,000, 256 from
+ * 10,500 and 128 below, with the ring groups and bounded workspace of the
  * pair-once forward (at most 1 GiB up to n = 2^22).  With grad_p NULL it
  * does not form the potential-weight terms (with the same variant, bitwise
  * the result of zero weights); the default variant is the same.  Below 6,200 one
  * launch of row groups (as the forward's, 1 to 4 rows each) evaluates every
- * ordered pair (from 4,000 as the small-n form of the step-split variants,
- * with the workspace of their plan); above 2^24 every ordered pair is gathered
+ * ordered pair (from 4,000 as the small-n form of a pair-once
+ * variant, with the workspace of its plan); above 2^24 every ordered pair is gathered
  * per row.
  */
 nbody_status nbody_forces_backward(const float *x, const float *m, int64_t n, float eps2,

@@ -566,19 +566,19 @@ __device__ __forceinline__ void load_xw(const SymBwdArgs &A, int j, float4 &xm, 
     }
 }
 
-// Steps s0 .. s0 + NS - 1 of diagonal tile t for one wave (lane l meets tile
-// particle (l + s) mod 64 at step s): row tile a = a0 + k pair-once if a < t,
+// The steps of diagonal tile t for one wave (lane l meets tile particle
+// (l + s) mod 64 at step s): row tile a = a0 + k pair-once if a < t,
 // masked ordered pairs if a == t, nothing if a > t (met on diagonal tile a).
-template <int K, int NS = 64>
+template <int K>
 __device__ __forceinline__ void adj_diag_steps(const AdjRow (&row)[K], const int (&kk)[K],
                                                const float4 *tile_xm, const float4 *tile_wv,
                                                float4 *slot, int lane, int a0, int t, int jbase,
-                                               int s0, float eps2, float4 (&tk)[K])
+                                               float eps2, float4 (&tk)[K])
 {
     const bool any_once = a0 < t;
-    float4 q = tile_xm[(lane + s0) & 63];
-    float4 wq = tile_wv[(lane + s0) & 63];
-    for (int s = s0; s < s0 + NS; ++s) {
+    float4 q = tile_xm[lane];
+    float4 wq = tile_wv[lane];
+    for (int s = 0; s < 64; ++s) {
         const int jj = (lane + s) & 63;
         // keep this step's slot read after the previous step's write
         __asm__ volatile("" ::: "memory");
@@ -611,21 +611,19 @@ __device__ __forceinline__ void adj_diag_steps(const AdjRow (&row)[K], const int
 // reads entry l + s and updates slot l + s with no index wrap (immediate
 // LDS offsets in the unrolled loop); particle e's j-side sum is slot e plus
 // slot e + 64, folded into slot e at the end.  Same scheme and ordering
-// argument as the forward pair-once kernel.  The wave takes steps
-// s0 .. s0 + NS - 1 (all 64 unless a tile's steps are split between waves;
-// s0 + NS <= 64 keeps every entry and slot below 128).
-template <int K, bool HAS_V = true, int NS = 64>
+// argument as the forward pair-once kernel.
+template <int K, bool HAS_V = true>
 __device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const float4 *tile_xm,
                                                const float4 *tile_wv, float4 *slot, int lane,
-                                               int s0, float eps2, float4 (&tk)[K])
+                                               float eps2, float4 (&tk)[K])
 {
-    const float4 *txm = tile_xm + lane + s0;
-    const float4 *twv = tile_wv + lane + s0;
-    float4 *sl = slot + lane + s0;
+    const float4 *txm = tile_xm + lane;
+    const float4 *twv = tile_wv + lane;
+    float4 *sl = slot + lane;
     float4 q = txm[0];
     float4 wq = twv[0];
 #pragma unroll 4
-    for (int s = 0; s < NS; ++s) {
+    for (int s = 0; s < 64; ++s) {
         // keep this step's slot read after the previous step's write
         __asm__ volatile("" ::: "memory");
         float4 ja = sl[s];
@@ -644,24 +642,18 @@ __device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const flo
 
 // HAS_V false: no potential weights (grad_p NULL); their terms are not
 // formed on ring tiles (bitwise the same result as v = 0).
-// S = 1: each wave owns K * 64 of the block's rows.  S = W > 1: the W waves
-// share the block's K * 64 rows and each takes 64 / W of every tile's steps
-// (workgroups W times shorter for the same block size, so the grid's drain
-// is shorter); their row sums are added in wave order at the end.
-// Buffers, barriers, slot sums and the tile split of one-wave blocks (T waves)
+// Each wave owns K * 64 of the block's rows.  Buffers, barriers, slot sums and the tile split of one-wave blocks (T waves)
 // as in pair_once_block.
 template <int W>
 constexpr int kAdjSplit = W == 1 ? kTileSplit : 1;
 template <int W>
 constexpr int kAdjThreads = 64 * W * kAdjSplit<W>;
 
-template <int W, int K, bool HAS_V, int S = 1>
-__global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs A)
+template <int W, int K, bool HAS_V>
+__global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void backward_sym_kernel(SymBwdArgs A)
 {
-    static_assert(S == 1 || (S == W && K <= 2), "a step split spans all waves, two rows at most");
-    constexpr int PB = (S > 1 ? 64 : W * 64) * K;
+    constexpr int PB = W * 64 * K;
     constexpr int TPB = PB / 64;
-    constexpr int NS = 64 / S;
     constexpr int NB = kSymBuffers<W>;
     constexpr int T = kAdjSplit<W>;
     static_assert(K * 64 <= kTileLds + kTileLds + kSlotLds, "row sums fit a wave's region");
@@ -688,15 +680,13 @@ __global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs
     const int I = blockIdx.x - c * M;
     float eps2 = A.eps2;
     in_vgpr(eps2);
-    const int wrow = S > 1 ? 0 : wv;      // this wave's row group
-    const int s0 = S > 1 ? wv * NS : 0;   // and first step of each tile
 
     AdjRow row[K];
     float4 acc[K];
     int kk[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int i = I * PB + wrow * 64 * K + k * 64 + lane;
+        const int i = I * PB + wv * 64 * K + k * 64 + lane;
         kk[k] = i;
         float4 xm = make_float4(kBwdPadRow, kBwdPadRow, kBwdPadRow, 0.f);
         float4 wv4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -762,10 +752,9 @@ __global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs
         const float4 *txm = tile_xm + b * kTileLds, *twv = tile_wv + b * kTileLds;
         const bool diag = (cur_delta == 0);
         if (!diag)
-            adj_ring_steps<K, HAS_V, NS>(row, txm, twv, slot, lane, s0, eps2, tk);
+            adj_ring_steps<K, HAS_V>(row, txm, twv, slot, lane, eps2, tk);
         else
-            adj_diag_steps<K, NS>(row, kk, txm, twv, slot, lane, wrow * K, cur_u, cur_base, s0, eps2,
-                                  tk);
+            adj_diag_steps<K>(row, kk, txm, twv, slot, lane, wv * K, cur_u, cur_base, eps2, tk);
         __asm__ volatile("" ::: "memory");
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -793,10 +782,9 @@ __global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs
                     if (cur_base + (f >> 2) < n) reinterpret_cast<float *>(out)[f] = -sum;
                 }
             }
-        } else if (wv == (S > 1 ? 0 : cur_u / K)) {
-            // this wave holds diagonal tile cur_u's rows (lane-slot cur_u % K;
-            // with a step split every wave does, and wave 0 adds); the
-            // diagonal steps use slots 0..63 only
+        } else if (wv == cur_u / K) {
+            // this wave holds diagonal tile cur_u's rows (lane-slot cur_u % K);
+            // the diagonal steps use slots 0..63 only
             float4 sum = jacc[b * W][lane];
 #pragma unroll
             for (int w2 = 1; w2 < W; ++w2) {
@@ -806,7 +794,7 @@ __global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs
                 sum.z += v.z;
                 sum.w += v.w;
             }
-            const int kt = cur_u - wrow * K;
+            const int kt = cur_u - wv * K;
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 if (k == kt) {
@@ -817,27 +805,6 @@ __global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs
                 }
         }
         if (NB == 2) b ^= 1;
-    }
-    if (S > 1) {
-        // the waves' row sums, added in wave order by wave 0 (through the
-        // j-side slots, which the last tile's reads are done with)
-        __syncthreads();
-        if (wv > 0) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) jacc[wv][k * 64 + lane] = acc[k];
-        }
-        __syncthreads();
-        if (wv > 0) return;
-#pragma unroll
-        for (int w2 = 1; w2 < W; ++w2)
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const float4 v = jacc[w2][k * 64 + lane];
-                acc[k].x += v.x;
-                acc[k].y += v.y;
-                acc[k].z += v.z;
-                acc[k].w += v.w;
-            }
     }
     if constexpr (T == 1) {
 #pragma unroll
@@ -861,15 +828,23 @@ __global__ __launch_bounds__(kAdjThreads<W>) void backward_sym_kernel(SymBwdArgs
 }
 
 // Workgroups of W waves per CU (counting each wave of a tile split as one).
-template <int W, int K, int S>
+template <int W, int K>
 nbody_status adj_occupancy(int *per_cu)
 {
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        per_cu, backward_sym_kernel<W, K, true, S>, kAdjThreads<W>, 0);
+        per_cu, backward_sym_kernel<W, K, true>, kAdjThreads<W>, 0);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (*per_cu < 1) *per_cu = 1;
     *per_cu *= kAdjSplit<W>;
     return NBODY_OK;
+}
+
+// The two-row one-wave kernel counted in workgroups of two waves.
+nbody_status adj_occupancy_half(int *per_cu)
+{
+    const nbody_status st = adj_occupancy<1, 2>(per_cu);
+    if (st == NBODY_OK) *per_cu = (*per_cu + 1) / 2;
+    return st;
 }
 
 // Sizes at which the two-wave step-split pair-once variants run the row-group
@@ -900,53 +875,32 @@ nbody_status backward_rows_run(int least, const char *name, const Device &dev, c
     return check_launch(name);
 }
 
-// OCC divides the chunk count and ROUNDS multiplies it (as in the
-// pair-once forward kernel); S splits each tile's steps between the waves.
-// The kernel may hold a block of W waves x K rows as KW waves x KK rows (the
-// same particles and plan).
-template <int W, int K, int OCC, int ROUNDS = 1, int S = 1, int KW = W, int KK = K>
-nbody_status run_backward_sym(const char *name, const Device &dev, const float *x, const float *m,
-                              int n, float eps2, const float *ga, const float *gp, float *gx,
-                              float *gm, hipStream_t stream, const LfEpi *epi, bool *fused,
-                              const Arena &arena)
+// The launches of a plan whose blocks are KW waves x KK rows.
+template <int W, int K>
+nbody_status launch_backward_sym(const SymPlan &pl, void *ws, const char *name, const float *x,
+                                 const float *m, int n, float eps2, const float *ga,
+                                 const float *gp, float *gx, float *gm, hipStream_t stream,
+                                 const LfEpi *epi, bool *fused)
 {
-    static_assert(KW * KK == W * K && (S == 1 || KW == W), "the same block");
-    constexpr int PB = (S > 1 ? 64 : W * 64) * K;
-    int per_cu = 0;
-    nbody_status st = adj_occupancy<W, K, S>(&per_cu);
-    if (st != NBODY_OK) return st;
-    SymPlan pl;
-    if (!sym_plan(n, PB, (int64_t)per_cu * dev.num_cu * ROUNDS, OCC,
-                  arena.budget(sym_workspace_budget(n)), &pl))
-        return fail(NBODY_ERROR_INVALID_ARGUMENT,
-                    "n = %d needs more than the %zu-byte workspace limit of %s", n,
-                    arena.budget(sym_workspace_budget(n)), name);
-    void *ws = nullptr;
-    st = arena.get(dev, stream, pl.bytes(), &ws);
-    if (st != NBODY_OK) return st;
-    if constexpr (S == 2 && K == 2)
-        // the plan and its workspace stay the variant's, whichever kernel runs
-        if (bwd_row_band(n))
-            return backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi, fused);
+    constexpr int PB = W * 64 * K;
     float4 *partial = static_cast<float4 *>(ws);
     double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
                                 : nullptr;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
-    // a tile split needs a partial per workgroup, fewer than the plan allows
-    const int C = (pl.C + kAdjSplit<KW> - 1) / kAdjSplit<KW>;
+    const int C = pl.C;
     for (int g = 0; g < pl.groups; ++g) {
         SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, C, 0, 0, partial};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (gp)
-            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, true, S>), dim3(pl.M * C),
-                               dim3(kAdjThreads<KW>), 0, stream, A);
+            hipLaunchKernelGGL((backward_sym_kernel<W, K, true>), dim3(pl.M * C),
+                               dim3(kAdjThreads<W>), 0, stream, A);
         else
-            hipLaunchKernelGGL((backward_sym_kernel<KW, KK, false, S>), dim3(pl.M * C),
-                               dim3(kAdjThreads<KW>), 0, stream, A);
+            hipLaunchKernelGGL((backward_sym_kernel<W, K, false>), dim3(pl.M * C),
+                               dim3(kAdjThreads<W>), 0, stream, A);
         prof_mark(stream, 1);
-        st = check_launch(name);
+        nbody_status st = check_launch(name);
         if (st != NBODY_OK) return st;
         const int first = g == 0, last = g == pl.groups - 1;
         if (last && lf)
@@ -962,6 +916,57 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     }
     if (lf && fused) *fused = true;
     return NBODY_OK;
+}
+
+// OCC divides the chunk count and ROUNDS multiplies it (as in the
+// pair-once forward kernel).  The kernel may hold a block of W waves x K rows
+// as KW waves x KK rows (the same particles and plan); SMALL variants (one
+// wave, two rows) run the row-group kernel in its band.
+//
+// One-wave two-row variants take a tile per wave up to kOneTileEnd, four rows
+// per lane (half the LDS traffic per pair, half the slots to fold) from
+// kOneTileBegin.  Calls with potential weights, chunks of one or two tiles as
+// planned (below 12,000: two waves to a tile) / two rows, a tile per wave / four
+// rows, a tile per wave: 40.2 / 36.1 / 43.7 us at 8,000 bodies, 58.4 / 56.8 /
+// 59.3 at 10,000, 66.4 / 63.7 / 60.9 at 11,000, 126 / 126 / 124 at 16,384, 182 /
+// 182 / 175 at 20,000, 404 / 394 / 371 at 30,000, 660 / 655 / 618 at 39,000,
+// and 1396 / 1399 / 1397 at 60,000.
+template <int W, int K, int OCC, int ROUNDS = 1, int KW = W, int KK = K, bool SMALL = false>
+nbody_status run_backward_sym(const char *name, const Device &dev, const float *x, const float *m,
+                              int n, float eps2, const float *ga, const float *gp, float *gx,
+                              float *gm, hipStream_t stream, const LfEpi *epi, bool *fused,
+                              const Arena &arena)
+{
+    static_assert(KW * KK == W * K, "the same block");
+    constexpr int PB = W * 64 * K;
+    int per_cu = 0;
+    nbody_status st = SMALL ? adj_occupancy_half(&per_cu) : adj_occupancy<W, K>(&per_cu);
+    if (st != NBODY_OK) return st;
+    SymPlan pl;
+    if (!sym_plan(n, PB, (int64_t)per_cu * dev.num_cu * ROUNDS, OCC,
+                  arena.budget(sym_workspace_budget(n)), &pl))
+        return fail(NBODY_ERROR_INVALID_ARGUMENT,
+                    "n = %d needs more than the %zu-byte workspace limit of %s", n,
+                    arena.budget(sym_workspace_budget(n)), name);
+    void *ws = nullptr;
+    st = arena.get(dev, stream, pl.bytes(), &ws);
+    if (st != NBODY_OK) return st;
+    if constexpr (SMALL)
+        // the plan and its workspace stay the variant's, whichever kernel runs
+        if (bwd_row_band(n))
+            return backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi, fused);
+    if constexpr (KW == 1 && KK == 2) {
+        SymPlan one;
+        if (n >= kOneTileBegin && n < kOneTileEnd && one_tile_plan(n, 4, pl, &one))
+            return launch_backward_sym<1, 4>(one, ws, name, x, m, n, eps2, ga, gp, gx, gm, stream,
+                                             epi, fused);
+        if (n < kOneTileBegin && one_tile_plan(n, 2, pl, &one))
+            return launch_backward_sym<1, 2>(one, ws, name, x, m, n, eps2, ga, gp, gx, gm, stream,
+                                             epi, fused);
+    }
+    if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
+    return launch_backward_sym<KW, KK>(pl, ws, name, x, m, n, eps2, ga, gp, gx, gm, stream, epi,
+                                       fused);
 }
 
 using KernelFn = void (*)(BwdArgs);
@@ -981,24 +986,24 @@ struct Variant {
     int sym_w, sym_k, sym_occ, sym_rounds;
     bool row;      // row-group kernel, groups of a multiple of row_k rows
     int row_k;
-    int sym_split;  // pair-once: waves sharing a block's rows (0 or 1: none)
+    bool sym_small;  // row groups in bwd_row_band
 };
 
 // Particles per pair-once block of a variant.
 int sym_block(const Variant &V)
 {
-    return V.sym_w * 64 * V.sym_k / (V.sym_split > 1 ? V.sym_split : 1);
+    return V.sym_w * 64 * V.sym_k;
 }
 
 #define BWD_VARIANT(B, K, U) \
     {"bwd_b" #B "_k" #K "_u" #U, B, K, U, backward_kernel<B, K, U, false>, backward_kernel<B, K, U, true>, nullptr, nullptr, 0, 0, 0, 1}
 #define BWD_SYM_VARIANT(W, K, O) \
     {"bwd_sym_w" #W "_k" #K "_o" #O, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, O>, \
-     adj_occupancy<W, K, 1>, W, K, O, 1}
+     adj_occupancy<W, K>, W, K, O, 1}
 // Pair-once blocks in R rounds of workgroups (R times the chunks).
 #define BWD_SYM_R_VARIANT(W, K, R) \
     {"bwd_sym_w" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, 1, R>, \
-     adj_occupancy<W, K, 1>, W, K, 1, R}
+     adj_occupancy<W, K>, W, K, 1, R}
 
 // The same with each block held by half the waves, twice the rows per lane:
 // half the LDS traffic per pair.  GPU time per call with / without potential
@@ -1007,13 +1012,13 @@ int sym_block(const Variant &V)
 // 2^18.
 #define BWD_SYM_R_HALF_VARIANT(W, K, R) \
     {"bwd_sym_w" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, \
-     run_backward_sym<W, K, 1, R, 1, W / 2, 2 * K>, adj_occupancy<W, K, 1>, W, K, 1, R}
+     run_backward_sym<W, K, 1, R, W / 2, 2 * K>, adj_occupancy<W, K>, W, K, 1, R}
 
-// Pair-once blocks of K * 64 rows whose W waves split each tile's steps, in
-// R rounds of workgroups.
-#define BWD_SYM_S_VARIANT(W, K, R) \
-    {"bwd_sym_s" #W "_k" #K "_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<W, K, 1, R, W>, \
-     adj_occupancy<W, K, W>, W, K, 1, R, false, 0, W}
+// Blocks of 128 rows in plans for workgroups of two waves (half as many chunks
+// as the one-wave variants'), R rounds; the row-group kernel in its band.
+#define BWD_SYM_S_VARIANT(R) \
+    {"bwd_sym_s2_k2_r" #R, 0, 0, 0, nullptr, nullptr, run_backward_sym<1, 2, 1, R, 1, 2, true>, \
+     adj_occupancy_half, 1, 2, 1, R, false, 0, true}
 
 #define BWD_ROW_VARIANT(K) \
     {"bwd_row_k" #K, 64, K, 0, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 1, true, K}
@@ -1044,8 +1049,8 @@ const Variant kVariants[] = {
     BWD_SYM_R_HALF_VARIANT(4, 2, 8),
     BWD_ROW_VARIANT(1),
     BWD_ROW_VARIANT(2),
-    BWD_SYM_S_VARIANT(2, 2, 8),
-    BWD_SYM_S_VARIANT(2, 2, 16),
+    BWD_SYM_S_VARIANT(8),
+    BWD_SYM_S_VARIANT(16),
     BWD_SYM_R_VARIANT(1, 2, 16),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
@@ -1076,42 +1081,34 @@ int backward_default_variant(int64_t n)
     static const int pair_once_large = variant_index("bwd_sym_w4_k2_r8");
     static const int pair_once_r8 = variant_index("bwd_sym_w1_k2_r8");
     static const int pair_once_r16 = variant_index("bwd_sym_w1_k2_r16");
-    static const int pair_once_split = variant_index("bwd_sym_s2_k2_r8");
+    static const int pair_once_small = variant_index("bwd_sym_s2_k2_r8");
     static const int gather = variant_index("bwd_b256_k1_u8");
     static const int row_1 = variant_index("bwd_row_k1");
     static const int row_2 = variant_index("bwd_row_k2");
     if (n > (1 << 24)) return gather;
-    // Eight rounds of workgroups (each block's tiles cut into eight times as
-    // many chunks as the device holds workgroups, down to one tile; the
-    // dispatcher hands the short ones out as slots free up) lead from 4,000
-    // bodies up in forced-variant sweeps on one box (whole calls, with and
-    // without potential weights): blocks of 128 rows whose two waves split
-    // each tile's steps up to 12,000 (4-6% ahead of the two-row row kernel
-    // at 4,000, level with it at 3,500; 5-10% ahead of one round of two-wave
-    // one-row blocks from 4,500 to 5,600; 2-7% ahead of one-wave two-row and
-    // two-wave one-row blocks in eight rounds from 7,000 to 10,000, level at
-    // 6,000 and 12,000), then one-wave two-row blocks (4-9% ahead of one round up to
-    // 2^17), in sixteen rounds from 24,000 to 29,999 (one tile per chunk
-    // where eight rounds mix chunks of one and two tiles: 4% ahead at
-    // 24,576, 1% at 28,000, behind at 22,000 and 32,768), 4-wave blocks
-    // from 40,000 (10-13% ahead of one round of two-wave blocks with
+    // Row groups below 6,200 bodies, then one-wave blocks with a tile per wave
+    // up to 40,000: the three variants of that range differ in the plan whose
+    // workspace they keep, not in the kernel (run_backward_sym).  Then 4-wave
+    // blocks in eight rounds of workgroups (the dispatcher hands short chunks
+    // out as slots free up: 10-13% ahead of one round of two-wave blocks with
     // potential weights at 49,152 and 60,000, 9-11% of 8-wave ones at 2^17)
     // and 8-wave blocks from 2^18 (3-7% ahead of one round of them at 2^18
-    // and 2^19).
+    // and 2^19).  A tile per wave against the 4-wave blocks: 809 / 809 us at
+    // 45,000, 987 / 989 at 50,021.
     if (n >= (1 << 18)) return pair_once_big;
     if (n >= 40000) return pair_once_large;
     if (n >= 24000 && n < 30000) return pair_once_r16;
     if (n >= 12000) return pair_once_r8;
-    if (n >= 4000) return pair_once_split;
+    if (n >= 4000) return pair_once_small;
     // row groups below 4,000 bodies (an even number of rows from 3,500), which
-    // also serve the step-split variant below kBwdRowBandEnd
+    // also serve the variant above below kBwdRowBandEnd
     return n >= 3500 ? row_2 : row_1;
 }
 
 bool backward_takes_rows(int variant, int n)
 {
     const Variant &V = kVariants[variant];
-    return V.row || (V.sym_split == 2 && V.sym_k == 2 && bwd_row_band(n));
+    return V.row || (V.sym_small && bwd_row_band(n));
 }
 
 // Geometry of the row gather: j-splits and j per split.

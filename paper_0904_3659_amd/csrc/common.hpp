@@ -118,12 +118,11 @@ bool backward_takes_rows(int variant, int n);
 
 // Sizes at which the one-wave two-row pair-once variants run the row-group
 // kernel instead: the pair-once grid is then one underfilled round of
-// workgroups and a fold of 4-5 us follows it.  Whole calls with the
-// potential, pair-once against row groups: 16.5 / 9.2 us at 4,500 bodies,
-// 20.7 / 13.7 at 6,001, 25.7 / 19.9 at 7,500, 38.4 / 32.5 at 10,000, 46.5 /
-// 44.5 at 12,000, 57.7 / 59.1 at 14,000.  Below 4,500 the default variants
-// are row groups by themselves.
-constexpr int kRowBandBegin = 4500, kRowBandEnd = 12000;
+// workgroups and a fold of 4-5 us follows it.  Calls with the potential, pair-
+// once (a tile per wave) against row groups: 22.9 / 21.5 us at 8,000 bodies,
+// 26.9 / 26.7 at 9,000, 34.3 / 32.3 at 10,000, 35.3 / 39.1 at 11,000.  Below 4,500
+// the default variants are row groups by themselves.
+constexpr int kRowBandBegin = 4500, kRowBandEnd = 10500;
 inline bool row_band(int n) { return n >= kRowBandBegin && n < kRowBandEnd; }
 
 // Rows per group K (a multiple of `least`, at most `most`) for n rows on

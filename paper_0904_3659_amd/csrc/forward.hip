@@ -603,18 +603,11 @@ int forward_default_variant(int64_t n)
     // 60,000, 3-5% behind at 36,000; forced-variant sweep, same box).
     if (n >= (1 << 20)) return pair_once_8;
     if (n >= 40000) return pair_once_4;
-    // four-row one-wave blocks lead from about 18,000 (2% at 18,000 and
-    // 22,000, 3% at 24,000; 1-2% behind at 16,384)
+    // one-wave blocks below, a tile per wave from kRowBandEnd: the variants
+    // differ in the plan whose workspace they keep, not in the kernel
+    // (forward_sym_run)
     if (n >= 18000) return pair_once_1;
-    // eight rounds of one-wave blocks of 128 particles from 10,000: below
-    // that one round already cuts every block's sequence into one-tile
-    // chunks (the same plan, the same time), above it one round leaves
-    // chunks of one and two tiles and takes 11% longer (11,000 and 12,000
-    // bodies, forced-variant sweep, same box)
     if (n >= 10000) return pair_once_1s;
-    // one-wave blocks of 128 particles: twice the workgroups of 256-particle
-    // blocks, which evens out the one round of workgroups these sizes fill
-    // (3-17% faster from 3,000 to 10,000 bodies)
     // Small n: the row-group kernel (an even number of rows per group from
     // 3,000 bodies), which also serves the two-row one-wave variants below
     // kRowBandEnd; their names keep the pair-once geometry they have above it.

@@ -54,6 +54,48 @@ nbody_status sym_occupancy(int *per_cu)
     return NBODY_OK;
 }
 
+// The launches of a plan whose blocks are W waves x K rows per lane.
+template <int W, int K>
+nbody_status launch_sym(const SymPlan &pl, void *ws, const char *name, const float *x,
+                        const float *m, int n, float eps2, float *a, float *p, hipStream_t stream,
+                        const LfEpi *epi, bool *fused)
+{
+    constexpr int PB = W * 64 * K;
+    float4 *partial = static_cast<float4 *>(ws);
+    double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
+                                : nullptr;
+    if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
+    const bool lf = epi && epi->mode != kLfNone;
+    const int C = pl.C;
+    for (int g = 0; g < pl.groups; ++g) {
+        SymArgs A{x, m, n, eps2, pl.M, C, 0, 0, partial};
+        sym_group(pl, g, &A.d_lo, &A.d_hi);
+        prof_mark(stream, 0);
+        if (p)
+            hipLaunchKernelGGL((forward_sym_kernel<W, K, true>), dim3(pl.M * C),
+                               dim3(kSymThreads<W>), 0, stream, A);
+        else
+            hipLaunchKernelGGL((forward_sym_kernel<W, K, false>), dim3(pl.M * C),
+                               dim3(kSymThreads<W>), 0, stream, A);
+        prof_mark(stream, 1);
+        nbody_status st = check_launch(name);
+        if (st != NBODY_OK) return st;
+        const int first = g == 0, last = g == pl.groups - 1;
+        if (last && lf)
+            hipLaunchKernelGGL((slot_fold_kernel<PB, true>), dim3((n + 63) / 64), dim3(256), 0,
+                               stream, partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, a,
+                               p, *epi);
+        else
+            hipLaunchKernelGGL((slot_fold_kernel<PB>), dim3((n + 63) / 64), dim3(256), 0, stream,
+                               partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, a, p,
+                               LfEpi{});
+        st = check_launch("slot_fold");
+        if (st != NBODY_OK) return st;
+    }
+    if (lf && fused) *fused = true;
+    return NBODY_OK;
+}
+
 // OCC divides the chunk count: 1 fills every resident workgroup slot once;
 // 2 gives half as many, twice as long workgroups (fewer partial slots, less
 // tail imbalance at small n, lower occupancy).  ROUNDS multiplies it: that
@@ -87,40 +129,20 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
         // the plan and its workspace stay the variant's, whichever kernel runs
         if (row_band(n))
             return forward_rows_run(1, name, dev, x, m, n, eps2, a, p, stream, epi, fused);
-    float4 *partial = static_cast<float4 *>(ws);
-    double4 *acc = pl.acc_bytes ? reinterpret_cast<double4 *>(static_cast<char *>(ws) + pl.partial_bytes)
-                                : nullptr;
-    if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
-    const bool lf = epi && epi->mode != kLfNone;
-    // a tile split needs a partial per workgroup, fewer than the plan allows
-    const int C = (pl.C + kSymSplit<KW> - 1) / kSymSplit<KW>;
-    for (int g = 0; g < pl.groups; ++g) {
-        SymArgs A{x, m, n, eps2, pl.M, C, 0, 0, partial};
-        sym_group(pl, g, &A.d_lo, &A.d_hi);
-        prof_mark(stream, 0);
-        if (p)
-            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, true>), dim3(pl.M * C),
-                               dim3(kSymThreads<KW>), 0, stream, A);
-        else
-            hipLaunchKernelGGL((forward_sym_kernel<KW, KK, false>), dim3(pl.M * C),
-                               dim3(kSymThreads<KW>), 0, stream, A);
-        prof_mark(stream, 1);
-        st = check_launch(name);
-        if (st != NBODY_OK) return st;
-        const int first = g == 0, last = g == pl.groups - 1;
-        if (last && lf)
-            hipLaunchKernelGGL((slot_fold_kernel<PB, true>), dim3((n + 63) / 64), dim3(256), 0,
-                               stream, partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, a,
-                               p, *epi);
-        else
-            hipLaunchKernelGGL((slot_fold_kernel<PB>), dim3((n + 63) / 64), dim3(256), 0, stream,
-                               partial, n, pl.M, C, A.d_lo, A.d_hi, first, last, acc, a, p,
-                               LfEpi{});
-        st = check_launch("slot_fold");
-        if (st != NBODY_OK) return st;
+    // A tile per one-wave block of 256 particles.  Calls with the potential, row
+    // groups (below 12,000) or planned chunks of 2-4 tiles / a tile per wave:
+    // 32.3 / 34.3 us at 10,000 bodies, 39.1 / 35.3 at 11,000, 50.7 / 47.9 at
+    // 13,000, 71.5 / 69.2 at 16,384, the same from 18,000 to 30,000 (there the
+    // plan has a tile per wave), 246 / 233 at 33,000, 341 / 325 at 39,000, four
+    // waves' blocks of 1,024 / a tile per wave: 373 / 354 at 40,000, 443 / 439 at
+    // 45,000, 500 / 497 at 48,000.
+    if constexpr (W == 1 || (W == 4 && K == 4 && KW == 4)) {
+        SymPlan one;
+        if (n >= kOneTileBegin && n < kOneTileEnd && one_tile_plan(n, 4, pl, &one))
+            return launch_sym<1, 4>(one, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
     }
-    if (lf && fused) *fused = true;
-    return NBODY_OK;
+    if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
+    return launch_sym<KW, KK>(pl, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
 }
 
 }  // namespace

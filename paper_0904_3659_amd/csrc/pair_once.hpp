@@ -228,6 +228,31 @@ __device__ __forceinline__ int chunk_begin(int U, int C, int c)
     return c + (int)((float)(U - C) * (4.0f / 3.0f) * (x - t * t));
 }
 
+// Waves that share a one-wave block's chunk: the chunk partials of one-wave
+// blocks were two thirds of what the fold reads (1 tile, 1 partial).  Forward
+// calls with four waves to a partial against one: 86.7 -> 81.5 us at 18,000
+// bodies, 144.9 -> 137.2 at 24,000, 218.7 -> 209.2 at 30,000.
+constexpr int kTileSplit = 4;
+
+// One-group plans of one-wave blocks of 64 K particles with at most one tile
+// per wave (kTileSplit waves a workgroup), laid out in the workspace of a
+// variant's own plan `pl`: false if it does not fit there.  C counts
+// workgroups.  Sizes that take it, and what it replaces there: see
+// forward_sym_run and run_backward_sym.
+inline bool one_tile_plan(int64_t n, int K, const SymPlan &pl, SymPlan *out)
+{
+    SymPlan t = pl;
+    t.M = (int)((n + 64 * K - 1) / (64 * K));
+    t.G = t.M / 2;
+    t.C = ((t.G + 1) * K + kTileSplit - 1) / kTileSplit;
+    if (pl.groups != 1 || t.C + t.G > pl.C + pl.G) return false;
+    *out = t;
+    return true;
+}
+// Below kOneTileBegin (and kOneTileEnd on) the blocks of 256 particles these
+// plans have are too few (too many): see the same places.
+constexpr int kOneTileBegin = 10500, kOneTileEnd = 50000;
+
 // Library workspace allowed for one pair-once evaluation of n particles
 // (partials and running sum) before the ring is split into more groups:
 // 1 GiB, or 16 float4 slots per particle where that is more (n > 2^22).
@@ -514,11 +539,6 @@ __device__ __forceinline__ void diag_tile_steps(const float (&xi)[K], const floa
 // LDS entries of one wave of a tile-split workgroup: the tile and the slots,
 // and at the end K <= 4 rows of row sums.
 constexpr int kWaveLds = kTileLds + kSlotLds;
-// Waves that share a one-wave block's chunk.  The chunk partials of one-wave
-// blocks were two thirds of what the fold reads: 1 tile, 1 partial.  With four
-// waves to a partial the fold takes 4.9 us instead of 9.1 at 16,384 bodies, 9
-// instead of 21 at 30,000.
-constexpr int kTileSplit = 4;
 
 // LDS buffers of a pair-once workgroup: blocks of several waves keep two tiles
 // and two sets of slots, so that one barrier per tile suffices; a one-wave

@@ -1,7 +1,9 @@
 """The row-group kernels of small and middle n against the oracle: every
 group size the sizes below choose, groups that straddle a tile, ragged last
 tiles and groups, and the edges of the band in which they stand in for the
-two-row pair-once variants."""
+two-row pair-once variants.  Above it: one-wave pair-once blocks with a tile
+per wave, ragged last blocks, odd and even block counts, the edges of their
+range."""
 
 import numpy as np
 import pytest
@@ -22,7 +24,8 @@ def nb():
 
 
 @pytest.mark.parametrize("n", [1, 2, 5, 8, 63, 64, 65, 127, 255, 257, 513, 1021, 1600, 2501, 3503, 4096,
-                               4499, 4500, 5003, 6209, 7001, 8200, 11999, 12000])
+                               4499, 4500, 5003, 6209, 7001, 8200, 10499, 10500, 11999, 12000, 12545,
+                               18001, 39999, 40000, 49999])
 @pytest.mark.parametrize("eps2", [0.0, 1e-4])
 def test_forward(nb, n, eps2):
     dev = need_gpu()
@@ -41,7 +44,8 @@ def test_forward(nb, n, eps2):
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 129, 255, 1021, 1601, 2501, 3001, 3501, 3999, 4000, 4501, 5003,
-                               6199, 6200])
+                               6199, 6200, 6401, 8193, 10499, 10500, 11777, 12000,
+                               16385, 24001])
 @pytest.mark.parametrize("with_v", [False, True])
 def test_adjoint(nb, n, with_v):
     dev = need_gpu()
