@@ -141,12 +141,21 @@ __global__ __launch_bounds__(W * 64) void batched_sym_kernel(BatSymArgs A)
 // free takes the next), which balances the tail better than a static deal
 // when units of equal estimated cost run at different speeds.  The last
 // workgroup to finish resets the counters for the next launch on the stream.
-template <int W, int K>
-__global__ __launch_bounds__(W * 64) void batched_sym_dyn_kernel(BatSymArgs A, int *ctr)
+//
+// The kTileSplit waves of a workgroup share a unit, each taking every fourth
+// tile: a unit of the largest systems is 16 to 20 tiles, 10 us each for one
+// wave alone on its SIMD.  Calls with one wave per unit (one-wave workgroups) /
+// four / eight: 4,096 systems of 8 to 2,048 bodies (18,468 units) 1288 / 1219 /
+// 1303 us, 1,024 of them (4,529) 448 / 325 / 326, 300 (1,342) 269 / 135 / 115,
+// 62 (191 units) 173 / 55 / 37, 481 of up to 290 bodies (532) 57 / 30 / 30, 3,250
+// of up to 409 (4,402) 170 / 107 / 122.  Four for all: a choice by the number of
+// units would make a system's sums depend on the rest of the batch.
+template <int K>
+__global__ __launch_bounds__(kTileSplit * 64) void batched_sym_dyn_kernel(BatSymArgs A, int *ctr)
 {
-    constexpr int PB = W * 64 * K;
-    __shared__ float4 tile[kSymBuffers<W> * kTileLds];
-    __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
+    constexpr int T = kTileSplit;
+    constexpr int PB = 64 * K;
+    __shared__ float4 lds[T * kWaveLds];  // per wave: the tile, then its slots
     __shared__ int s_idx;
     for (;;) {
         __syncthreads();  // every thread has read the previous ticket
@@ -157,8 +166,9 @@ __global__ __launch_bounds__(W * 64) void batched_sym_dyn_kernel(BatSymArgs A, i
         const int4 u = A.units[idx];
         const int ns = u.y;
         const int M = (ns + PB - 1) / PB;
-        pair_once_block<W, K, true>(A.x + 3 * (size_t)u.x, A.m + u.x, ns, A.eps2, M, u.z, 0, 1,
-                                    0, M / 2 + 1, A.partial + u.w, tile, jacc);
+        pair_once_block<1, K, true, true, T>(A.x + 3 * (size_t)u.x, A.m + u.x, ns, A.eps2, M, u.z,
+                                             0, 1, 0, M / 2 + 1, A.partial + u.w, lds,
+                                             reinterpret_cast<float4(*)[kSlotLds]>(lds + kTileLds));
     }
     if (threadIdx.x == 0) {
         // Every workgroup draws tickets until it fails once and only then
@@ -221,9 +231,9 @@ struct Variant {
 #define BAT_SYM_VARIANT(W, K) \
     {"bat_sym_w" #W "_k" #K, 0, 0, nullptr, W * 64 * K, batched_sym_kernel<W, K>, \
      batched_sym_reduce_kernel<W * 64 * K>, W * 64, nullptr}
-#define BAT_SYMD_VARIANT(W, K) \
-    {"bat_symd_w" #W "_k" #K, 0, 0, nullptr, W * 64 * K, batched_sym_kernel<W, K>, \
-     batched_sym_reduce_kernel<W * 64 * K>, W * 64, batched_sym_dyn_kernel<W, K>}
+#define BAT_SYMD_VARIANT(K) \
+    {"bat_symd_w1_k" #K, 0, 0, nullptr, 64 * K, nullptr, batched_sym_reduce_kernel<64 * K>, \
+     64 * kTileSplit, batched_sym_dyn_kernel<K>}
 
 const Variant kVariants[] = {
     BAT_VARIANT(64, 8),
@@ -235,9 +245,9 @@ const Variant kVariants[] = {
     BAT_SYM_VARIANT(2, 2),
     BAT_SYM_VARIANT(1, 8),
     BAT_SYM_VARIANT(2, 4),
-    BAT_SYMD_VARIANT(1, 3),
-    BAT_SYMD_VARIANT(1, 4),
-    BAT_SYMD_VARIANT(1, 2),
+    BAT_SYMD_VARIANT(3),
+    BAT_SYMD_VARIANT(4),
+    BAT_SYMD_VARIANT(2),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 

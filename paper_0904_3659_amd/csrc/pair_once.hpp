@@ -384,20 +384,21 @@ __device__ __forceinline__ void pair_once_rows(const float (&xi)[K], const float
 // tile entry l + s at step s and adds its j-side terms to slot l + s.
 // `tile` has kTileLds entries (the tile twice), `slot` this wave's
 // kSlotLds slots.
-// PARTIAL: only the first kv row groups of the wave hold particles (the
-// last block of a system); the others are padding with mass 0, whose terms
-// are exactly zero on both sides, so skipping them changes no bit.
-template <int K, bool PARTIAL = false, bool POT = true>
+// R < K: only the wave's first R row groups hold particles (the last block of
+// a system); the others are padding with mass 0, whose terms are exactly zero
+// on both sides, so skipping them changes no bit.
+template <int K, int R = K, bool POT = true>
 __device__ __forceinline__ void ring_tile_steps(const float (&xi)[K], const float (&yi)[K],
                                                 const float (&zi)[K], const float (&mi)[K],
                                                 const float4 *tile, float4 *slot, int lane,
                                                 float eps2, float (&tx)[K], float (&ty)[K],
-                                                float (&tz)[K], float (&tp)[K], int kv = K)
+                                                float (&tz)[K], float (&tp)[K])
 {
     const float4 *tq = tile + lane;
     float4 *sl = slot + lane;
     float4 q = tq[0];
-    constexpr int kUnroll = K > 8 ? 2 : K > 4 ? 4 : 8;  // about 600 to 1,200 operations per trip
+    // about 600 to 1,200 operations per trip; few where the loop is one of K
+    constexpr int kUnroll = R < K ? 2 : K > 8 ? 2 : K > 4 ? 4 : 8;
 #pragma unroll kUnroll
     for (int s = 0; s < 64; ++s) {
         // Compiler-only barrier: this step's slot read stays after the
@@ -405,15 +406,7 @@ __device__ __forceinline__ void ring_tile_steps(const float (&xi)[K], const floa
         __asm__ volatile("" ::: "memory");
         float4 g = sl[s];
         const float4 qn = tq[s + 1];  // next step's particle (read-only tile)
-        if constexpr (PARTIAL) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if (k < kv)
-                    pair_once_fold<POT>(xi[k], yi[k], zi[k], mi[k], q, eps2, tx[k], ty[k], tz[k],
-                                        tp[k], g);
-        } else {
-            pair_once_rows<K, K, POT>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
-        }
+        pair_once_rows<K, R, POT>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
         sl[s] = g;
         q = qn;
     }
@@ -422,6 +415,22 @@ __device__ __forceinline__ void ring_tile_steps(const float (&xi)[K], const floa
     const float4 lo = slot[lane];
     const float4 hi = slot[lane + 64];
     slot[lane] = make_float4(lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w);
+}
+
+// ring_tile_steps of the first kv < K row groups.
+template <int K, int R, bool POT>
+__device__ __forceinline__ void ring_tile_some(int kv, const float (&xi)[K], const float (&yi)[K],
+                                               const float (&zi)[K], const float (&mi)[K],
+                                               const float4 *tile, float4 *slot, int lane,
+                                               float eps2, float (&tx)[K], float (&ty)[K],
+                                               float (&tz)[K], float (&tp)[K])
+{
+    if constexpr (R > 0) {
+        if (kv == R)
+            ring_tile_steps<K, R, POT>(xi, yi, zi, mi, tile, slot, lane, eps2, tx, ty, tz, tp);
+        else
+            ring_tile_some<K, R - 1, POT>(kv, xi, yi, zi, mi, tile, slot, lane, eps2, tx, ty, tz, tp);
+    }
 }
 
 // One step s of a diagonal tile: rows k < R meet entry l + s pair-once.
@@ -562,7 +571,7 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 // wave that holds tile t's rows adds them to its own accumulators.
 // POT false: no potential is stored, and the ring and one-wave diagonal
 // tiles do not form its terms (the partials' w component is then partial).
-// SKIP_PAD: skip the ring-tile work of row groups that hold only padding
+// SKIP_PAD (ensembles): skip the ring-tile work of row groups that hold only padding
 // (bitwise neutral: their terms are exactly zero).  Worth it for ensembles
 // of small systems, where a last block is often part padding (5% of the
 // row-group work on the 4,096-system ensemble); single systems keep the
@@ -578,7 +587,8 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 // one of T consecutive sub-chunks of chunk c each, with an LDS region of
 // kWaveLds entries per wave (its tile, then its slots) from `tile` on; their
 // row sums are added in wave order at the end, so that a chunk writes (and the
-// fold reads) one partial for T waves' tiles.
+// fold reads) one partial for T waves' tiles.  (Ensembles, one chunk per block:
+// every T-th tile each.)
 template <int W, int K, bool SKIP_PAD = false, bool POT = true, int T = 1>
 __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                                                 const float *__restrict__ m, int n, float eps2,
@@ -635,8 +645,11 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     // tiles that hold only padding are skipped (uniform).
     const int U = group_tiles(I, M, d_lo, d_hi, TPB);
     const int dj = group_first_delta(d_lo);
-    const int u0 = chunk_begin(U, C * T, c * T + tw);
-    const int u1 = chunk_begin(U, C * T, c * T + tw + 1);
+    // (a small system's one chunk: every T-th tile, cheap diagonal ones evenly)
+    constexpr bool kStride = T > 1 && SKIP_PAD;
+    constexpr int kStep = kStride ? T : 1;
+    const int u0 = kStride ? tw : chunk_begin(U, C * T, c * T + tw);
+    const int u1 = kStride ? U : chunk_begin(U, C * T, c * T + tw + 1);
     // Small workgroups prefetch the next tile into registers while the
     // current one is consumed; 16-wave blocks (one per CU, 128 VGPRs) have
     // no registers to spare and rely on the other waves to hide the load.
@@ -653,7 +666,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     // at 2^20 bodies).
     constexpr bool kSelfDiag = (W == 1 && K <= 4);
     int u = u0, delta = 0, jbase = 0;
-    for (; u < u1; ++u)
+    for (; u < u1; u += kStep)
         if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
     float4 next = make_float4(0.f, 0.f, 0.f, 0.f);
     if (kPrefetch && u < u1 && tid < 64) next = load_particle(x, m, jbase + tid, n);
@@ -677,7 +690,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     };
     // the tile after the current one, and its load
     const auto advance = [&]() {
-        for (++u; u < u1; ++u)
+        for (u += kStep; u < u1; u += kStep)
             if ((jbase = tile_base<PB>(u, I, M, d_lo, delta)) < n) break;
         if (kPrefetch && u < u1 && tid < 64) next = load_particle(x, m, jbase + tid, n);
     };
@@ -711,11 +724,10 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
         float4 *slot = &jacc[b * W + wv][0];
         if (!diag) {
             if (!SKIP_PAD || kv == K)
-                ring_tile_steps<K, false, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz,
-                                               tp);
-            else if (kv > 0)
-                ring_tile_steps<K, true, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz,
-                                              tp, kv);
+                ring_tile_steps<K, K, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz, tp);
+            else
+                ring_tile_some<K, K - 1, POT>(kv, xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty,
+                                              tz, tp);
         } else if constexpr (kSelfDiag) {
             // one wave: its row group k is the block's tile k, so diagonal
             // tile t meets row groups k < t pair-once and row group t itself

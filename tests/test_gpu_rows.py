@@ -3,7 +3,7 @@ group size the sizes below choose, groups that straddle a tile, ragged last
 tiles and groups, and the edges of the band in which they stand in for the
 two-row pair-once variants.  Above it: one-wave pair-once blocks with a tile
 per wave, ragged last blocks, odd and even block counts, the edges of their
-range."""
+range.  Ensembles on the same blocks."""
 
 import numpy as np
 import pytest
@@ -67,6 +67,20 @@ def test_adjoint(nb, n, with_v):
     # normwise, the adjoint's tolerance of the other GPU tests
     assert np.linalg.norm(host(gx[:n]) - rx, axis=1).max() <= 1e-4 * np.linalg.norm(rx, axis=1).max()
     assert np.abs(host(gm[:n]) - rm).max() <= 1e-4 * np.abs(rm).max()
+
+
+@pytest.mark.parametrize("sizes", [[1, 63, 64, 65, 128, 129, 193, 256], [257, 300, 385, 449, 511, 512, 513],
+                                   [640, 705, 769, 1000, 1025, 1217, 1281, 1793, 2048]])
+def test_ensemble(nb, sizes):
+    # four waves share a block's tiles: last blocks of one to four row groups,
+    # odd and even block counts, fewer tiles than waves
+    dev = need_gpu()
+    ens = inputs.ensemble(sizes + [sizes[-1]], key=(77, len(sizes)))
+    a, p = nb.forces_batched(to_dev(ens.x, dev), to_dev(ens.m, dev), ens.offsets, ens.eps2)
+    a2, _ = nb.forces_batched(to_dev(ens.x, dev), to_dev(ens.m, dev), ens.offsets, ens.eps2)
+    assert torch.equal(a, a2)
+    ar, pr = R.forces_batched(ens.offsets, ens.x, ens.m, ens.eps2)
+    assert_parity(host(a), host(p), ar, pr, label=f"ensemble {sizes}")
 
 
 @pytest.mark.parametrize("n", [1, 130, 2501, 5003, 11999])
