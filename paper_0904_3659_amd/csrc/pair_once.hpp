@@ -221,7 +221,7 @@ inline void sym_group(const SymPlan &pl, int g, int *d_lo, int *d_hi)
 // 87% CU-busy).
 __device__ __forceinline__ int chunk_begin(int U, int C, int c)
 {
-    if (U <= C) return (int)((long long)U * c / C);
+    if (U <= C) return c < U ? c : U;
     if (c == C) return U;
     const float x = (float)c / (float)C;
     const float t = fmaxf(x - 0.5f, 0.0f);
