@@ -965,6 +965,11 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
                                              epi, fused);
     }
     if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
+    // Two-wave blocks of 512 keep at most 52 chunks (partials to write and fold per
+    // row).  As planned / 76 / 52 / 44: 647 / 641 / 633 / 640 us at 40,000 bodies
+    // (104 planned), 867 / 858 / 845 / 849 at 47,000, 975 / 971 / 959 / 959 at
+    // 50,021, 1616 / 1611 / 1604 / 1607 at 65,536.
+    if (KW == 2 && KK == 4 && ROUNDS > 1 && pl.C > 52) pl.C = 52;
     return launch_backward_sym<KW, KK>(pl, ws, name, x, m, n, eps2, ga, gp, gx, gm, stream, epi,
                                        fused);
 }

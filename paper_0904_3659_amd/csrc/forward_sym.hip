@@ -142,6 +142,11 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
             return launch_sym<1, 4>(one, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
     }
     if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
+    // Two-wave blocks of 1,024 keep at most 72 chunks (partials to write and fold
+    // per row).  As planned / 96 / 72 / 52: 541 / 524 / 521 / 558 us at 50,000
+    // bodies (168 planned), 709 / 699 / 688 / 717 at 60,000, 823 / 819 / 807 /
+    // 820 at 65,536, 1203 / 1205 / 1195 / 1196 at 80,000.
+    if (KW == 2 && KK == 8 && ROUNDS > 1 && pl.C > 72) pl.C = 72;
     return launch_sym<KW, KK>(pl, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
 }
 
