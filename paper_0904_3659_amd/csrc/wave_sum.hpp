@@ -1,5 +1,5 @@
-// Sum over the 64 lanes of a wave in a fixed order, for the row-group
-// and row-per-wave kernels of small n.
+// Sums over the 64 lanes of a wave in a fixed order, for the row-group kernels
+// of small n.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -12,19 +12,6 @@ __device__ __forceinline__ float dpp_swap_add(float v)
 {
     const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false);
     return v + __builtin_bit_cast(float, o);
-}
-
-// Every lane gets the same bits: each step adds lane pairs that exchange
-// values, and a + b rounds as b + a.  Call with all 64 lanes active.
-__device__ __forceinline__ float wave_sum(float v)
-{
-    v = dpp_swap_add<0xB1>(v);   // quad_perm [1,0,3,2]: lane l ^ 1
-    v = dpp_swap_add<0x4E>(v);   // quad_perm [2,3,0,1]: lane l ^ 2
-    v = dpp_swap_add<0x141>(v);  // row_half_mirror: the other quad of 8 lanes
-    v = dpp_swap_add<0x140>(v);  // row_mirror: the other half of 16 lanes
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    return v;
 }
 
 // The other half of a pair of registers: lanes 32..63 of a and lanes 0..31 of
@@ -45,7 +32,9 @@ __device__ __forceinline__ float swap16_add(float a, float b)
 }
 
 // Sums of four values over the 64 lanes, in a fixed order: row g of 16 lanes
-// ends with the total of v[quad_of_row(g)] in every lane.  Four values share
+// ends with the total of v[quad_of_row(g)] in every lane (the same bits in each:
+// every step adds lane pairs that exchange values, and a + b rounds as b + a).
+// Call with all 64 lanes active.  Four values share
 // the first two halvings, so they take 9 cross-lane steps instead of 24.
 __device__ __forceinline__ float wave_sum4(const float (&v)[4])
 {
