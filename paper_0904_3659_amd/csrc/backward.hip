@@ -847,11 +847,12 @@ nbody_status adj_occupancy_half(int *per_cu)
     return st;
 }
 
-// Sizes at which the two-wave step-split pair-once variants run the row-group
-// kernel instead (as kRowBandEnd of the forward).  Whole calls with / without
-// potential weights, pair-once against row groups: 21.1 / 20.4 and 14.6 / 13.2
-// us at 4,096 bodies, 24.1 / 23.3 and 20.5 / 18.8 at 5,000, 29.9 / 28.8 and
-// 27.3 / 24.9 at 6,001, 31.8 / 30.3 and 33.0 / 30.4 at 6,500.
+// Sizes at which the bwd_sym_s2 variants run the row-group kernel instead (as
+// kRowBandEnd of the forward).  Whole calls with / without potential weights,
+// pair-once (two waves to a tile) against row groups: 21.1 / 20.4 and 14.6 /
+// 13.2 us at 4,096 bodies, 24.1 / 23.3 and 20.5 / 18.8 at 5,000, 29.9 / 28.8 and
+// 27.3 / 24.9 at 6,001, 31.8 / 30.3 and 33.0 / 30.4 at 6,500; a tile per wave
+// takes 28.2 with them at 6,200.
 constexpr int kBwdRowBandBegin = 4000, kBwdRowBandEnd = 6200;
 bool bwd_row_band(int n) { return n >= kBwdRowBandBegin && n < kBwdRowBandEnd; }
 

@@ -572,7 +572,7 @@ static int variant_index(const char *name)
 }
 
 // Measured on MI355X: the pair-once kernel wins from about 4,500 particles
-// on, one wave per row below.  Its
+// on, row groups below.  Its
 // workspace is bounded (ring groups, about 1 GiB up to 2^22 particles,
 // 256 n bytes above); beyond 2^24 particles, where a group would hold very
 // few ring offsets, the float64-sum gather takes over.

@@ -19,7 +19,7 @@
 //       H_I = (M-1)/2, plus delta = M/2 when M is even and I < M/2,
 //   so every unordered pair of distinct blocks is met exactly once.  The
 //   block's tile sequence (diagonal tiles, then ring tiles delta-major) is
-//   cut into the C chunks (chunk_begin).
+//   cut into the C chunks (chunk_begin; one_tile_plan).
 //
 // j-tiles of 64 particles are staged in LDS twice over (entries e and
 // e + 64 hold particle e).  On a ring tile, lane l at step s (0..63) meets
