@@ -571,7 +571,7 @@ static int variant_index(const char *name)
     return 0;
 }
 
-// Measured on MI355X: the pair-once kernel wins from about 4,500 particles
+// Measured on MI355X: the pair-once kernel wins from about 10,500 particles
 // on, row groups below.  Its
 // workspace is bounded (ring groups, about 1 GiB up to 2^22 particles,
 // 256 n bytes above); beyond 2^24 particles, where a group would hold very
