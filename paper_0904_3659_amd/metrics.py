@@ -43,7 +43,8 @@ def pairs_ensemble(sizes) -> int:
 
 
 def is_pair_once(variant: str) -> bool:
-    """Whether a kernel variant evaluates each unordered pair once."""
+    """Whether a kernel variant evaluates each unordered pair once (away from
+    the small sizes at which it runs as row groups, every ordered pair)."""
     return variant.startswith(("fwd_sym", "bwd_sym", "bat_sym"))
 
 
