@@ -640,6 +640,70 @@ __device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const flo
     slot[lane] = make_float4(lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w);
 }
 
+// One step s of a one-wave block's diagonal tile: rows k < R meet entry l + s
+// pair-once.
+template <int K, int R, bool HAS_V>
+__device__ __forceinline__ void adj_diag_step(const AdjRow (&row)[K], const float4 *txm,
+                                              const float4 *twv, float4 *sl, int s, float eps2,
+                                              float4 (&tk)[K])
+{
+    if constexpr (R > 0) {
+        // keep this step's slot read after the previous step's write
+        __asm__ volatile("" ::: "memory");
+        const float4 q = txm[s];
+        const float4 wq = twv[s];
+        float4 ja = sl[s];
+        adj_pair_rows<K, HAS_V, R>(row, q, wq, -3.0f * q.w, eps2, tk, ja);
+        sl[s] = ja;
+    }
+}
+
+// Diagonal tile t of a one-wave block, whose rows are the wave's row group t:
+// row groups k < t meet it pair-once, and group t its own 64 particles (lane l
+// and particle l + s for s = 1..31; at s = 32 both lanes of a pair take their
+// own side), as diag_self_steps of the forward.  Loops of two steps kept rolled:
+// there are K instances.  Calls against masked ordered pairs, one row at a
+// time, with / without potential weights: 37.0 / 34.9 -> 35.8 / 33.9 us at 8,000
+// bodies, 48.1 -> 43.8 at 9,000, 74.7 / 70.8 -> 74.0 / 67.5 at 12,500, 123.6 /
+// 114.2 -> 122.9 / 111.6 at 16,384, 612 / 561 -> 613 / 549 at 39,000.
+template <int K, bool HAS_V, int KT = 0>
+__device__ __forceinline__ void adj_self_steps(int t, const AdjRow (&row)[K], const float4 *tile_xm,
+                                               const float4 *tile_wv, float4 *slot, int lane,
+                                               float eps2, float4 (&tk)[K])
+{
+    if (t != KT) {
+        if constexpr (KT + 1 < K)
+            adj_self_steps<K, HAS_V, KT + 1>(t, row, tile_xm, tile_wv, slot, lane, eps2, tk);
+        return;
+    }
+    const float4 *txm = tile_xm + lane;
+    const float4 *twv = tile_wv + lane;
+    float4 *sl = slot + lane;
+    adj_diag_step<K, KT, HAS_V>(row, txm, twv, sl, 0, eps2, tk);
+#pragma nounroll
+    for (int s = 1; s < 31; s += 2) {
+        adj_diag_step<K, KT + 1, HAS_V>(row, txm, twv, sl, s, eps2, tk);
+        adj_diag_step<K, KT + 1, HAS_V>(row, txm, twv, sl, s + 1, eps2, tk);
+    }
+    adj_diag_step<K, KT + 1, HAS_V>(row, txm, twv, sl, 31, eps2, tk);
+    adj_diag_step<K, KT, HAS_V>(row, txm, twv, sl, 32, eps2, tk);
+    const AdjRow &w = row[KT];
+    adj_row_term(make_float4(w.x, w.y, w.z, w.m), make_float4(w.wx, w.wy, w.wz, w.v), txm[32],
+                 twv[32], eps2, false, tk[KT]);
+    if (KT > 0) {
+#pragma nounroll
+        for (int s = 33; s < 63; s += 2) {
+            adj_diag_step<K, KT, HAS_V>(row, txm, twv, sl, s, eps2, tk);
+            adj_diag_step<K, KT, HAS_V>(row, txm, twv, sl, s + 1, eps2, tk);
+        }
+        adj_diag_step<K, KT, HAS_V>(row, txm, twv, sl, 63, eps2, tk);
+    }
+    __asm__ volatile("" ::: "memory");
+    const float4 lo = slot[lane];
+    const float4 hi = slot[lane + 64];
+    slot[lane] = make_float4(lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w);
+}
+
 // HAS_V false: no potential weights (grad_p NULL); their terms are not
 // formed on ring tiles (bitwise the same result as v = 0).
 // Each wave owns K * 64 of the block's rows.  Buffers, barriers, slot sums and the tile split of one-wave blocks (T waves)
@@ -753,6 +817,8 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
         const bool diag = (cur_delta == 0);
         if (!diag)
             adj_ring_steps<K, HAS_V>(row, txm, twv, slot, lane, eps2, tk);
+        else if constexpr (W == 1)
+            adj_self_steps<K, HAS_V>(cur_u, row, txm, twv, slot, lane, eps2, tk);
         else
             adj_diag_steps<K>(row, kk, txm, twv, slot, lane, wv * K, cur_u, cur_base, eps2, tk);
         __asm__ volatile("" ::: "memory");
@@ -784,7 +850,7 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
             }
         } else if (wv == cur_u / K) {
             // this wave holds diagonal tile cur_u's rows (lane-slot cur_u % K);
-            // the diagonal steps use slots 0..63 only
+            // tile particle e's sums are in slot e
             float4 sum = jacc[b * W][lane];
 #pragma unroll
             for (int w2 = 1; w2 < W; ++w2) {
