@@ -28,7 +28,7 @@
  *   stream's workspace, counters and the batched plan exist; a first call
  *   allocates and a first batched call synchronises, which capture forbids).
  *   The graph keeps the workspace addresses of that stream (partial sums,
- *   the leap-frog calls' second buffers, counters): while it may
+ *   the leap-frog adjoint's buffer, counters): while it may
  *   replay, make no call on that stream that needs a larger one of them, do
  *   not call nbody_release_workspace(), run no variant timer
  *   (nbody_autotune, nbody_autotune_batched) on that stream, and keep the
@@ -265,9 +265,9 @@ nbody_status nbody_kick_drift(float *x, float *v, const float *a, int64_t n, flo
  * step's end kick, the next step's start kick and its drift run in the
  * final reduction kernel of the pair-once force variants (two launches per
  * step), in the force kernel itself where that is the row-group kernel (one
- * launch per step), otherwise in one element-wise launch after the force.
- * Library memory: that of nbody_forces plus, where the row-group kernel
- * runs, 12 n bytes per (device, stream) for a second position array.
+ * launch per step, a holding positions in between; its contents are undefined
+ * if the call fails), otherwise in one element-wise launch after the force.
+ * Library memory: that of nbody_forces.
  * Errors: n < 0 or > NBODY_MAX_N, steps < 0 or > NBODY_MAX_STEPS, eps2 as
  * for nbody_forces, dt not finite, NULL x, v, a or m with n > 0 and
  * steps > 0, any two of x, v, a, m, x_hist overlapping -> INVALID_ARGUMENT.

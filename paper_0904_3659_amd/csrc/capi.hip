@@ -707,13 +707,12 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
     const int variant = select_variant(NBODY_KIND_FORWARD, n);
     const float kick = -0.5f * dt;  // half kick with the physical acceleration -a
     // The row-group kernels update v and x after their sums while other
-    // workgroups still read x: the positions then alternate between x and a
-    // second buffer, starting where the last drift ends in x.
-    // Without that buffer the update runs in a launch of its own.
-    float *cur = x, *other = nullptr;
-    if (steps > 1 && forward_takes_rows(variant, (int)n))
-        other = static_cast<float *>(workspace_aux_try(dev, s, v3));
-    const bool rows = other != nullptr;
+    // workgroups still read x: the positions then alternate between x and a,
+    // which holds a result only after the last step, starting where the last
+    // drift ends in x.  Both are the caller's: no library memory that another
+    // thread's call on the stream, or a captured call, would share.
+    const bool rows = steps > 1 && forward_takes_rows(variant, (int)n);
+    float *cur = x, *other = a;
     if (rows && ((steps - 1) & 1)) std::swap(cur, other);
     // start kick and drift of the first step
     LfEpi e;
@@ -739,7 +738,8 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
         e.xh = (!last && x_hist) ? x_hist + 3 * (size_t)n * (size_t)(t + 1) : nullptr;
         bool fused = false;
         prof_mark(s, -1);
-        st = forward_run(variant, dev, cur, m, (int)n, eps2, a, nullptr, s, &e, &fused);
+        st = forward_run(variant, dev, cur, m, (int)n, eps2, rows && !last ? nullptr : a, nullptr, s,
+                         &e, &fused);
         if (st == NBODY_OK && !fused) st = lf_epilogue_run(a, nullptr, n, e, s);
         if (st == NBODY_OK) prof_mark(s, 2);
         if (rows && !last) std::swap(cur, other);

@@ -40,8 +40,9 @@ __global__ __launch_bounds__(256) void kick_drift_kernel(float *__restrict__ x,
 }
 
 // The leap-frog update of `e` for rows whose force (or VJP) result is
-// already stored in r3 / r1: the unfused form of the reduction epilogue.
-__global__ __launch_bounds__(256) void lf_epilogue_kernel(const float *__restrict__ r3,
+// already stored in r3 / r1: the unfused form of the reduction epilogue.  e.xo
+// may be r3 (each row is read and written by one thread).
+__global__ __launch_bounds__(256) void lf_epilogue_kernel(const float *r3,
                                                           const float *__restrict__ r1, int n,
                                                           LfEpi e)
 {

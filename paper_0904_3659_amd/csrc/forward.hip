@@ -353,8 +353,9 @@ struct RowArgs {
     float *p;
 };
 
-// With the leap-frog update after the store of a (a struct of its own: the
-// launch copies its arguments, and a plain call should not copy these).
+// With the leap-frog update (a struct of its own: the launch copies its
+// arguments, and a plain call should not copy these).  a NULL: not stored (the
+// array serves as the other position buffer).
 struct RowEpiArgs : RowArgs {
     LfEpi e;
 };
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(256) void forward_row_kernel(
 #pragma unroll
     for (int w = 1; w < 4; ++w) s += red[w][threadIdx.x];
     if (c < 3) {
-        P.a[3 * (size_t)(i0 + k) + c] = s;
+        if (!EPI || P.a) P.a[3 * (size_t)(i0 + k) + c] = s;
         if constexpr (EPI) lf_coord(P.e, 3 * (size_t)(i0 + k) + c, s);
     } else if (POT) {
         P.p[i0 + k] = s;
