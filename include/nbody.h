@@ -28,7 +28,7 @@
  *   stream's workspace, counters and the batched plan exist; a first call
  *   allocates and a first batched call synchronises, which capture forbids).
  *   The graph keeps the workspace addresses of that stream (partial sums,
- *   the leap-frog adjoint's buffer, counters): while it may
+ *   the leap-frog adjoint's 16 n-byte buffer, counters): while it may
  *   replay, make no call on that stream that needs a larger one of them, do
  *   not call nbody_release_workspace(), run no variant timer
  *   (nbody_autotune, nbody_autotune_batched) on that stream, and keep the
@@ -302,7 +302,7 @@ nbody_status nbody_leapfrog(float *x, float *v, float *a, const float *m, int64_
  * The updates run in the final reduction kernel of the pair-once adjoint
  * variants and in the row-group adjoint kernel itself (the next step's
  * lv += dt lx with them).  Library memory: that of nbody_forces_backward
- * plus 16 n bytes per (device, stream), 28 n with the row-group kernel.
+ * plus 16 n bytes per (device, stream).
  * Errors: unknown flag bits, n, steps, eps2 or dt as for nbody_leapfrog,
  * NULL pos, m, lx, lv or lm with n > 0 and steps > 0, any two arrays
  * overlapping -> INVALID_ARGUMENT.

@@ -156,27 +156,6 @@ nbody_status workspace_aux(const Device &dev, hipStream_t stream, size_t bytes, 
     return grow_buffer(dev, stream, 1, bytes, ptr);
 }
 
-void *workspace_aux_try(const Device &dev, hipStream_t stream, size_t bytes)
-{
-    {
-        std::lock_guard<std::mutex> lock(g_ws_mu);
-        auto it = g_ws.find({dev.id, stream, 1});
-        if (it != g_ws.end() && it->second.bytes >= bytes) return it->second.ptr;
-    }
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    void *ptr = nullptr;
-    if (workspace_aux(dev, stream, bytes, &ptr) != NBODY_OK) {
-        (void)hipGetLastError();
-        clear_error();
-        return nullptr;
-    }
-    return ptr;
-}
-
 size_t workspace_size(const Device &dev, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lock(g_ws_mu);
@@ -779,19 +758,16 @@ nbody_status nbody_leapfrog_adjoint(const float *pos, const float *m, int64_t n,
     const hipStream_t s = (hipStream_t)stream;
     const int variant = select_variant(NBODY_KIND_BACKWARD, n);
     // VJP results of variants that cannot take the update in their final
-    // reduction; for the row-group kernels, whose other workgroups still read
-    // the weights lv when a row's update is due, a second lv to alternate with
-    // (without it the update runs in a launch of its own)
-    void *aux = backward_takes_rows(variant, (int)n) ? workspace_aux_try(dev, s, 28 * (size_t)n)
-                                                     : nullptr;
-    const bool rows = aux != nullptr;
-    if (!rows) {
-        st = workspace_aux(dev, s, 16 * (size_t)n, &aux);
-        if (st != NBODY_OK) return st;
-    }
+    // reduction; for the row-group kernels, which always take it but whose
+    // other workgroups still read the weights lv when a row's update is due,
+    // a second lv to alternate with
+    void *aux = nullptr;
+    st = workspace_aux(dev, s, 16 * (size_t)n, &aux);
+    if (st != NBODY_OK) return st;
+    const bool rows = backward_takes_rows(variant, (int)n);
     float *gx = static_cast<float *>(aux);
     float *gm = gx + 3 * (size_t)n;
-    float *cur = lv, *other = rows ? gm + n : nullptr;
+    float *cur = lv, *other = rows ? gx : nullptr;
     LfEpi e;
     e.mode = kLfAdjoint;
     e.dt = dt;
@@ -807,7 +783,9 @@ nbody_status nbody_leapfrog_adjoint(const float *pos, const float *m, int64_t n,
         prof_mark(s, -1);
         nbody_status r = backward_run(variant, dev, xp, m, (int)n, eps2, cur, nullptr, gx, gm, s,
                                       &e, &fused);
-        if (r == NBODY_OK && !fused) r = lf_epilogue_run(gx, gm, n, e, s);
+        if (r == NBODY_OK && !fused)
+            r = rows ? fail(NBODY_ERROR_INTERNAL, "row-group adjoint without its update")
+                     : lf_epilogue_run(gx, gm, n, e, s);
         if (r == NBODY_OK) prof_mark(s, 2);
         if (rows && chain) std::swap(cur, other);
         return r;

@@ -36,11 +36,8 @@ nbody_status current_device(Device *dev);
 nbody_status workspace(const Device &dev, hipStream_t stream, size_t bytes, void **ptr);
 // A second buffer of the same kind (same lifetime rules), for callers that
 // keep data across calls that use workspace() (the leap-frog adjoint's
-// unfused VJP results).
+// unfused VJP results, or its second lv).
 nbody_status workspace_aux(const Device &dev, hipStream_t stream, size_t bytes, void **ptr);
-// That buffer where the caller can do without: NULL if it would have to be
-// allocated while the stream is being captured, or cannot be.
-void *workspace_aux_try(const Device &dev, hipStream_t stream, size_t bytes);
 
 // Per-(device, stream) array of at least `count` int counters that are zero
 // between calls (kernels that use them leave them at zero); zero-filled

@@ -100,3 +100,43 @@ def test_captured_call_holds_no_library_memory(nb, steps):
         torch.cuda.synchronize()
         assert all(torch.equal(t, w) for t, w in zip(got, want)), r
         assert all(torch.equal(t, w) for t, w in zip(beside, want)), r
+
+
+def test_captured_reverse_sweep_keeps_its_buffer(nb):
+    # 16 n bytes for the row-group adjoint too: at 65,536 bodies the 1 MiB that
+    # the captured small sweep already holds, so the buffer stays where it is
+    dev = need_gpu()
+    n, big, steps = 2000, 1 << 16, 3
+    pos = to_dev(inputs.normal((steps + 1, n, 3), (92, 0)), dev)
+    m = to_dev(inputs.lognormal_masses(n, (92, 1)), dev)
+    lx, lv = (to_dev(inputs.normal((n, 3), (92, 2 + k)), dev) for k in range(2))
+    lm = torch.zeros(n, device=dev)
+    want = [t.clone() for t in (lx, lv, lm)]
+    nb.leapfrog_adjoint_(pos, m, 1e-3, 1e-2, *want)
+    got = [t.clone() for t in (lx, lv, lm)]
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        nb.leapfrog_adjoint_(pos, m, 1e-3, 1e-2, *[t.clone() for t in (lx, lv, lm)])
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        nb.leapfrog_adjoint_(pos, m, 1e-3, 1e-2, *got)
+    pb = to_dev(inputs.normal((2, big, 3), (92, 5)), dev)
+    mb = to_dev(inputs.equal_masses(big), dev)
+    nb.set_variant(nb.BACKWARD, nb.variant_names(nb.BACKWARD).index("bwd_row_k1"))
+    try:
+        with torch.cuda.stream(s):
+            nb.leapfrog_adjoint_(pb, mb, 1e-3, 1e-2, torch.ones_like(pb[0]), torch.ones_like(pb[0]),
+                                 torch.zeros_like(mb))
+        torch.cuda.synchronize()
+    finally:
+        nb.set_variant(nb.BACKWARD, -1)
+    hold = [torch.full((1 << 18,), float("nan"), device=dev) for _ in range(8)]  # takes freed memory
+    for r in range(3):
+        for t, src in zip(got, (lx, lv, lm)):
+            t.copy_(src)
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(t, w) for t, w in zip(got, want)), r
+        assert all(bool(t.isnan().all()) for t in hold)
