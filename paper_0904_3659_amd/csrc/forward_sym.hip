@@ -25,19 +25,19 @@ constexpr int kSymSplit = W == 1 ? kTileSplit : 1;
 template <int W>
 constexpr int kSymThreads = 64 * W * kSymSplit<W>;
 
-template <int W, int K, bool POT>
-__global__ __launch_bounds__(kSymThreads<W>) void forward_sym_kernel(SymArgs A)
+template <int W, int K, bool POT, bool SHORT = false, bool HELD = W != 1>
+__global__ __launch_bounds__(kSymThreads<W>, K == 8 ? 3 : 1) void forward_sym_kernel(SymArgs A)
 {
     const int c = blockIdx.x / A.M;  // chunk-major (chunk_begin)
     const int I = blockIdx.x - c * A.M;
     if constexpr (W == 1) {
         __shared__ float4 lds[kTileSplit * kWaveLds];
-        pair_once_block<1, K, false, POT, kTileSplit>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo,
+        pair_once_block<1, K, false, POT, kTileSplit, SHORT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo,
                                                       A.d_hi, A.partial, lds, nullptr);
     } else {
         __shared__ float4 tile[kSymBuffers<W> * kTileLds];
         __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
-        pair_once_block<W, K, false, POT>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
+        pair_once_block<W, K, false, POT, 1, SHORT, HELD>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
                                           A.partial, tile, jacc);
     }
 }
@@ -55,7 +55,7 @@ nbody_status sym_occupancy(int *per_cu)
 }
 
 // The launches of a plan whose blocks are W waves x K rows per lane.
-template <int W, int K>
+template <int W, int K, bool SHORT, bool HELD = W != 1>
 nbody_status launch_sym(const SymPlan &pl, void *ws, const char *name, const float *x,
                         const float *m, int n, float eps2, float *a, float *p, hipStream_t stream,
                         const LfEpi *epi, bool *fused)
@@ -72,10 +72,10 @@ nbody_status launch_sym(const SymPlan &pl, void *ws, const char *name, const flo
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (p)
-            hipLaunchKernelGGL((forward_sym_kernel<W, K, true>), dim3(pl.M * C),
+            hipLaunchKernelGGL((forward_sym_kernel<W, K, true, SHORT, HELD>), dim3(pl.M * C),
                                dim3(kSymThreads<W>), 0, stream, A);
         else
-            hipLaunchKernelGGL((forward_sym_kernel<W, K, false>), dim3(pl.M * C),
+            hipLaunchKernelGGL((forward_sym_kernel<W, K, false, SHORT, HELD>), dim3(pl.M * C),
                                dim3(kSymThreads<W>), 0, stream, A);
         prof_mark(stream, 1);
         nbody_status st = check_launch(name);
@@ -139,15 +139,22 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     if constexpr (W == 1 || (W == 4 && K == 4 && KW == 4)) {
         SymPlan one;
         if (n >= kOneTileBegin && n < kOneTileEnd && one_tile_plan(n, 4, pl, &one))
-            return launch_sym<1, 4>(one, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
+            return launch_sym<1, 4, (4 > K)>(one, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
     }
     if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
     // Two-wave blocks of 1,024 keep at most 72 chunks (partials to write and fold
     // per row).  As planned / 96 / 72 / 52: 541 / 524 / 521 / 558 us at 50,000
     // bodies (168 planned), 709 / 699 / 688 / 717 at 60,000, 823 / 819 / 807 /
     // 820 at 65,536, 1203 / 1205 / 1195 / 1196 at 80,000.
-    if (KW == 2 && KK == 8 && ROUNDS > 1 && pl.C > 72) pl.C = 72;
-    return launch_sym<KW, KK>(pl, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
+    if constexpr (KW == 2 && KK == 8 && ROUNDS > 1) {
+        if (pl.C > 72) pl.C = 72;
+        // short chunks (up to some 110,000 bodies) hand nothing over in between:
+        // 1% less time at 65,536 bodies without that code
+        if (longest_chunk(pl, KW * KK) <= kHeldTiles)
+            return launch_sym<KW, KK, (KK > K), false>(pl, ws, name, x, m, n, eps2, a, p, stream, epi,
+                                                       fused);
+    }
+    return launch_sym<KW, KK, (KK > K)>(pl, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
 }
 
 }  // namespace

@@ -228,6 +228,14 @@ __device__ __forceinline__ int chunk_begin(int U, int C, int c)
     return c + (int)((float)(U - C) * (4.0f / 3.0f) * (x - t * t));
 }
 
+// Tiles of the longest chunk of a plan whose blocks hold TPB tiles (its first
+// group's first, rounded up).
+inline int longest_chunk(const SymPlan &pl, int TPB)
+{
+    const int U = (pl.G + 1) * TPB;
+    return U <= pl.C ? 1 : 2 + (int)((4LL * (U - pl.C) + 3LL * pl.C - 1) / (3LL * pl.C));
+}
+
 // Waves that share a one-wave block's chunk: the chunk partials of one-wave
 // blocks were two thirds of what the fold reads (1 tile, 1 partial).  Forward
 // calls with four waves to a partial against one: 86.7 -> 81.5 us at 18,000
@@ -417,6 +425,54 @@ __device__ __forceinline__ void ring_tile_steps(const float (&xi)[K], const floa
     slot[lane] = make_float4(lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w);
 }
 
+// ring_tile_steps with shorter slot chains, for blocks held with more rows per
+// lane than the plan they come from (twice the rows, twice as long float32
+// chains): the slots are emptied every kSlotSteps steps into the lane's sum of
+// its tile particle.  Error of p against float64 (2-norm) at 65,536 bodies: four
+// rows per lane 2.7e-8, eight 3.0e-8, eight so 2.6e-8; every 32 steps 2.7e-8.
+// Whole calls take 1% longer.
+constexpr int kSlotSteps = 16;
+
+template <int K, bool POT>
+__device__ __forceinline__ void ring_tile_short(const float (&xi)[K], const float (&yi)[K],
+                                                const float (&zi)[K], const float (&mi)[K],
+                                                const float4 *tile, float4 *slot, int lane,
+                                                float eps2, float (&tx)[K], float (&ty)[K],
+                                                float (&tz)[K], float (&tp)[K])
+{
+    const float4 *tq = tile + lane;
+    float4 *sl = slot + lane;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 q = tq[0], sum = zero;
+#pragma nounroll
+    for (int h = 0; h < 64 / kSlotSteps; ++h) {
+        constexpr int kUnroll = K > 4 ? 4 : 8;
+#pragma unroll kUnroll
+        for (int s = 0; s < kSlotSteps; ++s) {
+            // as in ring_tile_steps
+            __asm__ volatile("" ::: "memory");
+            float4 g = sl[s];
+            const float4 qn = tq[s + 1];
+            pair_once_rows<K, K, POT>(xi, yi, zi, mi, q, eps2, tx, ty, tz, tp, g);
+            sl[s] = g;
+            q = qn;
+        }
+        tq += kSlotSteps;
+        sl += kSlotSteps;
+        __asm__ volatile("" ::: "memory");
+        const float4 lo = slot[lane];
+        const float4 hi = slot[lane + 64];
+        sum.x += lo.x + hi.x;
+        sum.y += lo.y + hi.y;
+        sum.z += lo.z + hi.z;
+        sum.w += lo.w + hi.w;
+        slot[lane] = zero;
+        slot[lane + 64] = zero;
+    }
+    __asm__ volatile("" ::: "memory");
+    slot[lane] = sum;
+}
+
 // ring_tile_steps of the first kv < K row groups.
 template <int K, int R, bool POT>
 __device__ __forceinline__ void ring_tile_some(int kv, const float (&xi)[K], const float (&yi)[K],
@@ -545,6 +601,11 @@ __device__ __forceinline__ void diag_tile_steps(const float (&xi)[K], const floa
     }
 }
 
+// Tiles whose sums a row holds in float32 registers before they go to the
+// chunk's partial: a float32 sum over every tile of a long chunk loses more than
+// the rest of a row's sums together (from 64 tiles on; 2^18 bodies).
+constexpr int kHeldTiles = 16;
+
 // LDS entries of one wave of a tile-split workgroup: the tile and the slots,
 // and at the end K <= 4 rows of row sums.
 constexpr int kWaveLds = kTileLds + kSlotLds;
@@ -583,13 +644,17 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 // before the barrier) and all threads share the sum of the W slot sets, one
 // component each.
 //
+// HELD: chunks of more than kHeldTiles tiles hand their sums over in between.
+// SHORT: ring_tile_short.
+//
 // T > 1 (one-wave blocks): T waves of a workgroup hold the same rows and take
 // one of T consecutive sub-chunks of chunk c each, with an LDS region of
 // kWaveLds entries per wave (its tile, then its slots) from `tile` on; their
-// row sums are added in wave order at the end, so that a chunk writes (and the
-// fold reads) one partial for T waves' tiles.  (Ensembles, one chunk per block:
+// row sums are added in wave order (in float64) at the end, so that a chunk writes
+// (and the fold reads) one partial for T waves' tiles.  (Ensembles, one chunk per block:
 // every T-th tile each.)
-template <int W, int K, bool SKIP_PAD = false, bool POT = true, int T = 1>
+template <int W, int K, bool SKIP_PAD = false, bool POT = true, int T = 1, bool SHORT = false,
+          bool HELD = T == 1 && !SKIP_PAD>
 __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                                                 const float *__restrict__ m, int n, float eps2,
                                                 int M, int I, int c, int C, int d_lo, int d_hi,
@@ -695,6 +760,28 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
         if (kPrefetch && u < u1 && tid < 64) next = load_particle(x, m, jbase + tid, n);
     };
 
+    // The row sums so far, added to the chunk's partial: at the end, and every
+    // kHeldTiles tiles before (HELD).
+    [[maybe_unused]] int held = 0;
+    bool fresh = true;
+    const auto hand_over = [&]() {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (ii[k] < n) {
+                float4 *out = partial + (size_t)c * n + ii[k];
+                float4 v = make_float4(ax[k], ay[k], az[k], ap[k]);
+                if (!fresh) {
+                    const float4 w = *out;
+                    v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+                }
+                *out = v;
+            }
+            ax[k] = ay[k] = az[k] = ap[k] = 0.0f;
+        }
+        held = 0;
+        fresh = false;
+    };
+
     int b = 0;
     if (NB == 2 && u < u1) {
         __syncthreads();  // the LDS buffers are free
@@ -723,7 +810,9 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
         const float4 *cur_tile = tile + b * kTileLds;
         float4 *slot = &jacc[b * W + wv][0];
         if (!diag) {
-            if (!SKIP_PAD || kv == K)
+            if constexpr (SHORT)
+                ring_tile_short<K, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz, tp);
+            else if (!SKIP_PAD || kv == K)
                 ring_tile_steps<K, K, POT>(xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty, tz, tp);
             else
                 ring_tile_some<K, K - 1, POT>(kv, xi, yi, zi, mi, cur_tile, slot, lane, eps2, tx, ty,
@@ -797,12 +886,11 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                 }
         }
         if (NB == 2) b ^= 1;
+        if (HELD && ++held == kHeldTiles) hand_over();
     }
 
     if constexpr (T == 1) {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (ii[k] < n) partial[(size_t)c * n + ii[k]] = make_float4(ax[k], ay[k], az[k], ap[k]);
+        hand_over();
     } else {
         // the T waves' row sums through their own LDS regions, one component
         // of every 64 T / 4 rows per thread
@@ -813,10 +901,10 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
         float *out = reinterpret_cast<float *>(partial + (size_t)c * n + I * PB);
         const float *all = reinterpret_cast<const float *>(lds);
         for (int f = threadIdx.x; f < K * 256; f += T * 64) {
-            float sum = all[f];
+            double sum = all[f];
 #pragma unroll
             for (int w = 1; w < T; ++w) sum += all[w * kWaveLds * 4 + f];
-            if (I * PB + (f >> 2) < n) out[f] = sum;
+            if (I * PB + (f >> 2) < n) out[f] = (float)sum;
         }
     }
 }
