@@ -566,6 +566,20 @@ __device__ __forceinline__ void load_xw(const SymBwdArgs &A, int j, float4 &xm, 
     }
 }
 
+// acc += tk; tk = 0.
+template <int K>
+__device__ __forceinline__ void add_rows(float4 (&acc)[K], float4 (&tk)[K])
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        acc[k].x += tk[k].x;
+        acc[k].y += tk[k].y;
+        acc[k].z += tk[k].z;
+        acc[k].w += tk[k].w;
+        tk[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+}
+
 // The steps of diagonal tile t for one wave (lane l meets tile particle
 // (l + s) mod 64 at step s): row tile a = a0 + k pair-once if a < t,
 // masked ordered pairs if a == t, nothing if a > t (met on diagonal tile a).
@@ -610,34 +624,61 @@ __device__ __forceinline__ void adj_diag_steps(const AdjRow (&row)[K], const int
 // particle e) and the wave's j-side slots number 128, so lane l at step s
 // reads entry l + s and updates slot l + s with no index wrap (immediate
 // LDS offsets in the unrolled loop); particle e's j-side sum is slot e plus
-// slot e + 64, folded into slot e at the end.  Same scheme and ordering
-// argument as the forward pair-once kernel.
-template <int K, bool HAS_V = true>
+// slot e + 64.  Same scheme and ordering argument as the forward pair-once
+// kernel.
+//
+// The slots are emptied every kAdjSlotSteps steps into the lane's sum of its tile
+// particle, which ends in its slot, and one-wave blocks add their row sums tk to
+// acc in the middle of the tile: a slot's float32 chain grows with the rows per
+// lane, and a tile has one wave where two shared its steps before.  Error of
+// dL/dm against float64 (2-norm) at 16,384 bodies: two rows per lane and one
+// chain per tile 2.4e-7, four rows 2.9e-7, four rows so 1.9e-7 (emptied every 16
+// steps 2.1e-7: at 10,600 bodies 4% above the two waves' sums).  Calls take 1%
+// longer.
+template <int W, int K>
+constexpr int kAdjSlotSteps = W == 1 && K == 4 ? 8 : 16;
+
+template <int W, int K, bool HAS_V = true>
 __device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const float4 *tile_xm,
                                                const float4 *tile_wv, float4 *slot, int lane,
-                                               float eps2, float4 (&tk)[K])
+                                               float eps2, float4 (&tk)[K], float4 (&acc)[K])
 {
+    constexpr int kSteps = kAdjSlotSteps<W, K>;
     const float4 *txm = tile_xm + lane;
     const float4 *twv = tile_wv + lane;
     float4 *sl = slot + lane;
-    float4 q = txm[0];
-    float4 wq = twv[0];
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 q = txm[0], wq = twv[0], sum = zero;
+#pragma nounroll
+    for (int h = 0; h < 64 / kSteps; ++h) {
 #pragma unroll 4
-    for (int s = 0; s < 64; ++s) {
-        // keep this step's slot read after the previous step's write
+        for (int s = 0; s < kSteps; ++s) {
+            // keep this step's slot read after the previous step's write
+            __asm__ volatile("" ::: "memory");
+            float4 ja = sl[s];
+            const float4 qn = txm[s + 1];
+            const float4 wqn = twv[s + 1];
+            adj_pair_rows<K, HAS_V>(row, q, wq, -3.0f * q.w, eps2, tk, ja);
+            sl[s] = ja;
+            q = qn;
+            wq = wqn;
+        }
+        txm += kSteps;
+        twv += kSteps;
+        sl += kSteps;
         __asm__ volatile("" ::: "memory");
-        float4 ja = sl[s];
-        const float4 qn = txm[s + 1];
-        const float4 wqn = twv[s + 1];
-        adj_pair_rows<K, HAS_V>(row, q, wq, -3.0f * q.w, eps2, tk, ja);
-        sl[s] = ja;
-        q = qn;
-        wq = wqn;
+        const float4 lo = slot[lane];
+        const float4 hi = slot[lane + 64];
+        sum.x += lo.x + hi.x;
+        sum.y += lo.y + hi.y;
+        sum.z += lo.z + hi.z;
+        sum.w += lo.w + hi.w;
+        slot[lane] = zero;
+        slot[lane + 64] = zero;
+        if (W == 1 && h == 32 / kSteps - 1) add_rows(acc, tk);
     }
     __asm__ volatile("" ::: "memory");
-    const float4 lo = slot[lane];
-    const float4 hi = slot[lane + 64];
-    slot[lane] = make_float4(lo.x + hi.x, lo.y + hi.y, lo.z + hi.z, lo.w + hi.w);
+    slot[lane] = sum;
 }
 
 // One step s of a one-wave block's diagonal tile: rows k < R meet entry l + s
@@ -720,6 +761,7 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
     constexpr int TPB = PB / 64;
     constexpr int NB = kSymBuffers<W>;
     constexpr int T = kAdjSplit<W>;
+    constexpr bool HELD = T == 1;
     static_assert(K * 64 <= kTileLds + kTileLds + kSlotLds, "row sums fit a wave's region");
     // per set of W waves: the tile twice over, its weights, the W slot arrays
     constexpr int kLds = NB * (2 * kTileLds + W * kSlotLds);
@@ -791,6 +833,27 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
         jacc[b * W + wv][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
         jacc[b * W + wv][lane + 64] = make_float4(0.f, 0.f, 0.f, 0.f);
     };
+    // as in pair_once_block
+    [[maybe_unused]] int held = 0;
+    bool fresh = true;
+    const auto hand_over = [&]() {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (kk[k] < n) {
+                float4 *out = A.partial + (size_t)c * n + kk[k];
+                float4 v = acc[k];
+                if (!fresh) {
+                    const float4 w = *out;
+                    v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+                }
+                *out = v;
+            }
+            acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        held = 0;
+        fresh = false;
+    };
+
     int b = 0;
     if (NB == 2 && u < u1) {
         stage(0);
@@ -816,19 +879,13 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
         const float4 *txm = tile_xm + b * kTileLds, *twv = tile_wv + b * kTileLds;
         const bool diag = (cur_delta == 0);
         if (!diag)
-            adj_ring_steps<K, HAS_V>(row, txm, twv, slot, lane, eps2, tk);
+            adj_ring_steps<W, K, HAS_V>(row, txm, twv, slot, lane, eps2, tk, acc);
         else if constexpr (W == 1)
             adj_self_steps<K, HAS_V>(cur_u, row, txm, twv, slot, lane, eps2, tk);
         else
             adj_diag_steps<K>(row, kk, txm, twv, slot, lane, wv * K, cur_u, cur_base, eps2, tk);
         __asm__ volatile("" ::: "memory");
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            acc[k].x += tk[k].x;
-            acc[k].y += tk[k].y;
-            acc[k].z += tk[k].z;
-            acc[k].w += tk[k].w;
-        }
+        add_rows(acc, tk);
         if (NB == 2 && u < u1) stage(b ^ 1);
         block_sync();  // every wave's j-side slots are complete
         if (NB == 2 && u < u1) clear_slots(b ^ 1);
@@ -871,11 +928,10 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
                 }
         }
         if (NB == 2) b ^= 1;
+        if (HELD && ++held == kHeldTiles) hand_over();
     }
     if constexpr (T == 1) {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (kk[k] < n) A.partial[(size_t)c * n + kk[k]] = acc[k];
+        hand_over();
     } else {
         // the T waves' row sums through their own LDS regions
         __asm__ volatile("" ::: "memory");
@@ -885,10 +941,10 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
         float *out = reinterpret_cast<float *>(A.partial + (size_t)c * n + I * PB);
         const float *all = reinterpret_cast<const float *>(lds);
         for (int f = threadIdx.x; f < K * 256; f += T * 64) {
-            float sum = all[f];
+            double sum = all[f];
 #pragma unroll
             for (int w = 1; w < T; ++w) sum += all[w * kLds * 4 + f];
-            if (I * PB + (f >> 2) < n) out[f] = sum;
+            if (I * PB + (f >> 2) < n) out[f] = (float)sum;
         }
     }
 }
