@@ -238,19 +238,17 @@ constexpr int kBwdRowMax = 4;  // rows per group
 // difference e = x_j - x_k = -d, so that every term below is a plain product
 // or accumulating FMA (two-operand encodings; a negated operand would need
 // the longer one, which issues slower): with
-//     3 c . e = (3 m_j) (w_k . e) + (-3 m_k) (w_j . e)
-//     u = r^3 (r^2 (3 c . e) + b') = -r^3 (3 r^2 (c . d) - b'),  b' = -b
+//     c . e = m_j (w_k . e) + (-m_k) (w_j . e)
+//     u = r^3 (3 r^2 (c . e) + b') = -r^3 (3 r^2 (c . d) - b'),  b' = -b
 // the sums are A, B, G += r v_j + r^3 (w_j . e) and C += u e
 // (u e = r^3 (3 r^2 (c . d) + b) d).  MASKED: lanes whose particle is a row
 // itself, or past n, take r = 0.
 template <int K, bool HAS_V, bool MASKED>
 __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4 (&wk)[K],
-                                             const float (&m3)[K], const float (&mn)[K], float4 q,
-                                             float4 wq, float eps2, int j, int i0, int n,
+                                             const float (&mn)[K], float4 q, float4 wq, float eps2, int j, int i0, int n,
                                              RowAcc (&acc)[K])
 {
     float ex[K], ey[K], ez[K], rr[K];
-    const float q3 = 3.0f * q.w;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         ex[k] = q.x - xk[k].x;
@@ -278,10 +276,12 @@ __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4
         float wje = wq.x * ex[k];
         wje = __builtin_fmaf(wq.y, ey[k], wje);
         wje = __builtin_fmaf(wq.z, ez[k], wje);
-        const float c3 = __builtin_fmaf(q3, wke, m3[k] * wje);
-        // mn = -m_k, wk.w = -v_k here
-        const float e = HAS_V ? __builtin_fmaf(r2, c3, __builtin_fmaf(mn[k], wq.w, q.w * wk[k].w))
-                              : r2 * c3;
+        const float ce = __builtin_fmaf(q.w, wke, mn[k] * wje);
+        // mn = -m_k, wk.w = -v_k here.  The 3 goes to r^2, whose rounding differs
+        // from pair to pair: to the masses, a set of equal ones all rounded alike.
+        const float r23 = 3.0f * r2;
+        const float e = HAS_V ? __builtin_fmaf(r23, ce, __builtin_fmaf(mn[k], wq.w, q.w * wk[k].w))
+                              : r23 * ce;
         const float u = r3 * e;
         t.Cx = __builtin_fmaf(u, ex[k], t.Cx);
         t.Cy = __builtin_fmaf(u, ey[k], t.Cy);
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
         return v;
     };
     float4 xk[K], wk[K];
-    float m3[K], mn[K];  // -3 m_k, -m_k
+    float mn[K];  // -m_k
     RowAcc acc[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -322,7 +322,6 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
         wk[k] = weights(ic);
         wk[k].w = -wk[k].w;
         mn[k] = -xk[k].w;
-        m3[k] = 3.0f * mn[k];
         zero(acc[k]);
     }
     const int full = n >> 6;  // tiles without particles past n
@@ -338,7 +337,7 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
     const auto masked = [&](int t) {
         float4 a, b;
         load(t, a, b);
-        adj_row_tile<K, HAS_V, true>(xk, wk, m3, mn, a, b, eps2, t * 64 + lane, i0, n, acc);
+        adj_row_tile<K, HAS_V, true>(xk, wk, mn, a, b, eps2, t * 64 + lane, i0, n, acc);
     };
     // the tiles with pairs to leave out first, as in the forward kernel
     for (int t = self0; t <= self1; ++t)
@@ -349,7 +348,7 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
         for (int d = 0; d < D; ++d) {
             const int t = t0 + 4 * d;
             if (t < full && (t < self0 || t > self1))
-                adj_row_tile<K, HAS_V, false>(xk, wk, m3, mn, q[d], wq[d], eps2, 0, 0, 0, acc);
+                adj_row_tile<K, HAS_V, false>(xk, wk, mn, q[d], wq[d], eps2, 0, 0, 0, acc);
             load(t + 4 * D, q[d], wq[d]);
         }
     }
@@ -455,7 +454,7 @@ struct SymBwdArgs {
 // encoding).
 struct AdjRow {
     float x, y, z, m;      // position, mass
-    float mn, m3;          // -m, 3 m
+    float mn;              // -m
     float wx, wy, wz, v;   // weights
     float vn;              // -v
 };
@@ -463,13 +462,14 @@ struct AdjRow {
 // The first R rows (from row B on, in groups of four) of a lane against the
 // tile particle (q, wq), each pair met once, the rows' reciprocal square roots
 // as one group.  With e = x_j - x_k = -d:
-//     F = r^3 (c - t d) = r^3 (c + t e),  t = r^2 (3 m_k (w_j . e) - 3 m_j (w_k . e)) + b
+//     F = r^3 (c - t d) = r^3 (c + t e),  t = 3 r^2 (c . d) + b
+//     c . d = m_k (w_j . e) - m_j (w_k . e)
 // enters tk as +F and the slot ja as +F too, which the slots' readers negate,
 // as the j mass term r v_k + r^3 (w_k . d) = r v_k - r^3 (w_k . e): the slot
 // takes its opposite, r^3 (w_k . e) - r v_k.
 template <int K, bool HAS_V, int R = K, int B = 0>
 __device__ __forceinline__ void adj_pair_rows(const AdjRow (&row)[K], const float4 &q,
-                                              const float4 &wq, float q3n, float eps2,
+                                              const float4 &wq, float qn, float eps2,
                                               float4 (&tk)[K], float4 &ja)
 {
     constexpr int G = R < 4 ? R : 4;
@@ -497,11 +497,15 @@ __device__ __forceinline__ void adj_pair_rows(const AdjRow (&row)[K], const floa
         float wje = wq.x * ex[k];
         wje = __builtin_fmaf(wq.y, ey[k], wje);
         wje = __builtin_fmaf(wq.z, ez[k], wje);
-        const float c3 = __builtin_fmaf(q3n, wke, w.m3 * wje);
-        // without potential weights (v = 0) b vanishes and t = r^2 c3 exactly
-        // as the fused form with a zero addend
-        const float t = HAS_V ? __builtin_fmaf(r2, c3, __builtin_fmaf(w.m, wq.w, q.w * w.v))
-                              : r2 * c3;
+        const float cd = __builtin_fmaf(qn, wke, w.m * wje);
+        // The 3 goes to r^2, whose rounding differs from pair to pair: to the
+        // masses, a set of equal ones all rounded alike (10,600 bodies of one mass
+        // in a cube, eps2 0.01: dL/dx 1.2e-7 from float64, 0.7e-7 so).
+        // Without potential weights (v = 0) b vanishes and t is exactly the fused
+        // form with a zero addend.
+        const float r23 = 3.0f * r2;
+        const float t = HAS_V ? __builtin_fmaf(r23, cd, __builtin_fmaf(w.m, wq.w, q.w * w.v))
+                              : r23 * cd;
         const float ux = __builtin_fmaf(t, ex[k], __builtin_fmaf(q.w, w.wx, w.mn * wq.x));
         const float uy = __builtin_fmaf(t, ey[k], __builtin_fmaf(q.w, w.wy, w.mn * wq.y));
         const float uz = __builtin_fmaf(t, ez[k], __builtin_fmaf(q.w, w.wz, w.mn * wq.z));
@@ -518,7 +522,7 @@ __device__ __forceinline__ void adj_pair_rows(const AdjRow (&row)[K], const floa
     }
     if constexpr (R > 4) {
         __builtin_amdgcn_sched_barrier(0);
-        adj_pair_rows<K, HAS_V, R - 4, B + 4>(row, q, wq, q3n, eps2, tk, ja);
+        adj_pair_rows<K, HAS_V, R - 4, B + 4>(row, q, wq, qn, eps2, tk, ja);
     }
 }
 
@@ -600,13 +604,13 @@ __device__ __forceinline__ void adj_diag_steps(const AdjRow (&row)[K], const int
         if (any_once) ja = slot[jj];
         const float4 qn = tile_xm[(jj + 1) & 63];
         const float4 wqn = tile_wv[(jj + 1) & 63];
-        const float q3n = -3.0f * q.w;
+        const float nq = -q.w;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (a0 + k < t) {
                 const AdjRow one[1] = {row[k]};
                 float4 tk1[1] = {tk[k]};
-                adj_pair_rows<1, true>(one, q, wq, q3n, eps2, tk1, ja);
+                adj_pair_rows<1, true>(one, q, wq, nq, eps2, tk1, ja);
                 tk[k] = tk1[0];
             } else if (a0 + k == t) {
                 const AdjRow &w = row[k];
@@ -658,7 +662,7 @@ __device__ __forceinline__ void adj_ring_steps(const AdjRow (&row)[K], const flo
             float4 ja = sl[s];
             const float4 qn = txm[s + 1];
             const float4 wqn = twv[s + 1];
-            adj_pair_rows<K, HAS_V>(row, q, wq, -3.0f * q.w, eps2, tk, ja);
+            adj_pair_rows<K, HAS_V>(row, q, wq, -q.w, eps2, tk, ja);
             sl[s] = ja;
             q = qn;
             wq = wqn;
@@ -694,7 +698,7 @@ __device__ __forceinline__ void adj_diag_step(const AdjRow (&row)[K], const floa
         const float4 q = txm[s];
         const float4 wq = twv[s];
         float4 ja = sl[s];
-        adj_pair_rows<K, HAS_V, R>(row, q, wq, -3.0f * q.w, eps2, tk, ja);
+        adj_pair_rows<K, HAS_V, R>(row, q, wq, -q.w, eps2, tk, ja);
         sl[s] = ja;
     }
 }
@@ -797,7 +801,7 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
         float4 xm = make_float4(kBwdPadRow, kBwdPadRow, kBwdPadRow, 0.f);
         float4 wv4 = make_float4(0.f, 0.f, 0.f, 0.f);
         if (i < n) load_xw(A, i, xm, wv4);
-        row[k] = AdjRow{xm.x, xm.y, xm.z, xm.w, -xm.w, 3.0f * xm.w, wv4.x, wv4.y, wv4.z, wv4.w, -wv4.w};
+        row[k] = AdjRow{xm.x, xm.y, xm.z, xm.w, -xm.w, wv4.x, wv4.y, wv4.z, wv4.w, -wv4.w};
         acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 

@@ -31,12 +31,15 @@ FORWARD = [
     (1048576, "lognormal", "plummer", (3.816e-08, 2.979e-08)),
 ]
 ADJOINT = [
+    (8000, "equal", "cube", True, (7.234e-08, 2.239e-07)),
     (8000, "lognormal", "cube", False, (7.198e-08, 1.913e-07)),
     (8000, "lognormal", "plummer", True, (1.283e-07, 1.914e-07)),
+    (11000, "equal", "cube", True, (6.975e-08, 2.252e-07)),
     (11000, "lognormal", "cube", False, (6.619e-08, 1.883e-07)),
     (11000, "lognormal", "plummer", True, (1.161e-07, 1.904e-07)),
     (16384, "lognormal", "cube", False, (6.386e-08, 2.144e-07)),
     (16384, "lognormal", "plummer", True, (1.155e-07, 2.750e-07)),
+    (30000, "equal", "cube", True, (6.674e-08, 2.249e-07)),
     (50021, "lognormal", "cube", False, (4.992e-08, 1.829e-07)),
     (50021, "lognormal", "plummer", True, (8.171e-08, 2.842e-07)),
     (262144, "lognormal", "plummer", True, (6.459e-08, 2.989e-07)),
