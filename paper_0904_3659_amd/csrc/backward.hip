@@ -221,9 +221,12 @@ __global__ __launch_bounds__(BLOCK) void backward_kernel(BwdArgs P)
 // Row-group adjoint for small and middle n, as the forward's row groups: a
 // workgroup of four waves owns K rows (the same in every lane), wave w meets
 // the 64-particle tiles w, w + 4, ... with both its particles (x, m) and
-// their weights (w, v) loaded ahead, and gathers the row sums A, B, C, G;
-// eight sums per row are added by shared halvings and over the waves in
-// order.  One launch, no partials, bitwise reproducible.  HAS_V false: no
+// their weights (w, v) loaded ahead, and gathers the sums A, B, C, G.  Each
+// lane combines its own into dL/dx (w A and C are large next to their
+// difference where the field is smooth: combined after the sums over the lanes,
+// dL/dx of 5,000 bodies in a cube was 3 times as far from float64), and the
+// four sums per row are added by shared halvings, then in float64, and over the
+// waves in order.  One launch, no partials, bitwise reproducible.  HAS_V false: no
 // potential weights, whose terms are not formed (bitwise the result of zero
 // weights).
 //
@@ -245,8 +248,9 @@ constexpr int kBwdRowMax = 4;  // rows per group
 // itself, or past n, take r = 0.
 template <int K, bool HAS_V, bool MASKED>
 __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4 (&wk)[K],
-                                             const float (&mn)[K], float4 q, float4 wq, float eps2, int j, int i0, int n,
-                                             RowAcc (&acc)[K])
+                                             const float (&mn)[K], float4 q, float4 wq,
+                                             float eps2, int j, int i0, int n,
+                                             float4 (&bg)[K], float4 (&ca)[K])
 {
     float ex[K], ey[K], ez[K], rr[K];
 #pragma unroll
@@ -265,11 +269,11 @@ __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4
         const float r = rr[k];
         const float r2 = r * r;
         const float r3 = r * r2;
-        RowAcc &t = acc[k];
-        t.A = __builtin_fmaf(q.w, r3, t.A);
-        t.Bx = __builtin_fmaf(r3, wq.x, t.Bx);
-        t.By = __builtin_fmaf(r3, wq.y, t.By);
-        t.Bz = __builtin_fmaf(r3, wq.z, t.Bz);
+        float4 &b = bg[k], &c = ca[k];  // (B, G), (C, A)
+        c.w = __builtin_fmaf(q.w, r3, c.w);
+        b.x = __builtin_fmaf(r3, wq.x, b.x);
+        b.y = __builtin_fmaf(r3, wq.y, b.y);
+        b.z = __builtin_fmaf(r3, wq.z, b.z);
         float wke = wk[k].x * ex[k];
         wke = __builtin_fmaf(wk[k].y, ey[k], wke);
         wke = __builtin_fmaf(wk[k].z, ez[k], wke);
@@ -283,11 +287,11 @@ __device__ __forceinline__ void adj_row_tile(const float4 (&xk)[K], const float4
         const float e = HAS_V ? __builtin_fmaf(r23, ce, __builtin_fmaf(mn[k], wq.w, q.w * wk[k].w))
                               : r23 * ce;
         const float u = r3 * e;
-        t.Cx = __builtin_fmaf(u, ex[k], t.Cx);
-        t.Cy = __builtin_fmaf(u, ey[k], t.Cy);
-        t.Cz = __builtin_fmaf(u, ez[k], t.Cz);
-        if (HAS_V) t.G = __builtin_fmaf(r, wq.w, t.G);
-        t.G = __builtin_fmaf(r3, wje, t.G);
+        c.x = __builtin_fmaf(u, ex[k], c.x);
+        c.y = __builtin_fmaf(u, ey[k], c.y);
+        c.z = __builtin_fmaf(u, ez[k], c.z);
+        if (HAS_V) b.w = __builtin_fmaf(r, wq.w, b.w);
+        b.w = __builtin_fmaf(r3, wje, b.w);
     }
 }
 
@@ -296,7 +300,7 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
     typename std::conditional<EPI, BwdEpiArgs, BwdArgs>::type P)
 {
     constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
-    __shared__ float red[4][8 * K];
+    __shared__ double red[4][4 * K];
     const int n = P.n;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -314,15 +318,15 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
     };
     float4 xk[K], wk[K];
     float mn[K];  // -m_k
-    RowAcc acc[K];
+    float4 bg[K], ca[2][K];  // C and A of every second tile apart: half the chain
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        bg[k] = ca[0][k] = ca[1][k] = make_float4(0.f, 0.f, 0.f, 0.f);
         const unsigned ic = (unsigned)min(i0 + k, n - 1);  // rows past n are computed, not stored
         xk[k] = buffer_xm(bx, bm, ic);
         wk[k] = weights(ic);
         wk[k].w = -wk[k].w;
         mn[k] = -xk[k].w;
-        zero(acc[k]);
     }
     const int full = n >> 6;  // tiles without particles past n
     const int self0 = i0 >> 6, self1 = min(i0 + K - 1, n - 1) >> 6;
@@ -337,7 +341,8 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
     const auto masked = [&](int t) {
         float4 a, b;
         load(t, a, b);
-        adj_row_tile<K, HAS_V, true>(xk, wk, mn, a, b, eps2, t * 64 + lane, i0, n, acc);
+        adj_row_tile<K, HAS_V, true>(xk, wk, mn, a, b, eps2, t * 64 + lane, i0, n, bg,
+                                      ca[0]);
     };
     // the tiles with pairs to leave out first, as in the forward kernel
     for (int t = self0; t <= self1; ++t)
@@ -348,45 +353,46 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
         for (int d = 0; d < D; ++d) {
             const int t = t0 + 4 * d;
             if (t < full && (t < self0 || t > self1))
-                adj_row_tile<K, HAS_V, false>(xk, wk, mn, q[d], wq[d], eps2, 0, 0, 0, acc);
+                adj_row_tile<K, HAS_V, false>(xk, wk, mn, q[d], wq[d], eps2, 0, 0, 0, bg,
+                                               ca[d & 1]);
             load(t + 4 * D, q[d], wq[d]);
         }
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const float u[4] = {acc[k].A, acc[k].Bx, acc[k].By, acc[k].Bz};
-        const float v[4] = {acc[k].G, acc[k].Cx, acc[k].Cy, acc[k].Cz};
-        const float su = wave_sum4(u), sv = wave_sum4(v);
-        if ((lane & 15) == 0) {
-            red[wv][8 * k + quad_of_row(lane >> 4)] = su;
-            red[wv][8 * k + 4 + quad_of_row(lane >> 4)] = sv;
+        // dL/dx_k = w_k A - m_k B - C, lane by lane
+        float3 d[2];  // w A - C
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const float4 &f = ca[e][k];
+            d[e] = make_float3(__builtin_fmaf(wk[k].x, f.w, -f.x), __builtin_fmaf(wk[k].y, f.w, -f.y),
+                               __builtin_fmaf(wk[k].z, f.w, -f.z));
         }
+        const float v[4] = {__builtin_fmaf(mn[k], bg[k].x, d[0].x + d[1].x),
+                            __builtin_fmaf(mn[k], bg[k].y, d[0].y + d[1].y),
+                            __builtin_fmaf(mn[k], bg[k].z, d[0].z + d[1].z), bg[k].w};
+        const double s = wave_sum4(v);
+        if ((lane & 15) == 0) red[wv][4 * k + quad_of_row(lane >> 4)] = s;
     }
     __syncthreads();
     // thread 4 k + c stores component c of row i0 + k (c == 3: dL/dm)
     const int k = threadIdx.x >> 2, c = threadIdx.x & 3;
     const int i = i0 + k;
     if (k >= K || i >= n) return;
-    const auto total = [&](int e) {
-        float s = red[0][8 * k + e];
+    double sum = red[0][threadIdx.x];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) s += red[w][8 * k + e];
-        return s;
-    };
+    for (int w = 1; w < 4; ++w) sum += red[w][threadIdx.x];
+    const float g = (float)sum;
     if (c == 3) {
         if constexpr (EPI)
-            P.e.lm[i] = __builtin_fmaf(P.e.c, total(4), P.e.lm[i]);
+            P.e.lm[i] = __builtin_fmaf(P.e.c, g, P.e.lm[i]);
         else if (P.gm)
-            P.gm[i] = total(4);
-        return;
-    }
-    // dL/dx_k = w_k A - m_k B - C
-    const float w = P.ga ? P.ga[3 * (size_t)i + c] : 0.f;
-    const float g = w * total(0) - P.m[i] * total(1 + c) - total(5 + c);
-    if constexpr (EPI)
+            P.gm[i] = g;
+    } else if constexpr (EPI) {
         lf_coord(P.e, 3 * (size_t)i + c, g);
-    else
+    } else {
         P.gx[3 * (size_t)i + c] = g;
+    }
 }
 
 using RowFn = void (*)(const BwdArgs &, const LfEpi *, hipStream_t);

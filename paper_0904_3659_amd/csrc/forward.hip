@@ -333,8 +333,9 @@ __global__ __launch_bounds__(W * 64) void forward_la_kernel(LaArgs P)
 // waves owns K rows; their positions are the same for every lane, and the
 // lanes of wave w meet the j of the 64-particle tiles w, w + 4, w + 8, ...
 // for all K rows, D tiles loaded ahead.  The lane sums are added by halvings
-// that four sums share (wave_sum4), the four waves' sums in wave order
-// through LDS.  One launch, no partials, bitwise reproducible.
+// that four sums share (wave_sum4, in float64 from 16 lanes on), the four
+// waves' sums in wave order through LDS.  One launch, no partials, bitwise
+// reproducible.
 //
 // Bound by VALU issue: 14 operations per ordered pair, 41 cycles per 64 pairs
 // and SIMD at 16,384 bodies with K = 8 (36 if every pair of operations of two
@@ -397,7 +398,7 @@ __global__ __launch_bounds__(256) void forward_row_kernel(
     typename std::conditional<EPI, RowEpiArgs, RowArgs>::type P)
 {
     constexpr int D = K <= 2 ? 4 : 2;  // tiles loaded ahead
-    __shared__ float red[4][4 * K];
+    __shared__ double red[4][4 * K];
     const int n = P.n;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -444,16 +445,17 @@ __global__ __launch_bounds__(256) void forward_row_kernel(
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const float s = wave_sum4(acc[k]);
+        const double s = wave_sum4(acc[k]);
         if ((lane & 15) == 0) red[wv][4 * k + quad_of_row(lane >> 4)] = s;
     }
     __syncthreads();
     // thread 4 k + c stores component c of row i0 + k (c == 3: the potential)
     const int k = threadIdx.x >> 2, c = threadIdx.x & 3;
     if (k >= K || i0 + k >= n) return;
-    float s = red[0][threadIdx.x];
+    double sum = red[0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) s += red[w][threadIdx.x];
+    for (int w = 1; w < 4; ++w) sum += red[w][threadIdx.x];
+    const float s = (float)sum;
     if (c < 3) {
         if (!EPI || P.a) P.a[3 * (size_t)(i0 + k) + c] = s;
         if constexpr (EPI) lf_coord(P.e, 3 * (size_t)(i0 + k) + c, s);

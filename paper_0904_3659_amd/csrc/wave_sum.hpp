@@ -4,14 +4,18 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace nbody {
 
 // v plus v of the lane that DPP control CTRL names (all 64 lanes active).
 template <int CTRL>
-__device__ __forceinline__ float dpp_swap_add(float v)
+__device__ __forceinline__ double dpp_swap_add(double v)
 {
-    const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false);
-    return v + __builtin_bit_cast(float, o);
+    const auto b = __builtin_bit_cast(uint64_t, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return v + __builtin_bit_cast(double, (uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
 }
 
 // The other half of a pair of registers: lanes 32..63 of a and lanes 0..31 of
@@ -34,15 +38,18 @@ __device__ __forceinline__ float swap16_add(float a, float b)
 // Sums of four values over the 64 lanes, in a fixed order: row g of 16 lanes
 // ends with the total of v[quad_of_row(g)] in every lane (the same bits in each:
 // every step adds lane pairs that exchange values, and a + b rounds as b + a).
-// Call with all 64 lanes active.  Four values share
-// the first two halvings, so they take 9 cross-lane steps instead of 24.
-__device__ __forceinline__ float wave_sum4(const float (&v)[4])
+// Call with all 64 lanes active.  Four values share the first two halvings, so
+// they take 9 cross-lane steps instead of 24.  From the 16 sums of four lanes
+// on they are added in float64: a sum whose terms have one sign loses as much
+// to the roundings of the last few float32 levels as to its one rounding at
+// the end (p at 10,000 bodies, 2-norm: 4.2e-8 all in float32, 2.9e-8 so).
+__device__ __forceinline__ double wave_sum4(const float (&v)[4])
 {
-    float s = swap16_add(swap32_add(v[0], v[1]), swap32_add(v[2], v[3]));
-    s = dpp_swap_add<0xB1>(s);
-    s = dpp_swap_add<0x4E>(s);
-    s = dpp_swap_add<0x141>(s);
-    s = dpp_swap_add<0x140>(s);
+    double s = (double)swap16_add(swap32_add(v[0], v[1]), swap32_add(v[2], v[3]));
+    s = dpp_swap_add<0xB1>(s);   // quad_perm [1,0,3,2]: lane l ^ 1
+    s = dpp_swap_add<0x4E>(s);   // quad_perm [2,3,0,1]: lane l ^ 2
+    s = dpp_swap_add<0x141>(s);  // row_half_mirror: the other quad of 8 lanes
+    s = dpp_swap_add<0x140>(s);  // row_mirror: the other half of 16 lanes
     return s;
 }
 

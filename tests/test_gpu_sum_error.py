@@ -20,6 +20,10 @@ ROWS = 4096  # rows compared, evenly spaced
 # n, masses, positions(, potential weights), error of the plain form (vectors, scalars);
 # eps2 = 0.01
 FORWARD = [
+    (5003, "equal", "cube", (3.783e-08, 3.014e-08)),
+    (5003, "lognormal", "plummer", (4.643e-08, 2.997e-08)),
+    (10000, "equal", "cube", (3.504e-08, 2.755e-08)),
+    (10000, "lognormal", "plummer", (4.013e-08, 2.716e-08)),
     (12001, "equal", "cube", (3.488e-08, 2.737e-08)),
     (12001, "lognormal", "plummer", (3.964e-08, 2.661e-08)),
     (16384, "lognormal", "plummer", (3.809e-08, 2.584e-08)),
@@ -31,6 +35,12 @@ FORWARD = [
     (1048576, "lognormal", "plummer", (3.816e-08, 2.979e-08)),
 ]
 ADJOINT = [
+    (4501, "equal", "cube", True, (7.794e-08, 1.984e-07)),
+    (4501, "lognormal", "cube", False, (8.639e-08, 1.620e-07)),
+    (4501, "lognormal", "plummer", True, (1.420e-07, 1.975e-07)),
+    (6001, "equal", "cube", True, (7.465e-08, 2.116e-07)),
+    (6001, "lognormal", "cube", False, (8.012e-08, 1.838e-07)),
+    (6001, "lognormal", "plummer", True, (1.420e-07, 1.972e-07)),
     (8000, "equal", "cube", True, (7.234e-08, 2.239e-07)),
     (8000, "lognormal", "cube", False, (7.198e-08, 1.913e-07)),
     (8000, "lognormal", "plummer", True, (1.283e-07, 1.914e-07)),
