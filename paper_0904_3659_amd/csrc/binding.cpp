@@ -12,6 +12,7 @@
 
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cmath>
@@ -89,13 +90,17 @@ PyObject *pair_of(const at::Tensor &a, const at::Tensor &b)
 }
 
 // The result tensors of a call: those of `out` (None, or a tuple of a vector
-// array and a scalar array or None) or new ones.  False: not the common case.
-bool results(PyObject *out, int64_t n, bool scalar, const at::Tensor &like, at::Tensor *v,
+// array and a scalar array or None) or new ones, the scalar one if `scalar` is
+// true (looked at only here, as in nbody.py).  False: not the common case, or a
+// Python error is set.
+bool results(PyObject *out, int64_t n, PyObject *scalar, const at::Tensor &like, at::Tensor *v,
              at::Tensor *s)
 {
     if (out == Py_None) {
+        const int with = PyObject_IsTrue(scalar);
+        if (with < 0) return false;
         *v = at::empty({n, 3}, like.options().requires_grad(false));
-        if (scalar) *s = at::empty({n}, like.options().requires_grad(false));
+        if (with) *s = at::empty({n}, like.options().requires_grad(false));
         return true;
     }
     if (!PyTuple_CheckExact(out) || PyTuple_GET_SIZE(out) != 2) return false;
@@ -112,18 +117,21 @@ bool results(PyObject *out, int64_t n, bool scalar, const at::Tensor &like, at::
 
 float *data(const at::Tensor &t) { return t.defined() ? static_cast<float *>(t.data_ptr()) : nullptr; }
 
+// None for a call left to the Python code, or the Python error that is set.
+PyObject *declined()
+{
+    if (PyErr_Occurred()) return nullptr;
+    Py_RETURN_NONE;
+}
+
+// torch's C++ exceptions as the Python ones its own calls raise
+// (torch.OutOfMemoryError where an array cannot be had).
 template <class F>
 PyObject *guarded(F f)
 {
-    try {
-        return f();
-    } catch (const std::exception &e) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    } catch (...) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "C++ exception");
-        return nullptr;
-    }
+    HANDLE_TH_ERRORS
+    return f();
+    END_HANDLE_TH_ERRORS
 }
 
 // forces(x, m, eps2, out, potential, flags) -> (a, p or None), a status != 0,
@@ -138,7 +146,7 @@ PyObject *forces(PyObject *, PyObject *const *args, Py_ssize_t count)
         if (!m || !plain_eps2(args[2], &eps2)) Py_RETURN_NONE;
         const int64_t n = x->size(0);
         at::Tensor a, p;
-        if (!results(args[3], n, PyObject_IsTrue(args[4]) == 1, *x, &a, &p)) Py_RETURN_NONE;
+        if (!results(args[3], n, args[4], *x, &a, &p)) return declined();
         void *stream;
         if (!current_stream(x->get_device(), &stream)) return nullptr;
         const uint32_t flags = (uint32_t)PyLong_AsUnsignedLong(args[5]);
@@ -166,7 +174,7 @@ PyObject *backward(PyObject *, PyObject *const *args, Py_ssize_t count)
         const at::Tensor *gp = args[4] == Py_None ? &none : plain(args[4], n, 0);
         if (!ga || !gp) Py_RETURN_NONE;
         at::Tensor gx, gm;
-        if (!results(args[6], n, PyObject_IsTrue(args[5]) == 1, *x, &gx, &gm)) Py_RETURN_NONE;
+        if (!results(args[6], n, args[5], *x, &gx, &gm)) return declined();
         void *stream;
         if (!current_stream(x->get_device(), &stream)) return nullptr;
         float *px = data(*x), *pm = data(*m), *pga = data(*ga), *pgp = data(*gp);
