@@ -16,6 +16,7 @@ from __future__ import annotations
 import contextlib
 import ctypes
 import os
+import warnings
 
 import numpy as np
 import torch
@@ -99,20 +100,26 @@ def lib() -> ctypes.CDLL:
             getattr(L, f).restype = ctypes.c_int
         if L.nbody_abi_version() != ABI_VERSION:
             raise NBodyError(5, f"ABI version {L.nbody_abi_version()} != {ABI_VERSION}")
-        _LIB = L
         _bind_native(L)
+        _LIB = L
     return _LIB
 
 
 def _bind_native(L) -> None:
     """Hand the library's addresses to the native front.  With several devices
     a call may have to make its tensors' device current, which is left to the
-    Python path."""
+    Python path.  So is every call, with a warning, where the front does not
+    load (not built, or built for another torch)."""
     global _native, _fast_forces, _fast_backward
     _native = _fast_forces = _fast_backward = None
-    if _RAW_STREAM is None or torch.cuda.device_count() != 1 or not os.path.exists(_build.BINDING):
+    if _RAW_STREAM is None or torch.cuda.device_count() != 1:
         return
-    from . import _binding
+    try:
+        from . import _binding
+    except ImportError as e:
+        warnings.warn(f"the native front of forces and forces_backward does not load ({e}); "
+                      "the Python path serves their calls", RuntimeWarning, stacklevel=3)
+        return
     address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
     _binding.bind(address(L.nbody_forces_ex), address(L.nbody_forces_backward), _RAW_STREAM)
     _native, _fast_forces, _fast_backward = _binding, _binding.forces, _binding.backward
