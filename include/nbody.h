@@ -329,7 +329,8 @@ nbody_status nbody_set_variant(int kind, int index);
 /*
  * Time every variant of `kind` on each size in sizes[count] (synthetic
  * inputs in library workspace, HIP events on `stream`) and record the
- * fastest per size bucket in the in-process tuning table; if the
+ * fastest (of the single-system kinds the automatic choice, unless another
+ * takes 2% less) per size bucket in the in-process tuning table; if the
  * environment variable NBODY_TUNE_CACHE names a file, the table is also
  * written there as JSON and read back at load time.  Blocks the host until
  * the timing runs finish.  For NBODY_KIND_BATCHED each size is the number of
@@ -362,7 +363,8 @@ nbody_status nbody_autotune_batched(const int64_t *offsets, int64_t num_systems,
  * kernel fits blocks_per_cu workgroups per CU, and sets *timed (if not NULL)
  * to whether nbody_autotune would time the variant there with free_bytes
  * of free device memory.  The timer times a variant only if n lies in its
- * size band (the one-launch forward kernels stop at 2^16) and its workspace
+ * size band (the one-launch forward kernels stop at 2^16), it does not launch
+ * there what another timed variant does, and its workspace
  * fits the smaller of NBODY_TUNE_WORKSPACE_CAP bytes (environment; default
  * 2 GiB) and a quarter of the free memory; a variant whose allocation fails
  * while timing is skipped as well, and the workspace the timing grew on the

@@ -38,16 +38,19 @@ struct DeviceBuffers {
 };
 
 // Times run(v) for every v < count with timed(v), keeping the fastest in
-// *best (-1 if none ran).  A variant whose run fails for lack of memory is
+// *best (-1 if none ran): the default variant (-1: no such preference) unless
+// another takes 2% less, as the choice stands for a whole power of two of sizes
+// and a tie says nothing about the others.  A variant whose run fails for lack of memory is
 // skipped like one that is not timed; any other failure ends the timing.
 template <class Run, class Timed>
-nbody_status time_best(int count, hipStream_t stream, Run run, Timed timed, int *best)
+nbody_status time_best(int count, hipStream_t stream, Run run, Timed timed, int preferred,
+                       int *best)
 {
     Events ev;
     hipError_t e = hipEventCreate(&ev.a);
     if (e == hipSuccess) e = hipEventCreate(&ev.b);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
-    float best_ms = 0.f;
+    float best_ms = 0.f, preferred_ms = -1.f;
     *best = -1;
     int warm = -1;  // the first variant that is timed and runs
     for (int v = 0; v < count && warm < 0; ++v) {
@@ -90,11 +93,13 @@ nbody_status time_best(int count, hipStream_t stream, Run run, Timed timed, int 
             if (min_ms < 0.f || ms < min_ms) min_ms = ms;
             if (ms > 200.f) break;  // long runs: one timing is enough
         }
+        if (v == preferred) preferred_ms = min_ms;
         if (*best < 0 || min_ms < best_ms) {
             best_ms = min_ms;
             *best = v;
         }
     }
+    if (preferred_ms >= 0.f && best_ms > 0.98f * preferred_ms) *best = preferred;
     return NBODY_OK;
 }
 
@@ -114,7 +119,7 @@ nbody_status autotune_batched_run(const Device &dev, const int64_t *offsets, int
     begin_private_batched_plans();
     st = time_best(batched_variant_count(), stream, [&](int v) {
         return batched_run(v, dev, offsets, num_systems, x, m, eps2, a, p, stream);
-    }, [](int) { return true; }, &best);
+    }, [](int) { return true; }, -1, &best);
     end_private_batched_plans();
     if (st != NBODY_OK) return st;
     if (best < 0) return fail(NBODY_ERROR_OUT_OF_MEMORY, "no batched variant fits device memory");
@@ -144,7 +149,7 @@ nbody_status autotune_run(int kind, const Device &dev, const int64_t *sizes, int
             begin_private_batched_plans();  // plans of synthetic offsets: not kept
             st = time_best(batched_variant_count(), stream, [&](int v) {
                 return batched_run(v, dev, offsets.data(), systems, x, m, 1e-4f, a, p, stream);
-            }, [](int) { return true; }, &best);
+            }, [](int) { return true; }, -1, &best);
             end_private_batched_plans();
             if (st != NBODY_OK) return st;
             if (best < 0) return fail(NBODY_ERROR_OUT_OF_MEMORY, "no batched variant fits device memory");
@@ -171,7 +176,9 @@ nbody_status autotune_run(int kind, const Device &dev, const int64_t *sizes, int
                                                           : backward_plan_bytes(v, n, dev.num_cu, per_cu);
             const int64_t mx = kind == NBODY_KIND_FORWARD ? forward_variant_max_n(v)
                                                           : backward_variant_max_n(v);
-            admit[v] = tune_admissible(n, mx, ws, cap);
+            const bool alias = kind == NBODY_KIND_FORWARD ? forward_alias(v, n, dev.num_cu, per_cu)
+                                                          : backward_alias(v, n, dev.num_cu, per_cu);
+            admit[v] = !alias && tune_admissible(n, mx, ws, cap);
         }
         const auto timed = [&](int v) { return admit[v] != 0; };
         const size_t ws_before = workspace_size(dev, stream);
@@ -183,7 +190,7 @@ nbody_status autotune_run(int kind, const Device &dev, const int64_t *sizes, int
             if ((st = fill_synthetic(x, m, nullptr, nullptr, n, 11u, stream)) != NBODY_OK) return st;
             st = time_best(forward_variant_count(), stream, [&](int v) {
                 return forward_run(v, dev, x, m, n, 1e-4f, a, p, stream);
-            }, timed, &best);
+            }, timed, forward_default_variant(n), &best);
         } else {
             float *w, *vv, *gx, *gm;
             if ((st = buf.alloc(12 * (size_t)n, &w)) || (st = buf.alloc(4 * (size_t)n, &vv)) ||
@@ -192,7 +199,7 @@ nbody_status autotune_run(int kind, const Device &dev, const int64_t *sizes, int
             if ((st = fill_synthetic(x, m, w, vv, n, 13u, stream)) != NBODY_OK) return st;
             st = time_best(backward_variant_count(), stream, [&](int v) {
                 return backward_run(v, dev, x, m, n, 1e-4f, w, vv, gx, gm, stream);
-            }, timed, &best);
+            }, timed, backward_default_variant(n), &best);
         }
         const nbody_status trim = workspace_trim(dev, stream, ws_before);
         if (st != NBODY_OK) return st;

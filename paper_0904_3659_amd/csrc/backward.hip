@@ -1285,6 +1285,21 @@ int64_t backward_plan_bytes(int variant, int64_t n, int num_cu, int per_cu)
     return splits > 1 ? (int64_t)sizeof(float4) * splits * n : 0;
 }
 
+bool backward_alias(int variant, int64_t n, int num_cu, int per_cu)
+{
+    const int d = backward_default_variant(n);
+    const Variant &V = kVariants[variant], &D = kVariants[d];
+    if (n <= NBODY_MAX_N && backward_takes_rows(variant, (int)n) && backward_takes_rows(d, (int)n))
+        return n < kRowAliasBegin ? !V.row : variant != d;
+    // one-tile plans (run_backward_sym) of both
+    const auto two_row = [](const Variant &v) { return v.sym && v.sym_w == 1 && v.sym_k == 2; };
+    if (variant == d || !two_row(V) || !two_row(D) || n >= kOneTileEnd) return false;
+    SymPlan pl, one;
+    return sym_plan(n, sym_block(V), (int64_t)per_cu * num_cu * V.sym_rounds, V.sym_occ,
+                    sym_workspace_budget(n), &pl) &&
+           one_tile_plan(n, n >= kOneTileBegin ? 4 : 2, pl, &one);
+}
+
 int64_t backward_variant_max_n(int variant)
 {
     if (variant < 0 || variant >= kNumVariants) return -1;

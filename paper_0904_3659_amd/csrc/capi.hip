@@ -816,19 +816,23 @@ int64_t nbody_variant_plan(int kind, int index, int64_t n, int num_cu, int block
     clear_error();
     if (timed) *timed = 0;
     int64_t bytes = -1, max_n = -1;
+    bool alias = false;
     if (kind == NBODY_KIND_FORWARD) {
         bytes = forward_plan_bytes(index, n, num_cu, blocks_per_cu);
         max_n = forward_variant_max_n(index);
+        alias = bytes >= 0 && forward_alias(index, n, num_cu, blocks_per_cu);
     } else if (kind == NBODY_KIND_BACKWARD) {
         bytes = backward_plan_bytes(index, n, num_cu, blocks_per_cu);
         max_n = backward_variant_max_n(index);
+        alias = bytes >= 0 && backward_alias(index, n, num_cu, blocks_per_cu);
     }
     if (bytes < 0 || free_bytes < 0) {
         fail(NBODY_ERROR_INVALID_ARGUMENT, "no plan for kind %d variant %d at n = %lld", kind, index,
              (long long)n);
         return -1;
     }
-    if (timed) *timed = tune_admissible(n, max_n, bytes, tune_workspace_cap((size_t)free_bytes));
+    if (timed)
+        *timed = !alias && tune_admissible(n, max_n, bytes, tune_workspace_cap((size_t)free_bytes));
     return bytes;
 }
 

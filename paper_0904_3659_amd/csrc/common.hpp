@@ -113,13 +113,24 @@ nbody_status forward_rows_run(int least, const char *name, const Device &dev, co
 bool forward_takes_rows(int variant, int n);
 bool backward_takes_rows(int variant, int n);
 
+// Whether the variant timer passes a variant by at n, because it launches there
+// what another one that is timed does, which chooses better over the rest of the
+// power of two that a choice is recorded for.
+bool forward_alias(int variant, int64_t n, int num_cu, int per_cu);
+bool backward_alias(int variant, int64_t n, int num_cu, int per_cu);
+// Of the variants that run row groups at n: below this size the row variants are
+// timed, from it on the default (a pair-once variant, which leaves the row groups
+// at the right size by itself).
+constexpr int kRowAliasBegin = 4096;
+
 // Sizes at which the one-wave two-row pair-once variants run the row-group
 // kernel instead: the pair-once grid is then one underfilled round of
 // workgroups and a fold of 4-5 us follows it.  Calls with the potential, pair-
 // once (a tile per wave) against row groups: 22.9 / 21.5 us at 8,000 bodies,
 // 26.9 / 26.7 at 9,000, 34.3 / 32.3 at 10,000, 35.3 / 39.1 at 11,000.  Below 4,500
-// the default variants are row groups by themselves.
-constexpr int kRowBandBegin = 4500, kRowBandEnd = 10500;
+// the default variants are row groups by themselves; the band begins at the power
+// of two below, over which a choice of the variant timer holds.
+constexpr int kRowBandBegin = 4096, kRowBandEnd = 10500;
 inline bool row_band(int n) { return n >= kRowBandBegin && n < kRowBandEnd; }
 
 // Rows per group K (a multiple of `least`, at most `most`) for n rows on

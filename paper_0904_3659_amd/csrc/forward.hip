@@ -694,6 +694,28 @@ int64_t forward_plan_bytes(int variant, int64_t n, int num_cu, int per_cu)
     return splits > 1 ? entry * splits * n : 0;
 }
 
+// Whether a variant with blocks that one-tile plans replace gets one at n.
+static bool takes_one_tile(const Variant &V, int64_t n, int num_cu, int per_cu)
+{
+    if (!(V.sym_w == 1 || (V.sym_w == 4 && V.sym_k == 4)) || n < kOneTileBegin || n >= kOneTileEnd)
+        return false;
+    SymPlan pl, one;
+    return sym_plan(n, V.sym_w * 64 * V.sym_k, (int64_t)per_cu * num_cu * V.sym_rounds, V.sym_occ,
+                    sym_workspace_budget(n), &pl) &&
+           one_tile_plan(n, 4, pl, &one);
+}
+
+bool forward_alias(int variant, int64_t n, int num_cu, int per_cu)
+{
+    const int d = forward_default_variant(n);
+    const Variant &V = kVariants[variant], &D = kVariants[d];
+    if (n <= NBODY_MAX_N && forward_takes_rows(variant, (int)n) && forward_takes_rows(d, (int)n))
+        return n < kRowAliasBegin ? !V.row : variant != d;
+    // (the default's plan holds its one-tile plan throughout that range)
+    return variant != d && V.sym_w && D.sym_w && V.sym_k == D.sym_k &&
+           (D.sym_w == 1 || (D.sym_w == 4 && D.sym_k == 4)) && takes_one_tile(V, n, num_cu, per_cu);
+}
+
 int64_t forward_variant_max_n(int variant)
 {
     if (variant < 0 || variant >= kNumVariants) return -1;
