@@ -186,8 +186,9 @@ nbody_status forward_sym_run(int W, int K, int occ, int rounds, const char *name
         // four (the two take turns in groups of four, so three waves per SIMD
         // still fit).  Sustained calls: 8 x 4 as 4 x 8 220.1 -> 212.5 ms at 2^20
         // bodies; 4 x 4 as 2 x 8 874 -> 860 us at 65,536, 1975 -> 1947 at
-        // 100,000, but 358 -> 363 at 40,000, where the workgroups are too few.
-        if (W == 4 && K == 4 && occ == 1 && n >= 50000) return run_sym<4, 4, 1, 8, 2, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
+        // 100,000, but 358 -> 363 at 40,000, where the workgroups are too few.  Below
+        // kOneTileEnd a tile per wave is level or ahead (run_sym).
+        if (W == 4 && K == 4 && occ == 1 && n >= kOneTileEnd) return run_sym<4, 4, 1, 8, 2, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         if (W == 4 && K == 4 && occ == 1) return run_sym<4, 4, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         if (W == 8 && K == 4 && occ == 1) return run_sym<8, 4, 1, 8, 4, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         return fail(NBODY_ERROR_INTERNAL, "no pair-once forward kernel for W=%d K=%d occ=%d rounds=%d", W, K, occ, rounds);

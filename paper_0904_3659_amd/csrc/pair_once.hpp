@@ -257,9 +257,11 @@ inline bool one_tile_plan(int64_t n, int K, const SymPlan &pl, SymPlan *out)
     *out = t;
     return true;
 }
-// Below kOneTileBegin (and kOneTileEnd on) the blocks of 256 particles these
-// plans have are too few (too many): see the same places.
-constexpr int kOneTileBegin = 10500, kOneTileEnd = 50000;
+// Below kOneTileBegin the blocks of 256 particles these plans have are too few: see
+// the same places.  They end where the plan of the forward's 4-wave four-row
+// blocks ends: at M = 49 of its blocks it has 167 + 24 slots, and a tile per wave
+// takes 195.
+constexpr int kOneTileBegin = 10500, kOneTileEnd = 48 * 1024 + 1;
 
 // Library workspace allowed for one pair-once evaluation of n particles
 // (partials and running sum) before the ring is split into more groups:

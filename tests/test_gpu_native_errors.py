@@ -26,7 +26,7 @@ def nb(request, monkeypatch):
 
 def test_out_of_memory(nb):
     dev = need_gpu()
-    n = 1 << 20
+    n = 1 << 22  # results larger than what a cached segment of the inputs has left
     x, m = to_dev(inputs.uniform_cube(n, (96, 0)), dev), to_dev(inputs.equal_masses(n), dev)
     torch.cuda.empty_cache()
     torch.cuda.set_per_process_memory_fraction(1e-9)  # torch's own limit: no new block

@@ -45,3 +45,19 @@ def test_row_variants_below(L, kind, n, rows):  # noqa: F811
     (1, 20000, 8, {"bwd_sym_s2_k2_r8", "bwd_sym_s2_k2_r16", "bwd_sym_w1_k2_r8", "bwd_sym_w1_k2_r16"})])
 def test_one_tile_plans_once(L, kind, n, per_cu, same):  # noqa: F811
     assert timed(L, kind, n, per_cu) & same == {default(L, kind, n)}
+
+
+@pytest.mark.parametrize("per_cu", [4])
+def test_default_plan_holds_a_tile_per_wave_over_its_range(L, per_cu):  # noqa: F811
+    # 40,000 bodies to the end of the range: the slots of the 4-wave blocks' plan
+    # against those of blocks of 256, four tiles to a workgroup
+    def fits(n):
+        M = -(-n // 256)
+        need = (4 * (M // 2 + 1) + 3) // 4 + M // 2
+        return need <= plan(L, 0, "fwd_sym_w4_k4_r8", n, per_cu)[0] // (16 * n)
+
+    assert default(L, 0, 40000) == default(L, 0, 49999) == "fwd_sym_w4_k4_r8"
+    assert all(fits(n) for n in range(40000, 49153, 31)) and fits(49152)
+    # the timer's view of the same line: another name of that launch, then not
+    assert plan(L, 0, "fwd_sym_w1_k4_r8", 49152, 16)[1] == 0
+    assert plan(L, 0, "fwd_sym_w1_k4_r8", 49153, 16)[1] == 1
