@@ -213,13 +213,15 @@ inline void sym_group(const SymPlan &pl, int g, int *d_lo, int *d_hi)
 // First tile of chunk c of the C chunks a block's U tiles are cut into (c == C:
 // U).  Every chunk has one tile; the other U - C are dealt in equal shares to
 // the first half of the chunks and in shares falling linearly to nothing over
-// the second half.  The grid runs chunk-major (all blocks' first chunks, then
-// all second ones, ...), so a launch ends on its smallest workgroups instead
-// of on equal ones, and no workgroup's running sums span more than 4/3 of the
-// mean chunk.  With C equal chunks of 1/8 of a slot's share, the last of eight
-// rounds left CUs idle for 5-12% of the launch (65,536 and 2^18 bodies, 92 and
-// 87% CU-busy).
-__device__ __forceinline__ int chunk_begin(int U, int C, int c)
+// the second half, what is left of a tile to the later chunk (with fewer than two
+// tiles to a chunk the last one may so be among the longer ones; up to the
+// earlier chunk it took 0.7% longer at 65,536 bodies, level at 50,021 and from
+// 100,000).  The grid runs chunk-major (all blocks' first chunks, then all second
+// ones, ...), so a launch ends on its smaller workgroups instead of on equal
+// ones; no chunk has more than 2 + 4/3 (U - C) / C tiles.  With C equal chunks of
+// 1/8 of a slot's share, the last of eight rounds left CUs idle for 5-12% of the
+// launch (65,536 and 2^18 bodies, 92 and 87% CU-busy).
+__host__ __device__ __forceinline__ int chunk_begin(int U, int C, int c)
 {
     if (U <= C) return c < U ? c : U;
     if (c == C) return U;
@@ -228,12 +230,12 @@ __device__ __forceinline__ int chunk_begin(int U, int C, int c)
     return c + (int)((float)(U - C) * (4.0f / 3.0f) * (x - t * t));
 }
 
-// Tiles of the longest chunk of a plan whose blocks hold TPB tiles (its first
-// group's first, rounded up).
+// Tiles a chunk of a plan whose blocks hold TPB tiles may have (chunk_begin's bound,
+// in the first group).
 inline int longest_chunk(const SymPlan &pl, int TPB)
 {
     const int U = (pl.G + 1) * TPB;
-    return U <= pl.C ? 1 : 2 + (int)((4LL * (U - pl.C) + 3LL * pl.C - 1) / (3LL * pl.C));
+    return U <= pl.C ? 1 : 2 + (int)(4LL * (U - pl.C) / (3LL * pl.C));
 }
 
 // Waves that share a one-wave block's chunk: the chunk partials of one-wave
