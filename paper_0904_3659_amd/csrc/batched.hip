@@ -158,7 +158,9 @@ __global__ __launch_bounds__(kTileSplit * 64) void batched_sym_dyn_kernel(BatSym
     __shared__ float4 lds[T * kWaveLds];  // per wave: the tile, then its slots
     __shared__ int s_idx;
     for (;;) {
-        __syncthreads();  // every thread has read the previous ticket
+        // every thread has read the previous ticket, and every wave the others'
+        // row sums of the previous unit (pair_once_block, T > 1)
+        __syncthreads();
         if (threadIdx.x == 0) s_idx = atomicAdd(ctr, 1);
         __syncthreads();
         const int idx = s_idx;

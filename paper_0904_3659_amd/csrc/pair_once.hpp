@@ -623,8 +623,11 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 // One workgroup of W*64 lanes evaluates chunk c of block I.  x, m and
 // partial are the system's own arrays (offsets already applied).  tile
 // (kSymBuffers<W> tiles) and jacc (kSymBuffers<W> sets of W slot arrays) are
-// the workgroup's LDS buffers.  Starts with a workgroup barrier, so the LDS
-// buffers may be reused by consecutive calls.
+// the workgroup's LDS buffers.  Blocks of several waves start with a workgroup
+// barrier, so their LDS buffers may be reused by consecutive calls; one-wave
+// blocks (T == 1) need none.  With T > 1 there is no barrier after the last reads
+// of other waves' regions: a caller puts one between two calls (the ticket loop
+// of batched_sym_dyn_kernel has it).
 //
 // Diagonal tiles are pair-once too (for W <= 8; larger blocks meet them as
 // masked ordered pairs): the rows of lane-slot k of wave wv form
@@ -795,8 +798,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     }
     while (u < u1) {
         if (NB == 1) {
-            // the previous tile and its slot sums are done (the LDS buffers
-            // free on entry: callers may loop over blocks)
+            // the previous tile and its slot sums are done
             block_sync();
             stage(0);
             clear_slots(0);
