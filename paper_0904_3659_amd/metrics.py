@@ -19,6 +19,8 @@ units did.
 
 from __future__ import annotations
 
+import math
+
 import numpy as np
 
 FLOP_PER_PAIR = 38
@@ -42,15 +44,26 @@ def pairs_ensemble(sizes) -> int:
     return int(np.sum(s * np.maximum(s - 1, 0)))
 
 
-def is_pair_once(variant: str) -> bool:
-    """Whether a kernel variant evaluates each unordered pair once (away from
-    the small sizes at which it runs as row groups, every ordered pair)."""
+# Sizes [from, to) at which pair-once variants run row groups, every ordered pair.
+ROW_GROUPS = {"fwd_sym_w1_k2_": (4096, 10500), "bwd_sym_s2_k2_": (4000, 6200)}
+
+
+def is_pair_once(variant: str, n: int | None = None) -> bool:
+    """Whether a kernel variant evaluates each unordered pair once, at n
+    particles of a single system if n is given."""
+    if n is not None:
+        for prefix, (lo, hi) in ROW_GROUPS.items():
+            if variant.startswith(prefix) and lo <= n < hi:
+                return False
     return variant.startswith(("fwd_sym", "bwd_sym", "bat_sym"))
 
 
 def evaluated_pairs(ordered_pairs: int, variant: str) -> int:
-    """Interactions a variant evaluates to deliver ``ordered_pairs`` terms."""
-    return ordered_pairs // 2 if is_pair_once(variant) else ordered_pairs
+    """Interactions a variant evaluates to deliver ``ordered_pairs`` terms (of one
+    system, unless the variant is a batched one)."""
+    ordered_pairs = int(ordered_pairs)
+    n = (1 + math.isqrt(1 + 4 * ordered_pairs)) // 2  # n (n - 1) = ordered pairs
+    return ordered_pairs // 2 if is_pair_once(variant, n) else ordered_pairs
 
 
 def gflops(pair_count: float, seconds: float, flop_per_pair: float = FLOP_PER_PAIR) -> float:
