@@ -105,9 +105,9 @@ const char *nbody_last_error(void);
  * Outside that range the default evaluates every ordered pair: below 10,500
  * in one launch of row groups (a workgroup of four waves owns 1 to 8 rows,
  * its lanes splitting j, their sums added in a fixed order in registers and
- * LDS; no partial sums.  From 4,500 bodies that is the small-n form of the
- * pair-once variants of one-wave two-row blocks, and keeps the workspace of
- * their plan); above 2^24 gathered per row with j-splits, float64 row sums
+ * LDS; no workspace.  From 4,500 bodies that is the small-n form of the
+ * pair-once variants of one-wave two-row blocks, refused where their plan
+ * would be); above 2^24 gathered per row with j-splits, float64 row sums
  * (as NBODY_FORCES_F64_SUM below) and a reduction launch (at most
  * 32 n * splits bytes).
  * Positions must be finite with magnitude below 1e17 (padding slots sit
@@ -195,8 +195,8 @@ nbody_status nbody_forces_ex(const float *x, const float *m, int64_t n, float ep
  * does not form the potential-weight terms (with the same variant, bitwise
  * the result of zero weights); the default variant is the same.  Below 6,200 one
  * launch of row groups (as the forward's, 1 to 4 rows each) evaluates every
- * ordered pair (from 4,000 as the small-n form of a pair-once
- * variant, with the workspace of its plan); above 2^24 every ordered pair is gathered
+ * ordered pair (no workspace; from 4,000 as the small-n form of a pair-once
+ * variant, refused where its plan would be); above 2^24 every ordered pair is gathered
  * per row.
  */
 nbody_status nbody_forces_backward(const float *x, const float *m, int64_t n, float eps2,

@@ -1072,6 +1072,14 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
 {
     static_assert(KW * KK == W * K, "the same block");
     constexpr int PB = W * 64 * K;
+    if constexpr (SMALL) {
+        if (bwd_row_band(n)) {
+            const nbody_status st = rows_for_plan(name, dev, n, stream, arena);
+            return st != NBODY_OK ? st
+                                  : backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm,
+                                                      stream, epi, fused);
+        }
+    }
     int per_cu = 0;
     nbody_status st = SMALL ? adj_occupancy_half(&per_cu) : adj_occupancy<W, K>(&per_cu);
     if (st != NBODY_OK) return st;
@@ -1084,10 +1092,6 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     void *ws = nullptr;
     st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
-    if constexpr (SMALL)
-        // the plan and its workspace stay the variant's, whichever kernel runs
-        if (bwd_row_band(n))
-            return backward_rows_run(1, name, dev, x, m, n, eps2, ga, gp, gx, gm, stream, epi, fused);
     if constexpr (KW == 1 && KK == 2) {
         SymPlan one;
         if (n >= kOneTileBegin && n < kOneTileEnd && one_tile_plan(n, 4, pl, &one))
@@ -1273,6 +1277,7 @@ int64_t backward_plan_bytes(int variant, int64_t n, int num_cu, int per_cu)
     if (n == 0) return 0;
     const Variant &V = kVariants[variant];
     if (V.row) return 0;
+    if (V.sym_small && bwd_row_band((int)n)) return rows_refused(n, sym_workspace_budget(n)) ? -1 : 0;
     if (V.sym) {
         SymPlan pl;
         if (!sym_plan(n, sym_block(V), (int64_t)per_cu * num_cu * V.sym_rounds, V.sym_occ,

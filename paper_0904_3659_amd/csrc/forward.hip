@@ -682,6 +682,8 @@ int64_t forward_plan_bytes(int variant, int64_t n, int num_cu, int per_cu)
         la_geometry(V, (int)n, num_cu, &splits, &chunk);
         return splits > 1 ? (int64_t)sizeof(float4) * splits * n : 0;
     }
+    if (V.sym_w == 1 && V.sym_k == 2 && row_band((int)n))
+        return rows_refused(n, sym_workspace_budget(n)) ? -1 : 0;
     if (V.sym_w) {
         SymPlan pl;
         if (!sym_plan(n, V.sym_w * 64 * V.sym_k, (int64_t)per_cu * num_cu * V.sym_rounds, V.sym_occ,

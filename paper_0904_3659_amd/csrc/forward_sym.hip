@@ -111,6 +111,14 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
 {
     static_assert(KW * KK == W * K, "the same block");
     constexpr int PB = W * 64 * K;
+    if constexpr (W == 1 && K == 2) {
+        if (row_band(n)) {
+            // refused where the plan of many ring offsets would be; no workspace
+            const nbody_status st = rows_for_plan(name, dev, n, stream, arena);
+            return st != NBODY_OK ? st
+                                  : forward_rows_run(1, name, dev, x, m, n, eps2, a, p, stream, epi, fused);
+        }
+    }
     int per_cu = 0;
     // sized by the kernel that forms the potential, also when p is not
     // stored: the same plan keeps a bitwise the same either way
@@ -125,10 +133,6 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     void *ws = nullptr;
     st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
-    if constexpr (W == 1 && K == 2)
-        // the plan and its workspace stay the variant's, whichever kernel runs
-        if (row_band(n))
-            return forward_rows_run(1, name, dev, x, m, n, eps2, a, p, stream, epi, fused);
     // A tile per one-wave block of 256 particles.  Calls with the potential, row
     // groups (below 12,000) or planned chunks of 2-4 tiles / a tile per wave:
     // 32.3 / 34.3 us at 10,000 bodies, 39.1 / 35.3 at 11,000, 50.7 / 47.9 at

@@ -280,6 +280,24 @@ inline size_t sym_workspace_budget(int64_t n)
     return slots16 > ((size_t)1 << 30) ? slots16 : ((size_t)1 << 30);
 }
 
+// Row groups that stand in for blocks of 128 particles (more ring offsets than
+// slots that fit any small budget): refused exactly where sym_plan refuses, so that
+// a workspace limit means the same at every size of a variant, ...
+inline bool rows_refused(int64_t n, size_t budget) { return budget / (16 * (size_t)n) < 4; }
+
+// ... though they take no workspace: asked for none, an arena still reports an
+// injected allocation fault.
+inline nbody_status rows_for_plan(const char *name, const Device &dev, int n, hipStream_t stream,
+                                  const Arena &arena)
+{
+    const size_t budget = arena.budget(sym_workspace_budget(n));
+    if (rows_refused(n, budget))
+        return fail(NBODY_ERROR_INVALID_ARGUMENT,
+                    "n = %d needs more than the %zu-byte workspace limit of %s", n, budget, name);
+    void *none = nullptr;
+    return arena.get(dev, stream, 0, &none);
+}
+
 // Number of tiles of block I in ring group [d_lo, d_hi): the TPB diagonal
 // tiles when d_lo == 0, then TPB tiles per ring delta the block meets.
 __host__ __device__ __forceinline__ int group_tiles(int I, int M, int d_lo, int d_hi, int TPB)

@@ -61,3 +61,13 @@ def test_default_plan_holds_a_tile_per_wave_over_its_range(L, per_cu):  # noqa: 
     # the timer's view of the same line: another name of that launch, then not
     assert plan(L, 0, "fwd_sym_w1_k4_r8", 49152, 16)[1] == 0
     assert plan(L, 0, "fwd_sym_w1_k4_r8", 49153, 16)[1] == 1
+
+
+@pytest.mark.parametrize("kind,variant,n", [(0, "fwd_sym_w1_k2_o1", 4096), (0, "fwd_sym_w1_k2_r8", 10499),
+                                            (1, "bwd_sym_s2_k2_r8", 4000), (1, "bwd_sym_s2_k2_r16", 6199)])
+def test_row_groups_take_no_workspace(L, kind, variant, n, monkeypatch):  # noqa: F811
+    assert plan(L, kind, variant, n, 8)[0] == 0
+    monkeypatch.setenv("NBODY_SYM_WORKSPACE", str(16 * n * 4))
+    assert plan(L, kind, variant, n, 8)[0] == 0
+    monkeypatch.setenv("NBODY_SYM_WORKSPACE", str(16 * n * 4 - 1))  # as the plan's own limit
+    assert plan(L, kind, variant, n, 8)[0] == -1
