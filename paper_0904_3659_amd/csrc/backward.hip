@@ -764,14 +764,13 @@ constexpr int kAdjSplit = W == 1 ? kTileSplit : 1;
 template <int W>
 constexpr int kAdjThreads = 64 * W * kAdjSplit<W>;
 
-template <int W, int K, bool HAS_V>
+template <int W, int K, bool HAS_V, bool HELD = W != 1>
 __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void backward_sym_kernel(SymBwdArgs A)
 {
     constexpr int PB = W * 64 * K;
     constexpr int TPB = PB / 64;
     constexpr int NB = kSymBuffers<W>;
     constexpr int T = kAdjSplit<W>;
-    constexpr bool HELD = T == 1;
     static_assert(K * 64 <= kTileLds + kTileLds + kSlotLds, "row sums fit a wave's region");
     // per set of W waves: the tile twice over, its weights, the W slot arrays
     constexpr int kLds = NB * (2 * kTileLds + W * kSlotLds);
@@ -1009,7 +1008,7 @@ nbody_status backward_rows_run(int least, const char *name, const Device &dev, c
 }
 
 // The launches of a plan whose blocks are KW waves x KK rows.
-template <int W, int K>
+template <int W, int K, bool HELD = W != 1>
 nbody_status launch_backward_sym(const SymPlan &pl, void *ws, const char *name, const float *x,
                                  const float *m, int n, float eps2, const float *ga,
                                  const float *gp, float *gx, float *gm, hipStream_t stream,
@@ -1027,10 +1026,10 @@ nbody_status launch_backward_sym(const SymPlan &pl, void *ws, const char *name, 
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (gp)
-            hipLaunchKernelGGL((backward_sym_kernel<W, K, true>), dim3(pl.M * C),
+            hipLaunchKernelGGL((backward_sym_kernel<W, K, true, HELD>), dim3(pl.M * C),
                                dim3(kAdjThreads<W>), 0, stream, A);
         else
-            hipLaunchKernelGGL((backward_sym_kernel<W, K, false>), dim3(pl.M * C),
+            hipLaunchKernelGGL((backward_sym_kernel<W, K, false, HELD>), dim3(pl.M * C),
                                dim3(kAdjThreads<W>), 0, stream, A);
         prof_mark(stream, 1);
         nbody_status st = check_launch(name);
@@ -1106,7 +1105,13 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     // row).  As planned / 76 / 52 / 44: 647 / 641 / 633 / 640 us at 40,000 bodies
     // (104 planned), 867 / 858 / 845 / 849 at 47,000, 975 / 971 / 959 / 959 at
     // 50,021, 1616 / 1611 / 1604 / 1607 at 65,536.
-    if (KW == 2 && KK == 4 && ROUNDS > 1 && pl.C > 52) pl.C = 52;
+    if constexpr (KW == 2 && KK == 4 && ROUNDS > 1) {
+        if (pl.C > 52) pl.C = 52;
+        // short chunks (up to some 90,000 bodies) hand nothing over in between
+        if (longest_chunk(pl, KW * KK) <= kHeldTiles)
+            return launch_backward_sym<KW, KK, false>(pl, ws, name, x, m, n, eps2, ga, gp, gx, gm,
+                                                      stream, epi, fused);
+    }
     return launch_backward_sym<KW, KK>(pl, ws, name, x, m, n, eps2, ga, gp, gx, gm, stream, epi,
                                        fused);
 }

@@ -158,7 +158,9 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
             return launch_sym<KW, KK, (KK > K), false>(pl, ws, name, x, m, n, eps2, a, p, stream, epi,
                                                        fused);
     }
-    return launch_sym<KW, KK, (KK > K)>(pl, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
+    // (4-wave eight-row blocks, of 2^20 bodies and more: their chunks are so long that
+    // handing over alone takes more off the error than longer slot chains add)
+    return launch_sym<KW, KK, (KK > K && KW < 4)>(pl, ws, name, x, m, n, eps2, a, p, stream, epi, fused);
 }
 
 }  // namespace
