@@ -358,6 +358,7 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
             load(t + 4 * D, q[d], wq[d]);
         }
     }
+    float sums[K][4];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         // dL/dx_k = w_k A - m_k B - C, lane by lane
@@ -368,12 +369,12 @@ __global__ __launch_bounds__(256) void backward_row_kernel(
             d[e] = make_float3(__builtin_fmaf(wk[k].x, f.w, -f.x), __builtin_fmaf(wk[k].y, f.w, -f.y),
                                __builtin_fmaf(wk[k].z, f.w, -f.z));
         }
-        const float v[4] = {__builtin_fmaf(mn[k], bg[k].x, d[0].x + d[1].x),
-                            __builtin_fmaf(mn[k], bg[k].y, d[0].y + d[1].y),
-                            __builtin_fmaf(mn[k], bg[k].z, d[0].z + d[1].z), bg[k].w};
-        const double s = wave_sum4(v);
-        if ((lane & 15) == 0) red[wv][4 * k + quad_of_row(lane >> 4)] = s;
+        sums[k][0] = __builtin_fmaf(mn[k], bg[k].x, d[0].x + d[1].x);
+        sums[k][1] = __builtin_fmaf(mn[k], bg[k].y, d[0].y + d[1].y);
+        sums[k][2] = __builtin_fmaf(mn[k], bg[k].z, d[0].z + d[1].z);
+        sums[k][3] = bg[k].w;
     }
+    wave_sums<K>(sums, lane, [&](int k, double s) { red[wv][4 * k + quad_of_row(lane >> 4)] = s; });
     __syncthreads();
     // thread 4 k + c stores component c of row i0 + k (c == 3: dL/dm)
     const int k = threadIdx.x >> 2, c = threadIdx.x & 3;

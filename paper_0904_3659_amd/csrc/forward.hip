@@ -333,7 +333,8 @@ __global__ __launch_bounds__(W * 64) void forward_la_kernel(LaArgs P)
 // waves owns K rows; their positions are the same for every lane, and the
 // lanes of wave w meet the j of the 64-particle tiles w, w + 4, w + 8, ...
 // for all K rows, D tiles loaded ahead.  The lane sums are added by halvings
-// that four sums share (wave_sum4, in float64 from 16 lanes on), the four
+// that several sums share (wave_sums, in float64 from the sums of four or eight
+// lanes on), the four
 // waves' sums in wave order through LDS.  One launch, no partials, bitwise
 // reproducible.
 //
@@ -443,11 +444,7 @@ __global__ __launch_bounds__(256) void forward_row_kernel(
             q[d] = load(t + 4 * D);
         }
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double s = wave_sum4(acc[k]);
-        if ((lane & 15) == 0) red[wv][4 * k + quad_of_row(lane >> 4)] = s;
-    }
+    wave_sums<K>(acc, lane, [&](int k, double s) { red[wv][4 * k + quad_of_row(lane >> 4)] = s; });
     __syncthreads();
     // thread 4 k + c stores component c of row i0 + k (c == 3: the potential)
     const int k = threadIdx.x >> 2, c = threadIdx.x & 3;
