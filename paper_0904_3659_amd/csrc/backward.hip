@@ -230,7 +230,7 @@ __global__ __launch_bounds__(BLOCK) void backward_kernel(BwdArgs P)
 // potential weights, whose terms are not formed (bitwise the result of zero
 // weights).
 //
-// Bound by VALU issue (30 operations per ordered pair, 27 without potential
+// Bound by VALU issue (31 operations per ordered pair, 28 without potential
 // weights): 92 cycles per 64 pairs and SIMD at 16,384 bodies with K = 4, about
 // 10 of them the loads.  Per call with potential weights, one row per wave
 // before: 7.4 -> 6.2 us at 2,000 bodies, 11.8 -> 8.9 at 2,500, 13.4 -> 9.6 at
@@ -981,10 +981,9 @@ nbody_status adj_occupancy_half(int *per_cu)
 
 // Sizes at which the bwd_sym_s2 variants run the row-group kernel instead (as
 // kRowBandEnd of the forward).  Whole calls with / without potential weights,
-// pair-once (two waves to a tile) against row groups: 21.1 / 20.4 and 14.6 /
-// 13.2 us at 4,096 bodies, 24.1 / 23.3 and 20.5 / 18.8 at 5,000, 29.9 / 28.8 and
-// 27.3 / 24.9 at 6,001, 31.8 / 30.3 and 33.0 / 30.4 at 6,500; a tile per wave
-// takes 28.2 with them at 6,200.
+// pair-once (1 x 2, a tile per wave) against row groups: 20.9 / 20.4 and 20.5 / 18.3
+// us at 5,000 bodies, 28.0 / 26.4 and 27.1 / 24.5 at 6,001, 28.6 / 27.0 and 31.1 /
+// 28.1 at 6,200, 28.9 / 27.2 and 33.0 / 29.7 at 6,500.
 constexpr int kBwdRowBandBegin = 4000, kBwdRowBandEnd = 6200;
 bool bwd_row_band(int n) { return n >= kBwdRowBandBegin && n < kBwdRowBandEnd; }
 
@@ -1058,12 +1057,14 @@ nbody_status launch_backward_sym(const SymPlan &pl, void *ws, const char *name, 
 //
 // One-wave two-row variants take a tile per wave up to kOneTileEnd, four rows
 // per lane (half the LDS traffic per pair, half the slots to fold) from
-// kOneTileBegin.  Calls with potential weights, chunks of one or two tiles as
-// planned (below 12,000: two waves to a tile) / two rows, a tile per wave / four
-// rows, a tile per wave: 40.2 / 36.1 / 43.7 us at 8,000 bodies, 58.4 / 56.8 /
-// 59.3 at 10,000, 66.4 / 63.7 / 60.9 at 11,000, 126 / 126 / 124 at 16,384, 182 /
-// 182 / 175 at 20,000, 404 / 394 / 371 at 30,000, 660 / 655 / 618 at 39,000,
-// and 1396 / 1399 / 1397 at 60,000.
+// kOneTileBegin.  Calls with potential weights, two rows / four rows, a tile per
+// wave: 36.0 / 45.4 us at 8,000 bodies, 56.7 / 60.7 at 10,000, 63.7 / 61.9 at
+// 11,000; before the slots were emptied within a tile (1-2% less each) 182 / 175
+// at 20,000, 394 / 371 at 30,000, 655 / 618 at 39,000, with chunks of one or two
+// tiles as planned 40.2 us at 8,000, 182 at 20,000, 660 at 39,000.  Four rows, a
+// tile per wave / 2 x 4 (the 4-wave blocks), with and without potential weights:
+// 644 / 646 and 580 / 602 us at 40,000, 802 / 792 and 722 / 733 at 45,000, 1032 /
+// 976 and 951 / 901 at 50,021.
 template <int W, int K, int OCC, int ROUNDS = 1, int KW = W, int KK = K, bool SMALL = false>
 nbody_status run_backward_sym(const char *name, const Device &dev, const float *x, const float *m,
                               int n, float eps2, const float *ga, const float *gp, float *gx,
@@ -1103,9 +1104,10 @@ nbody_status run_backward_sym(const char *name, const Device &dev, const float *
     }
     if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
     // Two-wave blocks of 512 keep at most 52 chunks (partials to write and fold per
-    // row).  As planned / 76 / 52 / 44: 647 / 641 / 633 / 640 us at 40,000 bodies
-    // (104 planned), 867 / 858 / 845 / 849 at 47,000, 975 / 971 / 959 / 959 at
-    // 50,021, 1616 / 1611 / 1604 / 1607 at 65,536.
+    // row).  As planned / 76 / 52 / 44 (before the slots were emptied within a tile:
+    // 1-2% less each): 647 / 641 / 633 / 640 us at 40,000 bodies (104 planned), 867 /
+    // 858 / 845 / 849 at 47,000, 975 / 971 / 959 / 959 at 50,021, 1616 / 1611 / 1604 /
+    // 1607 at 65,536.
     if constexpr (KW == 2 && KK == 4 && ROUNDS > 1) {
         if (pl.C > 52) pl.C = 52;
         // short chunks (up to some 90,000 bodies) hand nothing over in between
@@ -1241,8 +1243,7 @@ int backward_default_variant(int64_t n)
     // out as slots free up: 10-13% ahead of one round of two-wave blocks with
     // potential weights at 49,152 and 60,000, 9-11% of 8-wave ones at 2^17)
     // and 8-wave blocks from 2^18 (3-7% ahead of one round of them at 2^18
-    // and 2^19).  A tile per wave against the 4-wave blocks: 809 / 809 us at
-    // 45,000, 987 / 989 at 50,021.
+    // and 2^19).  A tile per wave against the 4-wave blocks: run_backward_sym.
     if (n >= (1 << 18)) return pair_once_big;
     if (n >= 40000) return pair_once_large;
     if (n >= 24000 && n < 30000) return pair_once_r16;

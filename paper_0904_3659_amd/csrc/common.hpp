@@ -126,8 +126,9 @@ constexpr int kRowAliasBegin = 4096;
 // Sizes at which the one-wave two-row pair-once variants run the row-group
 // kernel instead: the pair-once grid is then one underfilled round of
 // workgroups and a fold of 4-5 us follows it.  Calls with the potential, pair-
-// once (a tile per wave) against row groups: 22.9 / 21.5 us at 8,000 bodies,
-// 26.9 / 26.7 at 9,000, 34.3 / 32.3 at 10,000, 35.3 / 39.1 at 11,000.  Below 4,500
+// once (a tile per wave) against row groups: 27.9 / 21.9 us at 8,000 bodies,
+// 29.1 / 26.5 at 9,000, 34.7 / 32.2 at 10,000, 35.4 / 35.2 at 10,499, 35.7 / 38.7
+// at 11,000 (without it 33.1 / 33.2 at 10,499).  Below 4,500
 // the default variants are row groups by themselves; the band begins at the power
 // of two below, over which a choice of the variant timer holds.
 constexpr int kRowBandBegin = 4096, kRowBandEnd = 10500;

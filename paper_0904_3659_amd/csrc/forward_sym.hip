@@ -134,12 +134,13 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     st = arena.get(dev, stream, pl.bytes(), &ws);
     if (st != NBODY_OK) return st;
     // A tile per one-wave block of 256 particles.  Calls with the potential, row
-    // groups (below 12,000) or planned chunks of 2-4 tiles / a tile per wave:
-    // 32.3 / 34.3 us at 10,000 bodies, 39.1 / 35.3 at 11,000, 50.7 / 47.9 at
-    // 13,000, 71.5 / 69.2 at 16,384, the same from 18,000 to 30,000 (there the
-    // plan has a tile per wave), 246 / 233 at 33,000, 341 / 325 at 39,000, four
-    // waves' blocks of 1,024 / a tile per wave: 373 / 354 at 40,000, 443 / 439 at
-    // 45,000, 500 / 497 at 48,000.
+    // groups / a tile per wave: 32.2 / 34.7 us at 10,000 bodies, 35.2 / 35.4 at
+    // 10,499, 38.7 / 35.7 at 11,000, 44.5 / 42.8 at 12,000; planned chunks of 2-4
+    // tiles / a tile per wave (both with longer slot chains): 50.7 / 47.9 at 13,000,
+    // 71.5 / 69.2 at 16,384, the same from 18,000 to 30,000 (there the plan has a
+    // tile per wave), 246 / 233 at 33,000, 341 / 325 at 39,000; four waves' blocks of
+    // 1,024 / a tile per wave: 373 / 354 at 40,000, 443 / 439 at 45,000, 500 / 497 at
+    // 48,000.
     if constexpr (W == 1 || (W == 4 && K == 4 && KW == 4)) {
         SymPlan one;
         if (n >= kOneTileBegin && n < kOneTileEnd && one_tile_plan(n, 4, pl, &one))
@@ -147,7 +148,7 @@ nbody_status run_sym(const char *name, const Device &dev, const float *x, const 
     }
     if (KW == 1) pl.C = (pl.C + kTileSplit - 1) / kTileSplit;  // counted in workgroups
     // Two-wave blocks of 1,024 keep at most 72 chunks (partials to write and fold
-    // per row).  As planned / 96 / 72 / 52: 541 / 524 / 521 / 558 us at 50,000
+    // per row; the rows' running sums then span up to 16 tiles).  As planned / 96 / 72 / 52: 541 / 524 / 521 / 558 us at 50,000
     // bodies (168 planned), 709 / 699 / 688 / 717 at 60,000, 823 / 819 / 807 /
     // 820 at 65,536, 1203 / 1205 / 1195 / 1196 at 80,000.
     if constexpr (KW == 2 && KK == 8 && ROUNDS > 1) {
@@ -190,9 +191,12 @@ nbody_status forward_sym_run(int W, int K, int occ, int rounds, const char *name
         if (W == 1 && K == 2 && occ == 1) return run_sym<1, 2, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         // Eight rows per lane halve the LDS reads and writes per pair against
         // four (the two take turns in groups of four, so three waves per SIMD
-        // still fit).  Sustained calls: 8 x 4 as 4 x 8 220.1 -> 212.5 ms at 2^20
-        // bodies; 4 x 4 as 2 x 8 874 -> 860 us at 65,536, 1975 -> 1947 at
-        // 100,000, but 358 -> 363 at 40,000, where the workgroups are too few.  Below
+        // still fit).  Sustained calls (before the sums of eight rows were cut
+        // shorter, which takes 0.5-1.5%; above 110,000 bodies 2-3%): 8 x 4 as 4 x 8
+        // 220.1 -> 212.5 ms at 2^20 bodies; 4 x 4 as 2 x 8 874 -> 860 us at 65,536,
+        // 1975 -> 1947 at 100,000, but 358 -> 363 at 40,000, where the workgroups
+        // are too few.  4 x 4 in equal chunks, one barrier more per tile, against 2 x 8
+        // with the shorter sums: 14.2 / 12.6 ms at 2^18, 145 / 136 at 850,000.  Below
         // kOneTileEnd a tile per wave is level or ahead (run_sym).
         if (W == 4 && K == 4 && occ == 1 && n >= kOneTileEnd) return run_sym<4, 4, 1, 8, 2, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);
         if (W == 4 && K == 4 && occ == 1) return run_sym<4, 4, 1, 8>(name, dev, x, m, n, eps2, a, p, stream, epi, fused, arena);

@@ -7,7 +7,7 @@ the attracting body, so the physical acceleration is g = -a and a kick is
 v += (dt/2) g = v - (dt/2) a.  A run of steps is one library call
 (``nbody_leapfrog``): per step the force kernel, then a reduction whose
 epilogue applies the step's end kick, the next step's start kick and its
-drift; the reverse sweep over a segment is one ``nbody_leapfrog_adjoint``
+drift (below 10,500 bodies the force kernel does so itself); the reverse sweep over a segment is one ``nbody_leapfrog_adjoint``
 call in the same way.  Tensors only hold device memory.
 
 Reverse sweep for a loss on the final state.  With adjoints (lx, lv) of the
@@ -28,7 +28,8 @@ step, so the forces at those two positions are never recomputed.  The
 kernels are deterministic, so the recomputed positions and hence the
 gradients are bitwise equal to those of a run that stores every position.
 
-HIP graphs: a k-step segment (2k + 1 launches), the recomputation of a
+HIP graphs: a k-step segment (k + 1 launches below 10,500 bodies, where a step
+is one row-group launch, 2k + 1 above), the recomputation of a
 segment's positions and the reverse sweep over an interior segment are each
 captured once as a HIP graph on fixed device buffers and replayed once per
 segment, instead of issuing every launch from the host.  The graphs run the
@@ -391,14 +392,14 @@ class Leapfrog(torch.autograd.Function):
 
 
 # Largest n for which ``leapfrog(graphs=None)`` replays HIP graphs.  The
-# 64-step gradient with checkpoints every 8 steps takes 11-19% less time
-# with graphs from 128 to 2,048 bodies, where a step's kernels take a few
-# microseconds and the host's launches show; from 3,000 bodies on the
-# eager launches are faster (5% at 3,000, 18% at 4,096, 2-8% at 16,384): a
-# graph's kernel nodes start a little later than launches into a stream,
-# and the eager reverse pass recomputes positions as far ahead of the sweep
-# as the host gets (a tensor per segment) where the graphs have two fixed
-# position buffers.
+# 64-step gradient with checkpoints every 8 steps, graphs / eager: 1.38 / 1.52
+# ms at 128 and 1,024 bodies, 1.40 / 1.46 at 2,000, where a step's kernel takes
+# a few microseconds and the host's launches show.  Above neither leads
+# throughout: 1.72 / 1.58 at 2,500, 1.43 / 1.67 at 3,000, 2.02 / 2.17 at 4,096,
+# 3.03 / 2.87 at 5,000, 5.15 / 4.98 at 8,000.  A graph's kernel nodes start a
+# little later than launches into a stream, and the eager reverse pass
+# recomputes positions as far ahead of the sweep as the host gets (a tensor per
+# segment) where the graphs have two fixed position buffers.
 GRAPHS_MAX_N = 2048
 
 
