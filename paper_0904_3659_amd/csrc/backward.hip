@@ -454,6 +454,7 @@ struct SymBwdArgs {
     int C;
     int d_lo, d_hi;   // ring deltas of this launch's group
     float4 *partial;  // [C + G][n]: (dL/dx, dL/dm)
+    int held;         // held_tiles of the longest chunk
 };
 
 // A lane's row constants in the form the pair terms read (all terms are then
@@ -938,7 +939,7 @@ __global__ __launch_bounds__(kAdjThreads<W>, W == 1 && K == 4 ? 3 : 1) void back
                 }
         }
         if (NB == 2) b ^= 1;
-        if (HELD && ++held == kHeldTiles) hand_over();
+        if (HELD && ++held == A.held) hand_over();
     }
     if constexpr (T == 1) {
         hand_over();
@@ -1020,9 +1021,9 @@ nbody_status launch_backward_sym(const SymPlan &pl, void *ws, const char *name, 
                                 : nullptr;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
-    const int C = pl.C;
+    const int C = pl.C, held = held_tiles(longest_chunk(pl, W * K));
     for (int g = 0; g < pl.groups; ++g) {
-        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, C, 0, 0, partial};
+        SymBwdArgs A{x, m, ga, gp, n, eps2, pl.M, C, 0, 0, partial, held};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (gp)

@@ -16,6 +16,7 @@ struct SymArgs {
     int C;            // chunks per block
     int d_lo, d_hi;   // ring deltas of this launch's group
     float4 *partial;  // [C + G][n]
+    int held;         // held_tiles of the longest chunk
 };
 
 // Waves per workgroup: those of a block, or those that split a one-wave
@@ -38,7 +39,7 @@ __global__ __launch_bounds__(kSymThreads<W>, K == 8 ? 3 : 1) void forward_sym_ke
         __shared__ float4 tile[kSymBuffers<W> * kTileLds];
         __shared__ float4 jacc[kSymBuffers<W> * W][kSlotLds];
         pair_once_block<W, K, false, POT, 1, SHORT, HELD>(A.x, A.m, A.n, A.eps2, A.M, I, c, A.C, A.d_lo, A.d_hi,
-                                          A.partial, tile, jacc);
+                                          A.partial, tile, jacc, A.held);
     }
 }
 
@@ -66,9 +67,9 @@ nbody_status launch_sym(const SymPlan &pl, void *ws, const char *name, const flo
                                 : nullptr;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     const bool lf = epi && epi->mode != kLfNone;
-    const int C = pl.C;
+    const int C = pl.C, held = held_tiles(longest_chunk(pl, W * K));
     for (int g = 0; g < pl.groups; ++g) {
-        SymArgs A{x, m, n, eps2, pl.M, C, 0, 0, partial};
+        SymArgs A{x, m, n, eps2, pl.M, C, 0, 0, partial, held};
         sym_group(pl, g, &A.d_lo, &A.d_hi);
         prof_mark(stream, 0);
         if (p)

@@ -238,6 +238,17 @@ inline int longest_chunk(const SymPlan &pl, int TPB)
     return U <= pl.C ? 1 : 2 + (int)(4LL * (U - pl.C) / (3LL * pl.C));
 }
 
+// Tiles whose sums a row holds in float32 registers before they go to the chunk's
+// partial: a float32 sum over every tile of a long chunk loses more than the rest
+// of a row's sums together (from 64 tiles on; 2^18 bodies).  A hand-over reads and
+// writes a partial per row (every 16 tiles wrote 12.3 GiB at 2^20 bodies, and took
+// 3% of the time at 2^18), so a chunk makes few.
+constexpr int kHeldTiles = 16;
+inline int held_tiles(int longest)
+{
+    return longest < 2 * kHeldTiles ? kHeldTiles : longest > 128 ? 64 : longest / 2;
+}
+
 // Waves that share a one-wave block's chunk: the chunk partials of one-wave
 // blocks were two thirds of what the fold reads (1 tile, 1 partial).  Forward
 // calls with four waves to a partial against one: 86.7 -> 81.5 us at 18,000
@@ -623,11 +634,6 @@ __device__ __forceinline__ void diag_tile_steps(const float (&xi)[K], const floa
     }
 }
 
-// Tiles whose sums a row holds in float32 registers before they go to the
-// chunk's partial: a float32 sum over every tile of a long chunk loses more than
-// the rest of a row's sums together (from 64 tiles on; 2^18 bodies).
-constexpr int kHeldTiles = 16;
-
 // LDS entries of one wave of a tile-split workgroup: the tile and the slots,
 // and at the end K <= 4 rows of row sums.
 constexpr int kWaveLds = kTileLds + kSlotLds;
@@ -669,7 +675,7 @@ constexpr int kSymBuffers = W > 1 ? 2 : 1;
 // before the barrier) and all threads share the sum of the W slot sets, one
 // component each.
 //
-// HELD: chunks of more than kHeldTiles tiles hand their sums over in between.
+// HELD: chunks of more than held_tiles tiles hand their sums over in between.
 // SHORT: ring_tile_short.
 //
 // T > 1 (one-wave blocks): T waves of a workgroup hold the same rows and take
@@ -684,7 +690,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                                                 const float *__restrict__ m, int n, float eps2,
                                                 int M, int I, int c, int C, int d_lo, int d_hi,
                                                 float4 *partial, float4 *tile,
-                                                float4 (*jacc)[kSlotLds])
+                                                float4 (*jacc)[kSlotLds], int held_tiles = 0)
 {
     constexpr int PB = W * 64 * K;   // particles per block
     constexpr int TPB = PB / 64;     // 64-particle tiles per block
@@ -786,7 +792,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
     };
 
     // The row sums so far, added to the chunk's partial: at the end, and every
-    // kHeldTiles tiles before (HELD).
+    // held_tiles tiles before (HELD).
     [[maybe_unused]] int held = 0;
     bool fresh = true;
     const auto hand_over = [&]() {
@@ -910,7 +916,7 @@ __device__ __forceinline__ void pair_once_block(const float *__restrict__ x,
                 }
         }
         if (NB == 2) b ^= 1;
-        if (HELD && ++held == kHeldTiles) hand_over();
+        if (HELD && ++held == held_tiles) hand_over();
     }
 
     if constexpr (T == 1) {
