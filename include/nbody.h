@@ -92,12 +92,14 @@ const char *nbody_last_error(void);
  * the potential; the pair-once kernels then do not form its terms, and a is
  * bitwise the same as with p).
  * Arithmetic: float32 with fused multiply-add, hardware reciprocal square
- * root, and partial sums folded per j-tile (two-level accumulation).
+ * root, and float32 sums of limited length: a j-tile's pairs, then tiles of a
+ * workgroup's share, whose partials are added in float64; in the row groups
+ * below a lane's share of a row, the lanes added in float64.
  * The result is bitwise reproducible for a fixed n, variant and device.
  * Kernels: for 10,500 <= n <= 2^24 the default variant evaluates each
  * unordered pair once and gives the term to both particles (the softened
  * force is antisymmetric in the pair), in blocks of P = 2048 particles from
- * 2^20 up, 1024 from 50,000 and 256 below.  Each block meets
+ * 2^20 up, 1024 from 49,153 and 256 below.  Each block meets
  * the blocks after it on a ring; the ring offsets run in groups, one launch
  * per group, each followed by a launch that adds the group's partial sums
  * to a float64 running sum per particle, so the library workspace stays at
