@@ -757,6 +757,7 @@ nbody_status forward_rows_run(int least, const char *name, const Device &dev, co
     // an update that drifts x needs a second position buffer: the other
     // groups still read x
     if (epi && (p || epi->mode != kLfKick || (epi->drift && !epi->xo))) epi = nullptr;
+    if (!epi && !a) return fail(NBODY_ERROR_INTERNAL, "%s without its result array", name);
     if (epi && fused) *fused = true;
     if (fault_injected("launch")) return fail(NBODY_ERROR_LAUNCH_FAILED, "injected launch fault");
     prof_mark(stream, 0);
