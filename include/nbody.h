@@ -18,9 +18,12 @@
  *   address ranges).
  * - Library workspace (partial sums, work lists) is device memory owned by
  *   the library, cached per (device, stream) and grown on demand; it is held
- *   until nbody_release_workspace() or process exit.  Calls that share one
- *   stream reuse it safely; calls on different streams use different
- *   workspaces.
+ *   until nbody_release_workspace() or process exit.  Calls that one host
+ *   thread makes on a stream reuse it safely; calls on different streams use
+ *   different workspaces.  Host threads that call at the same time need a
+ *   stream each, except for calls that take no workspace: with the automatic
+ *   choice nbody_forces and nbody_leapfrog below 10,500 bodies,
+ *   nbody_forces_backward below 6,200, and the element-wise calls.
  * - HIP graph capture: nbody_forces, nbody_forces_ex, nbody_forces_backward,
  *   nbody_forces_batched, nbody_axpy, nbody_kick_drift, nbody_leapfrog and
  *   nbody_leapfrog_adjoint may be captured on a stream once the same call
